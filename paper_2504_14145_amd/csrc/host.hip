@@ -88,27 +88,28 @@ void release_memopt(dip_sim *h) {
 }
 
 void release_greedy(dip_sim *h) {
-  if (h->d_gr_caller) (void)hipFree(h->d_gr_caller);
   if (h->d_gr_src) (void)hipFree(h->d_gr_src);
   if (h->d_gr_rec) (void)hipFree(h->d_gr_rec);
   if (h->d_gr_succ) (void)hipFree(h->d_gr_succ);
   if (h->h_gr_stage) (void)hipHostFree(h->h_gr_stage);
-  if (h->d_gr_retry) (void)hipFree(h->d_gr_retry);
-  if (h->d_gr_retry_count) (void)hipFree(h->d_gr_retry_count);
+  if (h->d_gr_spills) (void)hipFree(h->d_gr_spills);
   if (h->h_gr_seen) (void)hipHostFree(h->h_gr_seen);
   if (h->gr_seen_ev) (void)hipEventDestroy(h->gr_seen_ev);
   if (h->d_gr_ring) (void)hipFree(h->d_gr_ring);
+  if (h->d_gr_joins) (void)hipFree(h->d_gr_joins);
   h->d_gr_ring = nullptr;
   h->gr_ring_bytes = 0;
+  h->d_gr_joins = nullptr;
+  h->gr_join_bytes = 0;
   h->h_gr_seen = nullptr;
   h->gr_seen_ev = nullptr;
   h->gr_seen_pending = false;
-  h->d_gr_caller = h->d_gr_src = nullptr;
+  h->gr_seen_last = 0;
+  h->gr_seen_n = h->gr_unseen_n = 0;
+  h->d_gr_src = nullptr;
   h->d_gr_rec = h->d_gr_succ = nullptr;
   h->h_gr_stage = nullptr;
-  h->d_gr_retry = nullptr;
-  h->d_gr_retry_count = nullptr;
-  h->gr_retry_cap = 0;
+  h->d_gr_spills = nullptr;
   h->gr_ok = h->gr_costs_ok = false;
 }
 
@@ -348,7 +349,7 @@ int dip_sim_get_info(const dip_sim *h, dip_sim_info *info) {
   info->pool_slots = v >= 8 ? h->pool_slots : 0;
   info->check_kernel = v >= 8 ? check_kind(h) : 0;
   info->greedy_inbox = h->gr_ok ? (h->gr_direct ? -1 : h->gr_K) : 0;
-  info->greedy_lds_bytes = h->gr_ok ? int32_t(h->gr_main.lds) : 0;
+  info->greedy_lds_bytes = h->gr_ok ? int32_t(h->gr_dense.lds) : 0;
   info->greedy_retry_ring_bytes = h->gr_ok ? h->gr_ring_bytes : 0;
   return DIP_OK;
 }

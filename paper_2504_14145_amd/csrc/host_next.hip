@@ -8,41 +8,103 @@ using namespace dipsim_host;
 
 namespace dipsim_host {
 
-bool greedy_layout(const dip_sim *h, int K, int pwl, dip_sim::GrLaunch *L, bool gring) {
+// The inbox sizes a grouping accepts: rings of K stages per rank and kind,
+// with the per-group tables and join accumulators, for a whole wave's
+// candidates within a block's LDS.  (The launches keep K / 2 of them in LDS
+// and go on in device memory, so they always fit; dip_sim_set_greedy_inbox
+// and the growth below stay within this bound.)
+bool greedy_inbox_fits(const dip_sim *h, int64_t K, int pwl) {
   const int64_t G = h->gr_G, P = h->P, J = h->gr_J;
-  L->pwl = pwl;
-  L->K = K;
-  L->wpb = 1;
-  L->gring = gring;
-  L->max_blocks = 0;
-  // two rings per rank (none in LDS with gring); two head/count words per
-  // lane (padding lanes' stay 0)
   const int64_t lanes = int64_t(1) << pwl;
-  const int64_t rings = gring ? 0 : P * (2 * K + 1) * 8;
-  L->off_pend = 0;
-  L->off_npend = int32_t(rings);
-  L->off_join = int32_t(rings + 8 * lanes);
-  const int64_t head = align16(std::max<int64_t>(4 * G, L->off_join + 8 * J));
-  L->off_gpos = int32_t(head);
-  L->off_ord = int32_t(head + align16(2 * G));
-  L->off_grk = int32_t(head + 2 * align16(2 * G));
-  // (wide E sets, 32 words, sit in LDS after the tables: each lane
-  // of the candidate two sets of gr_nw words)
+  const int64_t off_join = P * (2 * K + 1) * 8 + 8 * lanes;
+  const int64_t head = align16(std::max<int64_t>(4 * G, off_join + 8 * J));
   const int64_t ebits = h->gr_nw >= 32 ? lanes * 16 * int64_t(h->gr_nw) : 0;
-  L->cand_bytes = int32_t(head + 3 * align16(2 * G) + ebits);
-  L->lds = h->gr_meta_bytes + int64_t(kWave >> pwl) * L->cand_bytes;
+  const int64_t cand = head + 3 * align16(2 * G) + ebits;
+  return align16(2 * G) + int64_t(kWave >> pwl) * cand <= h->lds_block_max;
+}
+
+// LDS plan of a greedy launch: per candidate the bitmaps, rings, messages and
+// join accumulators overlay the priorities, which only the set-up reads; then
+// group -> priority rank and back.
+static bool greedy_layout(const dip_sim *h, int kl, bool wide, bool joins_dev,
+                          dip_sim::GrLaunch *L) {
+  const int64_t G = h->gr_G, P = h->P, J = h->gr_J;
+  const int64_t nwd = (G + 63) / 64;
+  L->kl = kl;
+  L->joins_dev = joins_dev;
+  const int64_t ring = P * (2 * nwd + 1) * 8;
+  const int64_t msg = ring + P * (2 * int64_t(kl) + 1) * 8;
+  const int64_t join = msg + (int64_t(16) << h->gr_rwl);
+  const int64_t head =
+      align16(std::max<int64_t>(4 * ((G + 3) & ~int64_t(3)), join + (joins_dev ? 0 : 8 * J)));
+  const int64_t tab = align16(2 * G);
+  L->off_ring = int32_t(ring);
+  L->off_msg = int32_t(msg);
+  L->off_join = int32_t(join);
+  L->off_qof = int32_t(head);
+  L->off_gof = int32_t(head + tab);
+  L->cand_bytes = int32_t(head + 2 * tab);
+  L->lds = (wide ? 1 : int64_t(kWave >> h->gr_rwl)) * int64_t(L->cand_bytes);
+  L->blocks_per_cu = 0;
   if (L->lds > h->lds_block_max) return false;
+  const void *k = greedy_kernel_ptr(h->gr_rwl, wide);
   int bpc = 0;
-  const void *k = greedy_kernel_ptr(pwl, h->gr_nw, gring);
   if (!k || (L->lds > 65536 && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    int(L->lds)) != hipSuccess) ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k, kWave * L->wpb,
-                                                   size_t(L->lds)) != hipSuccess) {
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc, k, kWave, size_t(L->lds)) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  L->blocks_per_cu = std::max(1, bpc);
-  return true;
+  L->blocks_per_cu = bpc;
+  return bpc > 0;
+}
+
+// Both launch shapes for the current inbox size: K / 2 ring entries in LDS
+// (with the first one in a register and a run of equal times beside the
+// ring, as many stages again), 4 where most candidates spill anyway.  Fewer
+// where they do not fit, and then the join accumulators in device memory.
+bool greedy_plan(dip_sim *h) {
+  const int want = h->gr_direct ? 4 : std::max(1, h->gr_K / 2);
+  for (int wide = 0; wide < 2; ++wide) {
+    dip_sim::GrLaunch &L = wide ? h->gr_wide : h->gr_dense;
+    bool ok = false;
+    for (int jd = 0; jd < 2 && !ok; ++jd)
+      for (int kl = want; kl >= 1 && !ok; kl /= 2) ok = greedy_layout(h, kl, wide != 0, jd != 0, &L);
+    if (!ok) L.blocks_per_cu = 0;
+  }
+  return h->gr_dense.blocks_per_cu > 0 || h->gr_wide.blocks_per_cu > 0;
+}
+
+// Device memory of the rings (and joins) for `slots` resident candidates
+static int ensure_greedy_slots(dip_sim *h, int64_t slots, bool joins) {
+  const int64_t rings = slots * h->P * 2 * int64_t(h->gr_kg) * 8;
+  if (rings > h->gr_ring_bytes) {
+    if (h->d_gr_ring) DIP_HIP(hipFree(h->d_gr_ring));
+    h->d_gr_ring = nullptr;
+    h->gr_ring_bytes = 0;
+    DIP_HIP(hipMalloc(&h->d_gr_ring, size_t(rings)));
+    h->gr_ring_bytes = rings;
+  }
+  const int64_t jb = joins ? slots * int64_t(h->gr_J) * 8 : 0;
+  if (jb > h->gr_join_bytes) {
+    if (h->d_gr_joins) DIP_HIP(hipFree(h->d_gr_joins));
+    h->d_gr_joins = nullptr;
+    h->gr_join_bytes = 0;
+    DIP_HIP(hipMalloc(&h->d_gr_joins, size_t(jb)));
+    h->gr_join_bytes = jb;
+  }
+  return DIP_OK;
+}
+
+// Resident candidate slots of a launch shape: what the CUs hold, within 1 GiB
+// of rings.
+static int64_t greedy_slots(const dip_sim *h, bool wide) {
+  const dip_sim::GrLaunch &L = wide ? h->gr_wide : h->gr_dense;
+  const int64_t gw = wide ? 1 : kWave >> h->gr_rwl;
+  const int64_t per = h->P * 2 * int64_t(h->gr_kg) * 8 * gw;
+  const int64_t blocks = std::max<int64_t>(
+      1, std::min<int64_t>(int64_t(h->n_cu) * L.blocks_per_cu, (int64_t(1) << 30) / per));
+  return L.blocks_per_cu > 0 ? blocks * gw : 0;
 }
 
 }  // namespace dipsim_host
@@ -91,16 +153,8 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
     }
     if (seen != N) return DIP_E_TOPO;
   }
-  // internal numbering: forward groups (and empty ones), then backward groups
-  std::vector<int32_t> caller, internal(n_groups);
-  for (int pass = 0; pass < 2; ++pass)
-    for (int32_t q = 0; q < n_groups; ++q)
-      if ((gk[q] == 1) == (pass == 1)) {
-        internal[q] = int32_t(caller.size());
-        caller.push_back(q);
-      }
   int32_t GF = 0;
-  while (GF < n_groups && gk[caller[GF]] != 1) ++GF;
+  for (int32_t q = 0; q < n_groups; ++q) GF += gk[q] == 1 ? 0 : 1;
   const int32_t wmax = (std::max(GF, n_groups - GF) + 63) / 64;
   int nw = 1;
   while (nw < wmax) nw *= 2;
@@ -110,14 +164,9 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
   release_rollouts(h);             // the classes belong to the old grouping
   release_greedy(h);
   h->gr_G = n_groups;
-  h->gr_GF = GF;
   h->gr_nw = nw;
-  h->gr_ig.assign(N, 0);
-  h->gr_op.assign(int64_t(n_groups) * P, -1);
-  for (int32_t g = 0; g < N; ++g) {
-    h->gr_ig[g] = internal[op_group[g]];
-    h->gr_op[int64_t(h->gr_ig[g]) * P + h->rank_of[g]] = g;
-  }
+  h->gr_ig.assign(op_group, op_group + N);
+  h->gr_op = at;
   h->gr_join.assign(N, -1);
   h->gr_J = 0;
   for (int32_t g = 0; g < N; ++g)
@@ -128,44 +177,32 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
   h->gr_n_extra = 0;
   for (int32_t g = 0; g < N; ++g) h->gr_n_extra += std::max(succ_ptr[g + 1] - succ_ptr[g] - 1, 0);
   std::vector<int32_t> src(P + 1, 0), src_list;
-  h->gr_max_nr = 0;
   for (int32_t r = 0; r < P; ++r) {
-    h->gr_max_nr = std::max(h->gr_max_nr, h->n_ops[r]);
     for (int32_t g = h->rank_off[r]; g < h->rank_off[r + 1]; ++g)
-      if (h->pred_ptr[g + 1] == h->pred_ptr[g]) src_list.push_back(h->gr_ig[g]);
+      if (h->pred_ptr[g + 1] == h->pred_ptr[g])
+        src_list.push_back(h->gr_ig[g] | (int32_t(h->kind[g]) << 16));
     src[r + 1] = int32_t(src_list.size());
   }
   src.insert(src.end(), src_list.begin(), src_list.end());
-  h->gr_meta_bytes = int32_t(align16(2 * int64_t(n_groups)));
-  // inboxes of 8 stages per kind to start with; the second launch sizes them
-  // to a whole rank
-  const int pwl = std::max(2, h->pwl);
+  // inboxes of 8 stages per kind to start with
+  h->gr_rwl = std::max(2, h->pwl);
   h->gr_K = 8;
   h->gr_K_fixed = false;
   h->gr_direct = false;
-  if (!greedy_layout(h, h->gr_K, pwl, &h->gr_main)) return DIP_E_UNSUPPORTED;
-  // a stage joins its rank's inbox of its kind once, so a ring of a power
-  // of two entries no fewer than the rank's stages of that kind never fills
+  if (!greedy_inbox_fits(h, h->gr_K, h->gr_rwl) || !greedy_plan(h)) return DIP_E_UNSUPPORTED;
+  // a stage joins its rank's ring of its kind once
   int32_t most = 1;
   {
     std::vector<int32_t> per(2 * int64_t(P), 0);
     for (int32_t g = 0; g < N; ++g) most = std::max(most, ++per[2 * h->rank_of[g] + h->kind[g]]);
   }
+  h->gr_kg = most;
+  // device rings at once where a whole rank's inboxes could not sit in LDS
+  // (they will be used), else with the first call
   int kr = 1;
   while (kr < most) kr *= 2;
-  if (kr > 0x8000) return DIP_E_UNSUPPORTED;      // 16-bit ring heads and counts
-  int pr = pwl;
-  while (pr <= 6 && !greedy_layout(h, kr, pr, &h->gr_retry)) ++pr;
-  int64_t ring_bytes = 0;
-  if (pr > 6) {
-    // rings in device memory, one region per resident candidate slot; at
-    // most 1 GiB of them (fewer resident blocks if need be)
-    if (!greedy_layout(h, kr, pwl, &h->gr_retry, true)) return DIP_E_UNSUPPORTED;
-    const int64_t per_block = int64_t(h->gr_retry.wpb) * (kWave >> pwl) * P * (2 * int64_t(kr) + 1) * 8;
-    const int64_t want = int64_t(h->n_cu) * h->gr_retry.blocks_per_cu;
-    h->gr_retry.max_blocks = int(std::max<int64_t>(1, std::min<int64_t>(want, (int64_t(1) << 30) / per_block)));
-    ring_bytes = int64_t(h->gr_retry.max_blocks) * per_block;
-  }
+  bool lds_whole = false;
+  for (int w = h->gr_rwl; w <= 6 && !lds_whole; ++w) lds_whole = greedy_inbox_fits(h, kr, w);
 
   auto fail = [&](hipError_t e) {
     g_last_hip = e;
@@ -175,21 +212,23 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
   hipError_t e;
   const int64_t rec_bytes = int64_t(n_groups) * P * 32;
   const int64_t ext_bytes = int64_t(std::max(h->gr_n_extra, 1)) * 16;
-  if ((e = hipMalloc(&h->d_gr_caller, size_t(n_groups) * 4)) != hipSuccess) return fail(e);
   if ((e = hipMalloc(&h->d_gr_src, src.size() * 4)) != hipSuccess) return fail(e);
   if ((e = hipMalloc(&h->d_gr_rec, size_t(rec_bytes))) != hipSuccess) return fail(e);
   if ((e = hipMalloc(&h->d_gr_succ, size_t(ext_bytes))) != hipSuccess) return fail(e);
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&h->h_gr_stage), size_t(rec_bytes + ext_bytes),
                          hipHostMallocDefault)) != hipSuccess)
     return fail(e);
-  if ((e = hipMemcpy(h->d_gr_caller, caller.data(), size_t(n_groups) * 4, hipMemcpyHostToDevice)) !=
-      hipSuccess)
-    return fail(e);
   if ((e = hipMemcpy(h->d_gr_src, src.data(), src.size() * 4, hipMemcpyHostToDevice)) != hipSuccess)
     return fail(e);
-  if (ring_bytes > 0) {
-    if ((e = hipMalloc(&h->d_gr_ring, size_t(ring_bytes))) != hipSuccess) return fail(e);
-    h->gr_ring_bytes = ring_bytes;
+  if ((e = hipMalloc(&h->d_gr_spills, 16)) != hipSuccess) return fail(e);
+  if ((e = launch_zero_words(h->d_gr_spills, 1, nullptr)) != hipSuccess) return fail(e);
+  if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return fail(e);
+  if (!lds_whole) {
+    const int rc = ensure_greedy_slots(h, int64_t(h->n_cu), false);
+    if (rc != DIP_OK) {
+      release_greedy(h);
+      return rc;
+    }
   }
   h->gr_ok = true;
   h->gr_costs_ok = false;
@@ -214,30 +253,35 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
        reinterpret_cast<uintptr_t>(out_bubble) | reinterpret_cast<uintptr_t>(out_peakmem)) & 3)
     return DIP_E_INVAL;
   if (reinterpret_cast<uintptr_t>(out_orders) & 1) return DIP_E_INVAL;
-  if (h->gr_retry_cap < n_cand) {
-    if (h->d_gr_retry) (void)hipFree(h->d_gr_retry);
-    h->d_gr_retry = nullptr;
-    h->gr_retry_cap = 0;
-    DIP_HIP(hipMalloc(&h->d_gr_retry, size_t(n_cand) * 8));
-    h->gr_retry_cap = n_cand;
-  }
-  if (!h->d_gr_retry_count) DIP_HIP(hipMalloc(&h->d_gr_retry_count, 16));
   if (h->gr_seen_pending && hipEventQuery(h->gr_seen_ev) == hipSuccess) {
-    // an earlier call's overflow count: more than 1/64 of its candidates
-    // doubles the first launch's inboxes while they fit LDS; more than half of
-    // them at the largest inbox that fits makes later calls skip the first
-    // launch (it would run them all only for the second to run them again)
+    // earlier calls' spill count: more than 1/64 of their candidates doubles
+    // the inboxes while they fit; more than half of them at the largest size
+    // gives the LDS back and leaves the rings to device memory
     h->gr_seen_pending = false;
-    dip_sim::GrLaunch bigger;
-    const int64_t seen = int64_t(*h->h_gr_seen);
-    if (!h->gr_K_fixed && seen * 64 > h->gr_seen_n) {
-      if (h->gr_K < 256 && greedy_layout(h, 2 * h->gr_K, h->gr_main.pwl, &bigger)) {
+    const int64_t seen = int64_t(uint32_t(*h->h_gr_seen - h->gr_seen_last));
+    h->gr_seen_last = *h->h_gr_seen;
+    if (!h->gr_K_fixed && !h->gr_direct && seen * 64 > h->gr_seen_n) {
+      if (h->gr_K < 256 && greedy_inbox_fits(h, 2 * h->gr_K, h->gr_rwl)) {
         h->gr_K *= 2;
-        h->gr_main = bigger;
+        (void)greedy_plan(h);
       } else if (seen * 2 > h->gr_seen_n) {
         h->gr_direct = true;
+        (void)greedy_plan(h);
       }
     }
+  }
+  // a wave per candidate while every one is resident at once and the SIMDs
+  // hold at most two waves each; else 64 >> rwl candidates a wave
+  const int64_t slots_w = greedy_slots(h, true), slots_d = greedy_slots(h, false);
+  const bool wide = slots_d == 0 || (n_cand <= slots_w && n_cand <= 8 * int64_t(h->n_cu));
+  const dip_sim::GrLaunch &L = wide ? h->gr_wide : h->gr_dense;
+  const int64_t gw = wide ? 1 : kWave >> h->gr_rwl;
+  const int64_t blocks = std::min<int64_t>((n_cand + gw - 1) / gw, (wide ? slots_w : slots_d) / gw);
+  {
+    // (and what any smaller batch would take, so that it allocates nothing)
+    const int64_t need = std::max(blocks * gw, std::min<int64_t>(n_cand, slots_w));
+    const int rc = ensure_greedy_slots(h, need, L.joins_dev);
+    if (rc != DIP_OK) return rc;
   }
   (void)hipGetLastError();
   h->prof_n = 0;
@@ -247,7 +291,6 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
     return hipEventRecord(h->prof_ev[i], stream);
   };
   (void)hipGetLastError();
-  DIP_HIP(launch_zero_words(h->d_gr_retry_count, 1, stream));
   GreedyArgs a{};
   a.prio = prio;
   a.n_cand = n_cand;
@@ -259,67 +302,44 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
   a.out_flags = out_flags;
   a.rec = h->d_gr_rec;
   a.succ = h->d_gr_succ;
-  a.caller = h->d_gr_caller;
   a.src = h->d_gr_src;
   a.rank_off = h->d_rank_off;
   a.busy = h->d_busy;
   a.cap = h->d_cap;
   a.P = h->P;
   a.G = h->gr_G;
-  a.GF = h->gr_GF;
   a.J = h->gr_J;
-  a.n_rounds = h->N;
+  a.n_stages = h->N;
   a.has_cap = 0;
   for (int r = 0; r < h->P; ++r) a.has_cap |= h->cap[r] >= 0 ? 1 : 0;
-  a.meta_bytes = h->gr_meta_bytes;
-  auto set_layout = [&](const dip_sim::GrLaunch &L) {
-    a.K = L.K;
-    a.wpb = L.wpb;
-    a.cand_bytes = L.cand_bytes;
-    a.off_pend = L.off_pend;
-    a.off_npend = L.off_npend;
-    a.off_join = L.off_join;
-    a.off_gpos = L.off_gpos;
-    a.off_ord = L.off_ord;
-    a.off_grk = L.off_grk;
-  };
-  set_layout(h->gr_main);
-  a.retry = h->d_gr_retry;
-  a.retry_count = h->d_gr_retry_count;
-  const int64_t per_block = int64_t(h->gr_main.wpb) * (kWave >> h->gr_main.pwl);
-  const int64_t blocks = (n_cand + per_block - 1) / per_block;
-  if (blocks > INT32_MAX) return DIP_E_INVAL;
+  a.nwd = (h->gr_G + 63) / 64;
+  a.kl = L.kl;
+  a.kg = h->gr_kg;
+  a.cand_bytes = L.cand_bytes;
+  a.off_ring = L.off_ring;
+  a.off_msg = L.off_msg;
+  a.off_join = L.off_join;
+  a.off_qof = L.off_qof;
+  a.off_gof = L.off_gof;
+  a.dring = h->d_gr_ring;
+  a.joins_dev = L.joins_dev ? h->d_gr_joins : nullptr;
+  a.spill_count = h->gr_K_fixed || h->gr_direct ? nullptr : h->d_gr_spills;
   DIP_HIP(mark(0));
-  if (!h->gr_direct)
-    DIP_HIP(launch_greedy(h->gr_main.pwl, h->gr_nw, false, int(blocks), h->gr_main.wpb,
-                          size_t(h->gr_main.lds), stream, a));
+  DIP_HIP(launch_greedy(h->gr_rwl, wide, int(blocks), size_t(L.lds), stream, a));
   DIP_HIP(mark(1));
-  // candidates whose inboxes overflowed (or, skipping the first launch, all
-  // of them), with inboxes as large as a rank
-  set_layout(h->gr_retry);
-  a.list = h->gr_direct ? nullptr : h->d_gr_retry;
-  a.list_count = h->gr_direct ? nullptr : h->d_gr_retry_count;
-  a.retry = nullptr;
-  a.retry_count = nullptr;
-  const int64_t per_block_r = int64_t(h->gr_retry.wpb) * (kWave >> h->gr_retry.pwl);
-  int64_t rb = std::min<int64_t>(int64_t(h->n_cu) * h->gr_retry.blocks_per_cu,
-                                 h->gr_direct ? (n_cand + per_block_r - 1) / per_block_r : blocks);
-  if (h->gr_retry.gring) {
-    rb = std::min<int64_t>(rb, h->gr_retry.max_blocks);   // one ring region per resident slot
-    a.gring = h->d_gr_ring;
-  }
-  DIP_HIP(launch_greedy(h->gr_retry.pwl, h->gr_nw, h->gr_retry.gring, int(rb), h->gr_retry.wpb,
-                        size_t(h->gr_retry.lds), stream, a));
-  DIP_HIP(mark(2));
-  if (!h->gr_K_fixed && !h->gr_direct && !h->gr_seen_pending) {
-    if (!h->h_gr_seen) {
-      DIP_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_gr_seen), 16, hipHostMallocDefault));
-      DIP_HIP(hipEventCreateWithFlags(&h->gr_seen_ev, hipEventDisableTiming));
+  if (a.spill_count) {
+    h->gr_unseen_n += n_cand;
+    if (!h->gr_seen_pending) {
+      if (!h->h_gr_seen) {
+        DIP_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_gr_seen), 16, hipHostMallocDefault));
+        DIP_HIP(hipEventCreateWithFlags(&h->gr_seen_ev, hipEventDisableTiming));
+      }
+      DIP_HIP(hipMemcpyAsync(h->h_gr_seen, h->d_gr_spills, 4, hipMemcpyDeviceToHost, stream));
+      DIP_HIP(hipEventRecord(h->gr_seen_ev, stream));
+      h->gr_seen_pending = true;
+      h->gr_seen_n = h->gr_unseen_n;
+      h->gr_unseen_n = 0;
     }
-    DIP_HIP(hipMemcpyAsync(h->h_gr_seen, h->d_gr_retry_count, 4, hipMemcpyDeviceToHost, stream));
-    DIP_HIP(hipEventRecord(h->gr_seen_ev, stream));
-    h->gr_seen_pending = true;
-    h->gr_seen_n = n_cand;
   }
   return DIP_OK;
 }
@@ -328,13 +348,11 @@ int dip_sim_set_greedy_inbox(dip_sim *h, int32_t k) {
   if (!h || k < 0 || k > 256 || (k & (k - 1)) != 0) return DIP_E_INVAL;
   if (!h->gr_ok) return DIP_E_STATE;
   const int kk = k ? k : 8;
-  dip_sim::GrLaunch L;
-  if (!greedy_layout(h, kk, h->gr_main.pwl, &L)) return DIP_E_UNSUPPORTED;
+  if (!greedy_inbox_fits(h, kk, h->gr_rwl)) return DIP_E_UNSUPPORTED;
   h->gr_K = kk;
-  h->gr_main = L;
   h->gr_K_fixed = k != 0;
   h->gr_direct = false;
-  return DIP_OK;
+  return greedy_plan(h) ? DIP_OK : DIP_E_UNSUPPORTED;
 }
 
 int dip_sim_configure_rollouts(dip_sim *h, int32_t n_classes, const int32_t *group_class) {

@@ -177,44 +177,42 @@ struct dip_sim {
   // greedy stage interleaving (dip_sim_configure_greedy / dip_sim_greedy)
   bool gr_ok = false;                  // groups configured
   bool gr_costs_ok = false;            // records hold the current costs
-  int32_t gr_G = 0, gr_GF = 0, gr_J = 0, gr_max_nr = 0;
-  int gr_pwl = 3, gr_nw = 1;
-  std::vector<int32_t> gr_op;          // [G*P] global op of (internal group, rank), -1 none
-  std::vector<int32_t> gr_ig;          // [N] internal group of each op
+  int32_t gr_G = 0, gr_J = 0;
+  int gr_rwl = 3;                      // log2 of the lanes playing ranks
+  int gr_nw = 1;                       // 64-group words of the larger kind, a power of two
+  std::vector<int32_t> gr_op;          // [G*P] global op of (group, rank), -1 none
+  std::vector<int32_t> gr_ig;          // [N] group of each op
   std::vector<int32_t> gr_join;        // [N] join index of an op with several predecessors
   std::vector<int32_t> gr_succ_ptr;    // [N+1] successors of each op ...
   std::vector<int32_t> gr_succ_op;     // ... and the edge they come through
   std::vector<int32_t> gr_succ_edge;
   int32_t gr_n_extra = 0;              // successors after each op's first
-  int32_t *d_gr_caller = nullptr;      // [G]
-  int32_t *d_gr_src = nullptr;         // [P+1] offsets, then the source groups
+  int32_t *d_gr_src = nullptr;         // [P+1] offsets, then the sources: group | kind << 16
   int4 *d_gr_rec = nullptr;            // [G*P*2]
   int4 *d_gr_succ = nullptr;           // [max(extra, 1)]
   unsigned char *h_gr_stage = nullptr; // pinned staging of the records
-  int64_t *d_gr_retry = nullptr;
-  uint32_t *d_gr_retry_count = nullptr;
-  int64_t gr_retry_cap = 0;
-  // adaptive inbox size: a call's retry count is copied back asynchronously
-  // and read by a later call, which doubles the inboxes when more than 1/64
-  // of its candidates needed the second launch
-  int gr_K = 16;
+  // adaptive inbox size: the running count of candidates whose rings went on
+  // into device memory is copied back asynchronously and read by a later call
+  uint32_t *d_gr_spills = nullptr;
+  int gr_K = 8;
   bool gr_K_fixed = false;             // dip_sim_set_greedy_inbox fixed it
-  bool gr_direct = false;              // later calls run only the whole-rank-inbox launch
+  bool gr_direct = false;              // most candidates spill at the largest size: small rings
   uint32_t *h_gr_seen = nullptr;       // pinned
   hipEvent_t gr_seen_ev = nullptr;
   bool gr_seen_pending = false;
-  int64_t gr_seen_n = 0;
+  uint32_t gr_seen_last = 0;           // the count at the last look
+  int64_t gr_seen_n = 0, gr_unseen_n = 0;   // candidates since then: in the copy, after it
   struct GrLaunch {
-    int pwl = 3, wpb = 1, K = 8, blocks_per_cu = 1;
-    bool gring = false;                // inboxes in device memory (d_gr_ring)
-    int max_blocks = 0;                // gring: blocks the ring memory has slots for
-    int32_t cand_bytes = 0, off_pend = 0, off_npend = 0, off_join = 0, off_gpos = 0,
-            off_ord = 0, off_grk = 0;
+    int kl = 4, blocks_per_cu = 0;
+    bool joins_dev = false;            // join accumulators in device memory
+    int32_t cand_bytes = 0, off_ring = 0, off_msg = 0, off_join = 0, off_qof = 0, off_gof = 0;
     int64_t lds = 0;
-  } gr_main, gr_retry;
-  int32_t gr_meta_bytes = 0;
-  uint64_t *d_gr_ring = nullptr;       // retry launch's inboxes when LDS cannot hold them
+  } gr_dense, gr_wide;                 // 64 >> rwl candidates a wave; one
+  int32_t gr_kg = 1;                   // device ring entries per rank and kind
+  uint64_t *d_gr_ring = nullptr;       // rings beyond LDS, per resident candidate slot
   int64_t gr_ring_bytes = 0;
+  uint32_t *d_gr_joins = nullptr;
+  int64_t gr_join_bytes = 0;
   // MCTS rollouts (dip_sim_configure_rollouts / dip_sim_rollouts)
   bool rl_ok = false;
   int32_t rl_n = 0;                    // classes
@@ -295,7 +293,8 @@ int upload_greedy_records(dip_sim *h, const dip_costs *c, hipStream_t stream);
 int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const StageLayout &L,
                       hipStream_t stream);
 int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream);
-bool greedy_layout(const dip_sim *h, int K, int pwl, dip_sim::GrLaunch *L, bool gring = false);
+bool greedy_inbox_fits(const dip_sim *h, int64_t K, int pwl);
+bool greedy_plan(dip_sim *h);
 void release_rollout_memopt(dip_sim *h);
 void release_rollouts(dip_sim *h);
 void release_memopt(dip_sim *h);

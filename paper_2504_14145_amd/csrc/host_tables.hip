@@ -33,9 +33,9 @@ StageLayout stage_layout(const dip_sim *h) {
   return L;
 }
 
-// Greedy records per (internal group, rank): {cost, act, local id |
+// Greedy records per (group, rank): {cost, act, local id |
 // successors << 16, index of the second successor}, then the first successor
-// {internal group | kind << 16 | rank << 17, comm, join index or -1, the
+// {group | kind << 16 | rank << 17, comm, join index or -1, the
 // join's predecessor count}; further successors in the same 16-byte form.
 // The staging area is guarded by the caller's wait on stage_done.
 int upload_greedy_records(dip_sim *h, const dip_costs *c, hipStream_t stream) {
@@ -269,10 +269,5 @@ int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream) {
   h->costs_set = true;
   return DIP_OK;
 }
-
-// LDS plan of one greedy candidate with inboxes of K entries: the inboxes,
-// their counts and the join accumulators overlay the priorities, which only
-// the set-up reads; then positions, position -> group and position -> global
-// rank (16-bit each).
 
 }  // namespace dipsim_host

@@ -334,7 +334,7 @@ hipError_t launch_sim(int pwl, int slots, bool paged, int blocks, int wpb, size_
 // order; "position" is a group's rank among the groups of its kind under the
 // candidate's priorities.
 struct GreedyArgs {
-  const int32_t *prio;      // [n_cand][G] caller-indexed priorities
+  const int32_t *prio;      // [n_cand][G] priorities
   int64_t n_cand;
   int16_t *out_orders;      // [n_cand][stride] or null
   int64_t stride;
@@ -342,38 +342,34 @@ struct GreedyArgs {
   int32_t *out_bub;
   int32_t *out_peak;
   uint8_t *out_flags;
-  const int4 *rec;          // [G][P][2] per (internal group, rank):
+  const int4 *rec;          // [G][P][2] per (group, rank):
                             //   {cost, act, local id | successors << 16 (0xffff: no stage),
                             //    index of the second successor in succ},
                             //   {first successor: word, comm, join or -1, join's predecessors}
   const int4 *succ;         // further successors, same form as the second half of rec
-  const int32_t *caller;    // [G] caller index of each internal group
-  const int32_t *src;       // [P+1] offsets, then the internal groups of each rank's sources
+  const int32_t *src;       // [P+1] offsets, then each rank's sources: group | kind << 16
   const int32_t *rank_off;  // [P+1]
   const int32_t *busy;      // [P]
   const int32_t *cap;       // [P]
-  int32_t P, G, GF, J, K, wpb;
-  int32_t n_rounds;         // N: every round schedules one stage of every candidate
+  int32_t P, G, J;
+  int32_t n_stages;         // N
   int32_t has_cap;          // some rank has a cap
-  int32_t meta_bytes;       // block-shared LDS: caller index of each group (u16)
+  int32_t nwd;              // 64-bit words of a priority-rank bitmap
+  int32_t kl, kg;           // ring entries per rank and kind in LDS (a power of two), in dring
   int32_t cand_bytes;       // LDS per candidate, 16-aligned
-  int32_t off_gpos, off_ord, off_grk, off_pend, off_npend, off_join;  // within a candidate
-  const int64_t *list;      // list mode: candidates list[0 .. *list_count-1]
-  const uint32_t *list_count;
-  int64_t *retry;           // candidates whose inbox overflowed
-  uint32_t *retry_count;
-  uint64_t *gring;          // device-memory inboxes: P * (2K + 1) entries per resident
-                            // candidate slot, slot = (block * wpb + wave) * (64 >> pwl) + group
+  int32_t off_ring, off_msg, off_join, off_qof, off_gof;   // within a candidate
+  uint64_t *dring;          // [resident candidate slots][P][2][kg]
+  uint32_t *joins_dev;      // [resident candidate slots][J][2], or null: in LDS
+  uint32_t *spill_count;    // candidates that put stages in dring (running count)
 };
-// successor word: internal group | kind << 16 | rank << 17
+// successor word: group | kind << 16 | rank << 17
 constexpr uint32_t kGreedyNoStage = 0xffffu;
-// nw: bitmap words per kind (1, 2, 4, 8, 16, 32); gring: inboxes in device
-// memory (GreedyArgs::gring) rather than LDS
 // Zeroes n (<= 64) words: a kernel instead of a memset node, so that code a
 // caller captures into a HIP graph holds no memset.
 hipError_t launch_zero_words(uint32_t *p, int n, hipStream_t s);
-const void *greedy_kernel_ptr(int pwl, int nw, bool gring);
-hipError_t launch_greedy(int pwl, int nw, bool gring, int blocks, int wpb, size_t lds, hipStream_t s,
+// rwl: log2 of the lanes that play ranks (2 .. 6); wide: a wave per candidate
+const void *greedy_kernel_ptr(int rwl, bool wide);
+hipError_t launch_greedy(int rwl, bool wide, int blocks, size_t lds, hipStream_t s,
                          const GreedyArgs &a);
 
 // ---------------------------------------------------------------- rollouts

@@ -15,26 +15,38 @@
 //   * the rank with the smallest t_min (lowest index on ties) commits its
 //     choice; when every rank is held back by its cap, the cap is lifted for
 //     one decision.
-// Every round commits exactly one stage of every candidate, so a candidate
-// takes N rounds.
 //
-// Mapping: a group of PW = 2^PWL lanes per candidate, lane = rank; 64 / PW
-// candidates per wave.  A rank's queued stages are kept by priority position
-// (the group's rank among groups of its kind under the candidate's
-// priorities):
-//   E      bitmap (registers) of queued stages with t_start < t_last (and the
-//          stages without predecessors while t_last is 0);
-//   inbox  two rings (LDS), forward and backward, of the other queued
-//          stages, sorted by (t_start, position): a ring's front is its
-//          kind's least t_start and, among equal ones, its best priority.
-// Lanes touch only their own bitmaps; the committing lane inserts the stages
-// its commit completes into the target ranks' inboxes, and each lane moves
-// the entries that came due into E at the start of the next round.  A group min over the
-// lanes' t_min picks the committing rank.  An inbox that fills up sends the
-// candidate to a list that a second launch, with inboxes as large as a rank's
-// stage count of that kind, simulates again; where such inboxes do not fit in
-// LDS, that launch keeps them in device memory (GRING), one region per
-// resident candidate slot.
+// Several decisions per round.  Let E be the least end time over the ranks'
+// current choices.  No stage can be delivered to any rank before E: the next
+// commits are these choices, or later stages of their ranks, which start no
+// earlier.  So every rank whose t_min lies below E keeps its choice whatever
+// the others do first, and all of them commit in the same round; the rank of
+// the least t_min always does.  On the workloads that is 2 to 5 commits a
+// round (11 on 64 equal ranks), with the sequential greedy's result.
+//
+// Mapping: lane = rank; a group of 2^GWL lanes per candidate.  GWL is the
+// rank count's power of two (64 >> GWL candidates side by side in a wave), or
+// 6: a wave per candidate, whose branches are then uniform, for batches too
+// small to fill the SIMDs otherwise (the launch chooses).
+//
+// A rank's queue, per kind, by overall priority rank q (0 best):
+//   S     a bitmap in LDS with a register mask of its non-zero words and its
+//         first member in a register.  All members have t_start < t_last
+//         (ts < t_last), or all have t_start == ts >= t_last: runs of equal
+//         times, such as the zero-cost stages of empty pieces, cost one bit
+//         a stage;
+//   ring  the stages that start later than S (or at t_last beside an
+//         earlier S), sorted by (t_start, q): the first in a register, the
+//         next few in LDS, the rest in device memory (one region per
+//         resident candidate slot, as large as the rank's stage count, so it
+//         never fills).  97 % of the time a ring is empty or holds one stage.
+// A committing lane changes its own queue only.  What its stage completes
+// goes to the target ranks as messages, one per sender and pass: the sender
+// writes {t_start, q, kind} into its slot and sets its bit in the target's
+// mask; each target takes its messages in turn.
+//
+// What bounds it: latency and vector issue of a round's serial chain (choice,
+// record, reductions, commit, messages); bandwidth is a few percent.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -47,493 +59,517 @@ namespace dipsim {
 
 namespace {
 
-constexpr uint32_t kNoPos = 0xffffu;
-constexpr uint32_t kNever = 0xffffffffu;
-
-// A set of priority positions 0 .. 64 * NW - 1, held in registers; indexes are
-// resolved by selects so that the words never leave registers.
-template <int NW>
-struct Bits {
-  uint64_t w[NW];
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) w[i] = 0;
-  }
-  __device__ __forceinline__ void clear(uint32_t p) {
-    const uint32_t k = p >> 6;
-    const uint64_t b = ~(uint64_t(1) << (p & 63u));
-#pragma unroll
-    for (int i = 0; i < NW; ++i) w[i] &= uint32_t(i) == k ? b : ~uint64_t(0);
-  }
-};
-
-// lowest position in a, kNoPos if empty
-template <int NW>
-__device__ __forceinline__ uint32_t first_in(const Bits<NW> &a) {
-  uint32_t r = kNoPos;
-#pragma unroll
-  for (int i = NW - 1; i >= 0; --i)
-    if (a.w[i] != 0) r = uint32_t(i) * 64u + uint32_t(__builtin_ctzll(a.w[i]));
-  return r;
-}
-
-// sets position p in f (kind 0) or b (kind 1) without branching
-template <int NW>
-__device__ __forceinline__ void set_kind(Bits<NW> &f, Bits<NW> &b, uint32_t kind, uint32_t p) {
-  const uint32_t k = p >> 6;
-  const uint64_t bit = uint64_t(1) << (p & 63u);
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const uint64_t m = uint32_t(i) == k ? bit : uint64_t(0);
-    f.w[i] |= kind ? uint64_t(0) : m;
-    b.w[i] |= kind ? m : uint64_t(0);
-  }
-}
-
-// The two E sets of one rank (forward, backward).  Up to 16 words a set they
-// live in registers; 32-word sets (every set or clear would touch every word
-// through selects) live in the lane's own LDS words, with a register mask of
-// the words that are not zero, so that a set, a clear and the first
-// position each take one or two LDS accesses.
-template <int NW, bool IN_LDS = (NW >= 32)>
-struct EPair {
-  Bits<NW> f, b;
-  __device__ __forceinline__ void init(uint64_t *) {
-    f.zero();
-    b.zero();
-  }
-  __device__ __forceinline__ void set(uint32_t kind, uint32_t p) { set_kind(f, b, kind, p); }
-  // clears position p of a kind; the kind's new first position
-  __device__ __forceinline__ uint32_t clear_first(uint32_t kind, uint32_t p) {
-    if (kind) {
-      b.clear(p);
-      return first_in(b);
-    }
-    f.clear(p);
-    return first_in(f);
-  }
-  __device__ __forceinline__ uint32_t first(uint32_t kind) const { return first_in(kind ? b : f); }
-};
-
-template <int NW>
-struct EPair<NW, true> {
-  static_assert(NW <= 32, "one summary bit per word");
-  uint64_t *w;        // [2][NW] this lane's words: forward, then backward
-  uint32_t nz[2];     // words that are not zero, per kind
-  __device__ __forceinline__ void init(uint64_t *words) {
-    w = words;
-#pragma unroll
-    for (int i = 0; i < 2 * NW; ++i) w[i] = 0;
-    nz[0] = nz[1] = 0;
-  }
-  __device__ __forceinline__ void set(uint32_t kind, uint32_t p) {
-    const uint32_t k = p >> 6;
-    __hip_atomic_fetch_or(w + kind * NW + k, uint64_t(1) << (p & 63u), __ATOMIC_RELAXED,
-                          __HIP_MEMORY_SCOPE_WAVEFRONT);
-    nz[kind] |= 1u << k;
-  }
-  __device__ __forceinline__ uint32_t first(uint32_t kind) const {
-    if (nz[kind] == 0) return kNoPos;
-    const uint32_t k = uint32_t(__builtin_ctz(nz[kind]));
-    return k * 64u + uint32_t(__builtin_ctzll(w[kind * NW + k]));
-  }
-  __device__ __forceinline__ uint32_t clear_first(uint32_t kind, uint32_t p) {
-    const uint32_t k = p >> 6;
-    const uint64_t bit = uint64_t(1) << (p & 63u);
-    const uint64_t old = __hip_atomic_fetch_and(w + kind * NW + k, ~bit, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_WAVEFRONT);
-    if ((old & ~bit) == 0) nz[kind] &= ~(1u << k);
-    return first(kind);
-  }
-};
+constexpr uint32_t kNone = 0xffffu;        // no priority rank
+constexpr uint32_t kNever = 0xffffffffu;   // no time
+constexpr uint64_t kNoEntry = ~uint64_t(0);
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
   return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, false));
 }
 
-// min / max over the 2^PWL lanes of a group: quad permutations, then the
+// min / max over aligned runs of 2^WL lanes: quad permutations, then the
 // half-row and row mirrors (each lane meets the other half), then shuffles
-template <int PWL, bool MAX>
-__device__ __forceinline__ uint32_t group_reduce(uint32_t v) {
+template <int WL, bool MAX>
+__device__ __forceinline__ uint32_t run_reduce(uint32_t v) {
   auto op = [](uint32_t x, uint32_t y) { return MAX ? max(x, y) : min(x, y); };
-  if constexpr (PWL >= 1) v = op(v, dpp<0xb1>(v));    // quad_perm [1,0,3,2]
-  if constexpr (PWL >= 2) v = op(v, dpp<0x4e>(v));    // quad_perm [2,3,0,1]
-  if constexpr (PWL >= 3) v = op(v, dpp<0x141>(v));   // row_half_mirror
-  if constexpr (PWL >= 4) v = op(v, dpp<0x140>(v));   // row_mirror
-  if constexpr (PWL >= 5) v = op(v, uint32_t(__shfl_xor(int(v), 16)));
-  if constexpr (PWL >= 6) v = op(v, uint32_t(__shfl_xor(int(v), 32)));
+  if constexpr (WL >= 1) v = op(v, dpp<0xb1>(v));    // quad_perm [1,0,3,2]
+  if constexpr (WL >= 2) v = op(v, dpp<0x4e>(v));    // quad_perm [2,3,0,1]
+  if constexpr (WL >= 3) v = op(v, dpp<0x141>(v));   // row_half_mirror
+  if constexpr (WL >= 4) v = op(v, dpp<0x140>(v));   // row_mirror
+  if constexpr (WL >= 5) v = op(v, uint32_t(__shfl_xor(int(v), 16)));
+  if constexpr (WL >= 6) v = op(v, uint32_t(__shfl_xor(int(v), 32)));
   return v;
 }
-template <int PWL>
-__device__ __forceinline__ uint32_t group_min(uint32_t v) { return group_reduce<PWL, false>(v); }
-template <int PWL>
-__device__ __forceinline__ uint32_t group_max(uint32_t v) { return group_reduce<PWL, true>(v); }
 
-// Orders the LDS accesses of the wave's lanes around this point without
-// waiting for its global stores.
-__device__ __forceinline__ void lds_sync() {
-  lds_wait();
-  __builtin_amdgcn_wave_barrier();
-}
-
-// ranking key: priority, then lower caller index first
-__device__ __forceinline__ uint64_t rank_key(int32_t prio, uint32_t caller) {
-  return (uint64_t(uint32_t(prio) ^ 0x80000000u) << 32) | uint64_t(0xffffu - caller);
+// the same over a candidate's 2^GWL lanes, whose ranks are the first 2^RWL
+template <int RWL, int GWL, bool MAX>
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v) {
+  v = run_reduce<RWL, MAX>(v);
+  if constexpr (GWL == 6 && RWL < 6) v = uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
+  return v;
 }
 
 // bits of this lane's group in a wave-wide mask, lowest rank at bit 0
-template <int PWL>
+template <int GWL>
 __device__ __forceinline__ uint64_t group_bits(uint64_t m, int grp) {
-  constexpr uint64_t low = (1 << PWL) == 64 ? ~uint64_t(0) : (uint64_t(1) << (1 << PWL)) - 1;
-  return (m >> (grp << PWL)) & low;
+  if constexpr (GWL == 6) return m;
+  constexpr uint64_t low = (uint64_t(1) << ((1 << GWL) & 63)) - 1;
+  return (m >> (grp << GWL)) & low;
 }
 
-// One rank's choice: start time, priority position, kind (0 forward, 1
-// backward) and, for a stage still in the inbox, its inbox index.
+// Where a rank's rings lie beyond their first entry: KL entries (a power of
+// two) a kind in LDS, KG entries a kind in device memory.
+struct RingMem {
+  uint64_t *lds, *dev;
+  uint32_t kl, kg;
+};
+
+// One kind's queue of one rank (registers of its lane).
+struct Queue {
+  uint64_t *bits;      // S, by priority rank
+  uint64_t nz;         // its non-zero words
+  uint32_t first;      // its first member, kNone if empty
+  uint32_t ts;         // the members' t_start when that is >= t_last
+  uint64_t fr;         // the ring's first entry (t_start << 32 | q), or kNoEntry
+  uint32_t h, n;       // head and count of its entries in LDS
+  uint32_t gh, gn;     // and in device memory
+  RingMem m;
+
+  __device__ __forceinline__ void clear(uint64_t *b, const RingMem &mem) {
+    bits = b;
+    m = mem;
+    nz = 0;
+    first = kNone;
+    ts = 0;
+    fr = kNoEntry;
+    h = n = gh = gn = 0;
+  }
+  __device__ __forceinline__ void set(uint32_t q) {
+    const uint32_t k = q >> 6;
+    bits[k] |= uint64_t(1) << (q & 63u);
+    nz |= uint64_t(1) << k;
+    first = min(first, q);
+  }
+  // takes the first member out
+  __device__ __forceinline__ void drop_first() {
+    uint32_t k = first >> 6;
+    uint64_t w = bits[k];
+    w &= w - 1;
+    bits[k] = w;
+    if (w == 0) {
+      nz &= nz - 1;
+      if (nz == 0) {
+        first = kNone;
+        return;
+      }
+      k = uint32_t(__builtin_ctzll(nz));
+      w = bits[k];
+    }
+    first = k * 64u + uint32_t(__builtin_ctzll(w));
+  }
+  __device__ __forceinline__ uint32_t dev_at(uint32_t i) const {
+    const uint32_t x = gh + i;
+    return x >= m.kg ? x - m.kg : x;
+  }
+  // x into the sorted ring; true if an entry went to device memory
+  __device__ __forceinline__ bool ring_insert(uint64_t x) {
+    if (x < fr) {
+      const uint64_t y = fr;
+      fr = x;
+      if (y == kNoEntry) return false;
+      x = y;
+    }
+    const uint32_t mask = m.kl - 1u;
+    bool spilled = false;
+    if (gn > 0 || n >= m.kl) {
+      // (entries in device memory only ever follow a non-empty LDS part)
+      spilled = true;
+      const uint64_t back = m.lds[(h + n - 1u) & mask];
+      if (back <= x) {
+        uint32_t i = gn;
+        for (; i > 0; --i) {
+          const uint64_t p = m.dev[dev_at(i - 1u)];
+          if (p <= x) break;
+          m.dev[dev_at(i)] = p;
+        }
+        m.dev[dev_at(i)] = x;
+        ++gn;
+        return true;
+      }
+      // the last entry in LDS makes room
+      gh = gh == 0 ? m.kg - 1u : gh - 1u;
+      m.dev[gh] = back;
+      ++gn;
+      --n;
+    }
+    uint32_t i = n;
+    for (; i > 0; --i) {
+      const uint64_t p = m.lds[(h + i - 1u) & mask];
+      if (p <= x) break;
+      m.lds[(h + i) & mask] = p;
+    }
+    m.lds[(h + i) & mask] = x;
+    ++n;
+    return spilled;
+  }
+  __device__ __forceinline__ void ring_pop() {
+    if (n == 0) {
+      fr = kNoEntry;
+      return;
+    }
+    const uint32_t mask = m.kl - 1u;
+    fr = m.lds[h & mask];
+    h = (h + 1u) & mask;
+    --n;
+    if (n == 0 && gn > 0) {
+      for (; n < m.kl && gn > 0; ++n, --gn) {
+        m.lds[(h + n) & mask] = m.dev[gh];
+        gh = dev_at(1u);
+      }
+    }
+  }
+  // whether a stage at t joins S: S is empty, or both lie before t_last, or
+  // it starts with S's run
+  __device__ __forceinline__ bool joins(uint32_t t, uint32_t t_last) const {
+    return first == kNone || (ts < t_last && t < t_last) || t == ts;
+  }
+  __device__ __forceinline__ void join(uint32_t t, uint32_t q) {
+    if (first == kNone) ts = t;
+    set(q);
+  }
+  // a stage arrives; true if an entry went to device memory
+  __device__ __forceinline__ bool arrive(uint32_t t, uint32_t q, uint32_t t_last) {
+    if (joins(t, t_last)) {
+      join(t, q);
+      return false;
+    }
+    if (ts < t_last || t > ts) return ring_insert((uint64_t(t) << 32) | q);
+    // S is a run of later stages: they go to the ring, the new one takes S
+    bool spilled = false;
+    do {
+      spilled |= ring_insert((uint64_t(ts) << 32) | first);
+      drop_first();
+    } while (first != kNone);
+    ts = t;
+    set(q);
+    return spilled;
+  }
+  // ring entries that now belong to S
+  __device__ __forceinline__ void pull(uint32_t t_last) {
+    while (fr != kNoEntry && joins(uint32_t(fr >> 32), t_last)) {
+      join(uint32_t(fr >> 32), uint32_t(fr) & 0xffffu);
+      ring_pop();
+    }
+  }
+  __device__ __forceinline__ uint32_t least() const { return first == kNone ? kNever : ts; }
+};
+
+// One rank's choice: start time, priority rank, kind (0 forward, 1 backward)
+// and whether it is the kind's first ring entry.
 struct Choice {
-  uint32_t tau, pos, kind, slot;
+  uint32_t tau, q, kind;
+  bool ring;
 };
 
 }  // namespace
 
-template <int PWL, int NW, bool GRING>
-__global__ __launch_bounds__(256) void greedy_kernel(GreedyArgs a) {
-  constexpr int PW = 1 << PWL;
-  constexpr int GW = kWave >> PWL;
+template <int RWL, int GWL>
+__global__ __launch_bounds__(64) void greedy_kernel(GreedyArgs a) {
+  constexpr int RW = 1 << RWL;
+  constexpr int GL = 1 << GWL;
+  constexpr int GW = kWave >> GWL;
   extern __shared__ __align__(16) unsigned char lds[];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int grp = lane >> PWL;
-  const int r = lane & (PW - 1);
-  const int G = a.G, GF = a.GF, P = a.P, K = a.K;
+  const int lane = threadIdx.x;
+  const int grp = lane >> GWL;
+  const int r = lane & (GL - 1);
+  const int G = a.G, P = a.P;
+  const int rk = r < P ? r : 0;
 
-  uint16_t *meta = reinterpret_cast<uint16_t *>(lds);
-  for (int i = threadIdx.x; i < G; i += blockDim.x) meta[i] = uint16_t(a.caller[i]);
-  __syncthreads();
+  unsigned char *cb = lds + int64_t(grp) * a.cand_bytes;
+  int32_t *prio = reinterpret_cast<int32_t *>(cb);               // set-up only ...
+  // ... then the bitmaps, rings, messages and joins
+  uint64_t *bits0 = reinterpret_cast<uint64_t *>(cb) + int64_t(rk) * (2 * a.nwd + 1);
+  uint64_t *ring0 = reinterpret_cast<uint64_t *>(cb + a.off_ring) + int64_t(rk) * (2 * a.kl + 1);
+  uint64_t *msg = reinterpret_cast<uint64_t *>(cb + a.off_msg);       // [RW] one per sender
+  uint64_t *mask = msg + RW;                                          // [RW] senders per target
+  uint16_t *qof = reinterpret_cast<uint16_t *>(cb + a.off_qof);       // group -> priority rank
+  uint16_t *gof = reinterpret_cast<uint16_t *>(cb + a.off_gof);       // priority rank -> group
+  const int64_t slot0 = int64_t(blockIdx.x) * GW + grp;
+  uint32_t *jtab = reinterpret_cast<uint32_t *>(cb + a.off_join);     // {latest, arrived}
+  uint32_t *jdev = a.joins_dev + slot0 * 2 * a.J;                     // in their place
+  uint64_t *dev0 = a.dring + (slot0 * P + rk) * 2 * int64_t(a.kg);
+  const RingMem memF{ring0, dev0, uint32_t(a.kl), uint32_t(a.kg)};
+  const RingMem memB{ring0 + a.kl, dev0 + a.kg, uint32_t(a.kl), uint32_t(a.kg)};
 
-  unsigned char *cb = lds + a.meta_bytes + int64_t(wave * GW + grp) * a.cand_bytes;
-  int32_t *prio = reinterpret_cast<int32_t *>(cb);               // setup only ...
-  // ... then the inboxes: per rank a forward ring and a backward ring of K
-  // entries each (and one spare entry); per lane (padding lanes included) a
-  // word {head, count << 16} per kind
-  // rank stride 2K + 1 entries, so that the lanes' rings start in different banks
-  const int64_t rstride = 2 * int64_t(K) + 1;
-  uint64_t *ring0;
-  if constexpr (GRING)
-    ring0 = a.gring + ((int64_t(blockIdx.x) * a.wpb + wave) * GW + grp) * P * rstride;
-  else
-    ring0 = reinterpret_cast<uint64_t *>(cb + a.off_pend);
-  uint64_t *ringF = ring0 + int64_t(r < P ? r : 0) * rstride;
-  uint64_t *ringB = ringF + K;
-  uint32_t *hcw = reinterpret_cast<uint32_t *>(cb + a.off_npend);
-  uint32_t *jtab = reinterpret_cast<uint32_t *>(cb + a.off_join);
-  uint16_t *gpos = reinterpret_cast<uint16_t *>(cb + a.off_gpos);
-  uint16_t *ord = reinterpret_cast<uint16_t *>(cb + a.off_ord);
-  uint16_t *grk = reinterpret_cast<uint16_t *>(cb + a.off_grk);
-  // wide E sets: each lane's 2 NW words at the end of its candidate's region
-  uint64_t *ebits = reinterpret_cast<uint64_t *>(cb + a.cand_bytes) - int64_t(PW - r) * 2 * NW;
-
-  const int64_t n_slots = int64_t(gridDim.x) * a.wpb * GW;
-  for (int64_t slot = (int64_t(blockIdx.x) * a.wpb + wave) * GW + grp;; slot += n_slots) {
-    int64_t cand = -1;
-    if (a.list) {
-      if (slot < int64_t(*a.list_count)) cand = a.list[slot];
-    } else if (slot < a.n_cand) {
-      cand = slot;
-    }
-    const bool has = cand >= 0;
+  const int64_t n_slots = int64_t(gridDim.x) * GW;
+  for (int64_t cand = slot0;; cand += n_slots) {
+    const bool has = cand < a.n_cand;
     if (!__any(has)) break;
     const bool real = has && r < P;
 
-    // ---- setup: positions of the groups under this candidate's priorities
+    // ---- set-up: priority ranks of the groups (priority, then index)
+    const int Gp = (G + 3) & ~3;
     if (has) {
       const int32_t *pv = a.prio + cand * G;
-      for (int g = r; g < G; g += PW) prio[g] = pv[meta[g]];
+      for (int g = r; g < Gp; g += GL) prio[g] = g < G ? pv[g] : INT32_MIN;
     }
     wave_sync();
     if (has) {
-      // rank of every group among all groups and among its kind, eight of
-      // this lane's groups against each group in turn
-      constexpr int B = 8;
-      for (int g0 = r; g0 < G; g0 += B * PW) {
-        uint64_t kg[B];
-        uint32_t nf[B], nb[B];
+      // B groups of this lane against every group in turn; a group of lower
+      // index wins a tie
+      constexpr int B = 4;
+      const int4 *p4 = reinterpret_cast<const int4 *>(prio);
+      for (int g0 = 0; g0 < G; g0 += B * GL) {
+        int32_t p[B];
+        uint32_t n[B];
 #pragma unroll
         for (int t = 0; t < B; ++t) {
-          const int g = g0 + t * PW;
-          kg[t] = g < G ? rank_key(prio[g], meta[g]) : ~uint64_t(0);
-          nf[t] = nb[t] = 0;
+          const int g = g0 + t * GL + r;
+          p[t] = g < G ? prio[g] : INT32_MAX;
+          n[t] = 0;
         }
-        for (int h = 0; h < GF; ++h) {
-          const uint64_t kh = rank_key(prio[h], meta[h]);
+        for (int h = 0; h < g0; h += 4) {
+          const int4 x = p4[h >> 2];
 #pragma unroll
-          for (int t = 0; t < B; ++t) nf[t] += kh > kg[t] ? 1u : 0u;
+          for (int t = 0; t < B; ++t)
+            n[t] += uint32_t(x.x >= p[t]) + uint32_t(x.y >= p[t]) + uint32_t(x.z >= p[t]) +
+                    uint32_t(x.w >= p[t]);
         }
-        for (int h = GF; h < G; ++h) {
-          const uint64_t kh = rank_key(prio[h], meta[h]);
 #pragma unroll
-          for (int t = 0; t < B; ++t) nb[t] += kh > kg[t] ? 1u : 0u;
+        for (int s = 0; s < B; ++s) {
+          const int hb = g0 + s * GL;
+          for (int h = hb; h < min(hb + GL, Gp); h += 4) {
+            const int4 x = p4[h >> 2];
+            const int32_t xs[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int t = 0; t < B; ++t) {
+                if (s < t)
+                  n[t] += uint32_t(xs[e] >= p[t]);
+                else if (s > t)
+                  n[t] += uint32_t(xs[e] > p[t]);
+                else
+                  n[t] += uint32_t(xs[e] > p[t] || (xs[e] == p[t] && h + e - hb < r));
+              }
+          }
+        }
+        for (int h = g0 + B * GL; h < Gp; h += 4) {
+          const int4 x = p4[h >> 2];
+#pragma unroll
+          for (int t = 0; t < B; ++t)
+            n[t] += uint32_t(x.x > p[t]) + uint32_t(x.y > p[t]) + uint32_t(x.z > p[t]) +
+                    uint32_t(x.w > p[t]);
         }
 #pragma unroll
         for (int t = 0; t < B; ++t) {
-          const int g = g0 + t * PW;
+          const int g = g0 + t * GL + r;
           if (g < G) {
-            const bool fg = g < GF;
-            const uint32_t same = fg ? nf[t] : nb[t];
-            gpos[g] = uint16_t(same);
-            const int at = fg ? int(same) : GF + int(same);
-            ord[at] = uint16_t(g);
-            grk[at] = uint16_t(nf[t] + nb[t]);
+            qof[g] = uint16_t(n[t]);
+            gof[n[t]] = uint16_t(g);
           }
         }
       }
     }
     wave_sync();
-    if (has)
-      for (int j = r; j < 2 * a.J; j += PW) jtab[j] = 0;
-    hcw[2 * r] = 0;
-    hcw[2 * r + 1] = 0;
-    // E: queued stages with t_start < t_last (and the stages without
-    // predecessors while t_last is still 0, their t_start); a stage with
-    // t_start >= t_last waits in its kind's inbox
-    EPair<NW> e;
-    e.init(ebits);
+    Queue qF, qB;
+    qF.clear(bits0, memF);
+    qB.clear(bits0 + a.nwd, memB);
+    if (has) {
+      if (a.joins_dev)
+        for (int j = r; j < 2 * a.J; j += GL) jdev[j] = 0;
+      else
+        for (int j = r; j < 2 * a.J; j += GL) jtab[j] = 0;
+      if (r < RW) mask[r] = 0;
+    }
     if (real) {
+      for (int i = 0; i < 2 * a.nwd; ++i) bits0[i] = 0;
+      // the stages without predecessors: t_start 0
       const int32_t *src_list = a.src + P + 1;
       for (int s = a.src[r]; s < a.src[r + 1]; ++s) {
         const int g = src_list[s];
-        e.set(g < GF ? 0u : 1u, gpos[g]);
+        if (g >> 16)
+          qB.join(0u, qof[g & 0xffff]);
+        else
+          qF.join(0u, qof[g]);
       }
     }
-    // first (best) position in each E, kept up to date: an entry moving in
-    // can only lower it; the commit that takes it looks again
-    uint32_t eF1 = e.first(0u), eB1 = e.first(1u);
+    if (a.joins_dev) __threadfence();
     wave_sync();
 
     uint32_t t_last = 0, last_kind = 0, n_emit = 0;
     uint32_t rec_key = kNever;
     int4 q0 = make_int4(0, 0, 0, 0), q1 = q0;
     int32_t live = 0, peak = 0;
-    bool ovf = false, stuck = false;
+    bool spilled = false, stuck = false, bad = false;
     const int32_t capr = real ? a.cap[r] : -1;
     const int64_t row = real ? cand * a.stride + a.rank_off[r] : 0;
     const uint32_t n_own = real ? uint32_t(a.rank_off[r + 1] - a.rank_off[r]) : 0u;
-    const uint32_t mask = uint32_t(K) - 1u;
+    int32_t left = has ? a.n_stages : 0;      // stages of the candidate to commit
 
-    for (int it = 0; it < a.n_rounds; ++it) {
-      // ---- 1. inboxes: entries that came due move into E; the fronts are
-      // each kind's least t_start (best position among equal ones)
-      const uint32_t cF0 = hcw[2 * r], cB0 = hcw[2 * r + 1];
-      uint32_t hF = cF0 & 0xffffu, nF = cF0 >> 16, hB = cB0 & 0xffffu, nB = cB0 >> 16;
-      uint64_t frF = ~uint64_t(0), frB = ~uint64_t(0);
-      for (; nF > 0; ++hF, --nF) {
-        frF = ringF[hF & mask];
-        if (uint32_t(frF >> 17) >= t_last) break;
-        const uint32_t p = uint32_t(frF >> 1) & 0xffffu;
-        e.set(0u, p);
-        eF1 = min(eF1, p);
-        frF = ~uint64_t(0);
-      }
-      for (; nB > 0; ++hB, --nB) {
-        frB = ringB[hB & mask];
-        if (uint32_t(frB >> 17) >= t_last) break;
-        const uint32_t p = uint32_t(frB >> 1) & 0xffffu;
-        e.set(1u, p);
-        eB1 = min(eB1, p);
-        frB = ~uint64_t(0);
-      }
-      const uint32_t cF = (hF & 0xffffu) | (nF << 16), cB = (hB & 0xffffu) | (nB << 16);
-      if (cF != cF0) hcw[2 * r] = cF;
-      if (cB != cB0) hcw[2 * r + 1] = cB;
-      const uint32_t pmF = nF ? uint32_t(frF >> 17) : kNever, pmB = nB ? uint32_t(frB >> 17) : kNever;
-      const uint32_t ppF = nF ? uint32_t(frF >> 1) & 0xffffu : kNoPos;
-      const uint32_t ppB = nB ? uint32_t(frB >> 1) & 0xffffu : kNoPos;
-
-      // ---- 2. this rank's choice
-      const uint32_t fF = eF1, fB = eB1;
-      const bool xF = fF != kNoPos && t_last > 0, xB = fB != kNoPos && t_last > 0;
-      // the best stage of each kind able to start at tau: E's first (E is
-      // non-empty only when tau == t_last) or the inbox front if due then
+    while (__any(left > 0)) {
+      // ---- 1. this rank's choice
+      // the best stage of each kind able to start at tau: S's first, or the
+      // ring's first when it starts at tau too (beside an S before t_last)
+      const uint32_t tB = qB.least();
       auto decide = [&](bool fw) {
         Choice c;
-        const uint32_t eF_ = fw ? fF : kNoPos, pF = fw ? pmF : kNever;
-        const bool anyE = eF_ != kNoPos || fB != kNoPos;
-        c.tau = anyE ? t_last : min(pF, pmB);
-        const bool inF = pF == c.tau && ppF < eF_;
-        const bool inB = pmB == c.tau && ppB < fB;
-        const uint32_t bF = inF ? ppF : eF_, bB = inB ? ppB : fB;
-        const uint32_t gF = grk[bF < uint32_t(GF) ? bF : 0u];
-        const uint32_t gB = grk[bB < uint32_t(G - GF) ? GF + bB : 0u];
-        const bool alt = fw && xF && xB;                           // 1F1B
-        const uint32_t k = bF == kNoPos ? 1u : (bB == kNoPos ? 0u : (gF < gB ? 0u : 1u));
-        c.kind = alt ? (last_kind ^ 1u) : k;
-        c.pos = c.kind ? bB : bF;
-        c.slot = (c.kind ? inB : inF) ? 1u : 0u;    // 1: the kind's inbox front
+        const uint32_t tF = fw ? qF.least() : kNever;
+        const uint32_t tmin = min(tF, tB);
+        c.tau = max(t_last, tmin);
+        uint32_t bF = tF <= c.tau && fw ? qF.first : kNone;
+        uint32_t bB = tB <= c.tau ? qB.first : kNone;
+        const bool inF = fw && uint32_t(qF.fr >> 32) == c.tau && (uint32_t(qF.fr) & 0xffffu) < bF;
+        const bool inB = uint32_t(qB.fr >> 32) == c.tau && (uint32_t(qB.fr) & 0xffffu) < bB;
+        if (inF) bF = uint32_t(qF.fr) & 0xffffu;
+        if (inB) bB = uint32_t(qB.fr) & 0xffffu;
+        const bool alt = tF < t_last && tB < t_last;               // 1F1B
+        c.kind = alt ? (last_kind ^ 1u) : (bF < bB ? 0u : 1u);
+        c.q = tmin == kNever ? kNone : (c.kind ? bB : bF);
+        c.ring = c.kind ? inB : inF;
         return c;
       };
       // the record of a choice: {cost, act, local id | successors << 16,
       // second successor's index}, {first successor}; kept while the choice
       // stays the same
       auto fetch = [&](const Choice &c) {
-        const uint32_t k = (c.kind << 16) | c.pos;
-        if (k != rec_key) {
-          const int4 *rp = a.rec + (int64_t(ord[c.kind ? GF + c.pos : c.pos]) * P + r) * 2;
+        if (c.q != rec_key) {
+          const int4 *rp = a.rec + (int64_t(gof[c.q]) * P + r) * 2;
           q0 = rp[0];
           q1 = rp[1];
-          rec_key = k;
+          rec_key = c.q;
         }
       };
-      const Choice ce = decide(true);
+      Choice ce = decide(true);
+      const bool act = left > 0 && r < P;
+      if (!act) ce.q = kNone;
       Choice cd = ce;
-      if (ce.pos != kNoPos) {
+      if (ce.q != kNone) {
         fetch(ce);
         if (a.has_cap && ce.kind == 0 && capr >= 0 && live + q0.y > capr) {
           cd = decide(false);                   // forward queue disabled
-          if (cd.pos != kNoPos) fetch(cd);
+          if (cd.q != kNone) fetch(cd);
         }
       }
 
-      // ---- 3. the rank with the smallest t_min commits
-      const uint32_t key_d = cd.pos != kNoPos ? cd.tau : kNever;
-      uint32_t m = group_min<PWL>(key_d);
-      uint32_t key = key_d;
+      // ---- 2. who commits: the rank of the least t_min, and every rank
+      // whose t_min lies before the least end
+      uint32_t key = cd.q != kNone ? cd.tau : kNever;
+      const uint32_t end = cd.tau + uint32_t(q0.x);
+      uint32_t m = group_reduce<RWL, GWL, false>(key);
+      const uint32_t e_min = group_reduce<RWL, GWL, false>(cd.q != kNone ? end : kNever);
       bool forced = false;
-      if (__any(has && m == kNever)) {
-        const uint32_t key_e = ce.pos != kNoPos ? ce.tau : kNever;
-        const uint32_t m2 = group_min<PWL>(key_e);
+      if (__any(left > 0 && m == kNever)) {
+        const uint32_t key_e = ce.q != kNone ? ce.tau : kNever;
+        const uint32_t m2 = group_reduce<RWL, GWL, false>(key_e);
         if (m == kNever) {
           forced = true;
           m = m2;
           key = key_e;
         }
       }
-      if (has && m == kNever) stuck = true;   // only a cyclic data graph gets here
-      const uint64_t mine = group_bits<PWL>(__ballot(real && m != kNever && key == m), grp);
-      const bool win = mine != 0 && r == __builtin_ctzll(mine);
+      if (left > 0 && m == kNever) {            // only a cyclic data graph gets here
+        stuck = true;
+        left = 0;
+      }
+      const uint64_t mine = group_bits<GWL>(__ballot(act && m != kNever && key == m), grp);
+      const bool win = mine != 0 && r == int(__builtin_ctzll(mine));
+      const bool com = win || (!forced && key < e_min);
+      const uint64_t coms = group_bits<GWL>(__ballot(com), grp);
+      left -= int32_t(__builtin_popcountll(coms));
 
-      if (win) {
-        const Choice c = forced ? ce : cd;
-        if (forced) fetch(c);
-        const uint32_t end = c.tau + uint32_t(q0.x);
-        if (c.slot == 0) {
-          if (c.kind)
-            eB1 = e.clear_first(1u, c.pos);
-          else
-            eF1 = e.clear_first(0u, c.pos);
-        } else {
-          // the kind's inbox front: one step on
-          const uint32_t hw = hcw[2 * r + c.kind];
-          hcw[2 * r + c.kind] = (((hw & 0xffffu) + 1u) & 0xffffu) | ((hw >> 16) - 1u) << 16;
+      // ---- 3. commits: each lane's own queue, order and memory
+      uint32_t ns = 0, t_end = 0;
+      if (com) {
+        Choice c = cd;
+        if (forced) {
+          c = ce;
+          fetch(c);
         }
-        t_last = end;
+        t_end = c.tau + uint32_t(q0.x);
+        t_last = t_end;
         last_kind = c.kind;
-        if (c.kind == 0) {
-          live += q0.y;
-          peak = max(peak, live);
+        if (c.kind) {
+          if (c.ring)
+            qB.ring_pop();
+          else
+            qB.drop_first();
         } else {
-          live -= q0.y;
+          if (c.ring)
+            qF.ring_pop();
+          else
+            qF.drop_first();
         }
+        qF.pull(t_last);
+        qB.pull(t_last);
+        live += c.kind ? -q0.y : q0.y;
+        if (c.kind == 0) peak = max(peak, live);
         if (n_emit < n_own) {
           if (a.out_orders) a.out_orders[row + n_emit] = int16_t(q0.z & 0xffff);
         } else {
-          ovf = true;     // more commits than stages: never with consistent tables
+          bad = true;     // more commits than stages: never with consistent tables
         }
         ++n_emit;
-        // successors whose last predecessor this was join the target inboxes,
-        // kept sorted by (t_start, position)
-        const uint32_t ns = uint32_t(q0.z) >> 16;
-        for (uint32_t s = 0; s < ns; ++s) {
-          const int4 e = s == 0 ? q1 : a.succ[q0.w + int32_t(s) - 1];
-          uint32_t t = end + uint32_t(e.y);
-          if (e.z >= 0) {
-            uint32_t *jb = jtab + 2 * e.z;
-            const uint32_t acc = max(jb[0], t), cnt = jb[1] + 1u;
-            jb[0] = acc;
-            jb[1] = cnt;
-            if (cnt < uint32_t(e.w)) continue;
-            t = acc;
-          }
-          const uint32_t w = uint32_t(e.x);
-          const uint32_t tr = (w >> 17) & 63u, tk = (w >> 16) & 1u;
-          const uint32_t h = hcw[2 * tr + tk];
-          const uint32_t head = h & 0xffffu, n = h >> 16;
-          if (n >= uint32_t(K)) {
-            ovf = true;
-            continue;
-          }
-          uint64_t *rt = ring0 + int64_t(tr) * rstride + (tk ? K : 0);
-          const uint64_t x = (uint64_t(t) << 17) | (uint64_t(gpos[w & 0xffffu]) << 1) | uint64_t(tk);
-          uint32_t i = n;
-          for (; i > 0; --i) {
-            const uint64_t prev = rt[(head + i - 1) & mask];
-            if (prev <= x) break;
-            rt[(head + i) & mask] = prev;
-          }
-          rt[(head + i) & mask] = x;
-          hcw[2 * tr + tk] = h + (1u << 16);
-        }
+        ns = uint32_t(q0.z) >> 16;
+        rec_key = kNever;
       }
-      if constexpr (GRING)
-        wave_sync();      // the inboxes' device-memory writes too
-      else
-        lds_sync();
+
+      // ---- 4. the stages these commits complete join their ranks' queues:
+      // pass s sends every committed stage's successor s
+      for (uint32_t s = 0; __any(s < ns); ++s) {
+        bool send = s < ns;
+        if (send) {
+          const int4 e = s == 0 ? q1 : a.succ[q0.w + int32_t(s) - 1];
+          uint32_t t = t_end + uint32_t(e.y);
+          if (e.z >= 0) {
+            // (every lane's maximum lands before any lane's count: the lanes
+            // take each of the two steps together)
+            if (a.joins_dev) {
+              uint32_t *jb = jdev + 2 * e.z;
+              atomicMax(jb, t);
+              __threadfence();
+              send = atomicAdd(jb + 1, 1u) + 1u >= uint32_t(e.w);
+              if (send) t = atomicMax(jb, 0u);
+            } else {
+              uint32_t *jb = jtab + 2 * e.z;
+              atomicMax(jb, t);
+              wave_lds_order();
+              send = atomicAdd(jb + 1, 1u) + 1u >= uint32_t(e.w);
+              if (send) t = jb[0];
+            }
+          }
+          if (send) {
+            const uint32_t w = uint32_t(e.x);
+            const uint32_t tr = (w >> 17) & 63u, tk = (w >> 16) & 1u;
+            msg[r] = (uint64_t(t) << 32) | (tk << 16) | qof[w & 0xffffu];
+            atomicOr(reinterpret_cast<unsigned long long *>(mask + tr),
+                     static_cast<unsigned long long>(uint64_t(1) << r));
+          }
+        }
+        wave_lds_order();
+        uint64_t from = 0;
+        if (act) {
+          from = mask[r];
+          if (from) mask[r] = 0;
+        }
+        while (__any(from != 0)) {
+          if (from) {
+            const uint64_t x = msg[__builtin_ctzll(from)];
+            from &= from - 1;
+            const uint32_t t = uint32_t(x >> 32), q = uint32_t(x) & 0xffffu;
+            if (uint32_t(x) & 0x10000u)
+              spilled |= qB.arrive(t, q, t_last);
+            else
+              spilled |= qF.arrive(t, q, t_last);
+          }
+        }
+        wave_lds_order();
+      }
     }
 
     // ---- outputs
-    const uint32_t T = group_max<PWL>(real ? t_last : 0u);
+    const uint32_t T = group_reduce<RWL, GWL, true>(real ? t_last : 0u);
     const uint64_t wcap = __ballot(real && capr >= 0 && peak > capr);
-    const uint64_t wovf = __ballot(ovf);
-    const bool gcap = group_bits<PWL>(wcap, grp) != 0;
-    const bool govf = group_bits<PWL>(wovf, grp) != 0;
+    const uint64_t wspill = __ballot(spilled);
+    const uint64_t wbad = __ballot(bad);
+    const bool gcap = group_bits<GWL>(wcap, grp) != 0;
+    const bool gbad = group_bits<GWL>(wbad, grp) != 0;
     if (has) {
-      if (govf && a.retry) {
-        if (r == 0) a.retry[atomicAdd(a.retry_count, 1u)] = cand;
-      } else if (govf) {      // cannot happen with inboxes as large as a rank
-        if (real) {
-          a.out_bub[cand * P + r] = -1;
-          a.out_peak[cand * P + r] = -1;
-        }
-        if (r == 0) {
-          a.out_ms[cand] = -1;
-          a.out_flags[cand] = DIP_FLAG_INVALID;
-        }
-      } else {
-        if (real) {
-          a.out_bub[cand * P + r] = stuck ? -1 : int32_t(T) - a.busy[r];
-          a.out_peak[cand * P + r] = peak;
-        }
-        if (r == 0) {
-          a.out_ms[cand] = stuck ? -1 : int32_t(T);
-          a.out_flags[cand] = uint8_t((stuck ? DIP_FLAG_DEADLOCK : 0u) | (gcap ? DIP_FLAG_CAP : 0u));
-        }
+      if (real) {
+        a.out_bub[cand * P + r] = stuck || gbad ? -1 : int32_t(T) - a.busy[r];
+        a.out_peak[cand * P + r] = gbad ? -1 : peak;
+      }
+      if (r == 0) {
+        a.out_ms[cand] = stuck || gbad ? -1 : int32_t(T);
+        a.out_flags[cand] = gbad ? uint8_t(DIP_FLAG_INVALID)
+                                 : uint8_t((stuck ? DIP_FLAG_DEADLOCK : 0u) | (gcap ? DIP_FLAG_CAP : 0u));
+        if (a.spill_count && group_bits<GWL>(wspill, grp) != 0) atomicAdd(a.spill_count, 1u);
       }
     }
     wave_sync();
   }
 }
-
-namespace {
-
-template <int PWL, bool GRING>
-const void *ptr_nw(int nw) {
-  switch (nw) {
-    case 1: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 1, GRING>);
-    case 2: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 2, GRING>);
-    case 4: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 4, GRING>);
-    case 8: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 8, GRING>);
-    case 16: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 16, GRING>);
-    case 32: return reinterpret_cast<const void *>(&greedy_kernel<PWL, 32, GRING>);
-    default: return nullptr;
-  }
-}
-
-template <int PWL>
-const void *ptr_pwl(int nw, bool gring) {
-  return gring ? ptr_nw<PWL, true>(nw) : ptr_nw<PWL, false>(nw);
-}
-
-}  // namespace
 
 __global__ void zero_words_kernel(uint32_t *p, int n) {
   if (int(threadIdx.x) < n) p[threadIdx.x] = 0u;
@@ -544,23 +580,31 @@ hipError_t launch_zero_words(uint32_t *p, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
-const void *greedy_kernel_ptr(int pwl, int nw, bool gring) {
-  switch (pwl) {
-    case 2: return ptr_pwl<2>(nw, gring);
-    case 3: return ptr_pwl<3>(nw, gring);
-    case 4: return ptr_pwl<4>(nw, gring);
-    case 5: return ptr_pwl<5>(nw, gring);
-    case 6: return ptr_pwl<6>(nw, gring);
+const void *greedy_kernel_ptr(int rwl, bool wide) {
+  switch (rwl) {
+    case 2:
+      return wide ? reinterpret_cast<const void *>(&greedy_kernel<2, 6>)
+                  : reinterpret_cast<const void *>(&greedy_kernel<2, 2>);
+    case 3:
+      return wide ? reinterpret_cast<const void *>(&greedy_kernel<3, 6>)
+                  : reinterpret_cast<const void *>(&greedy_kernel<3, 3>);
+    case 4:
+      return wide ? reinterpret_cast<const void *>(&greedy_kernel<4, 6>)
+                  : reinterpret_cast<const void *>(&greedy_kernel<4, 4>);
+    case 5:
+      return wide ? reinterpret_cast<const void *>(&greedy_kernel<5, 6>)
+                  : reinterpret_cast<const void *>(&greedy_kernel<5, 5>);
+    case 6: return reinterpret_cast<const void *>(&greedy_kernel<6, 6>);
     default: return nullptr;
   }
 }
 
-hipError_t launch_greedy(int pwl, int nw, bool gring, int blocks, int wpb, size_t lds,
-                         hipStream_t s, const GreedyArgs &a) {
-  const void *k = greedy_kernel_ptr(pwl, nw, gring);
+hipError_t launch_greedy(int rwl, bool wide, int blocks, size_t lds, hipStream_t s,
+                         const GreedyArgs &a) {
+  const void *k = greedy_kernel_ptr(rwl, wide);
   if (!k) return hipErrorInvalidValue;
   void *args[] = {const_cast<GreedyArgs *>(&a)};
-  return hipLaunchKernel(k, dim3(unsigned(blocks)), dim3(unsigned(wpb * kWave)), args, lds, s);
+  return hipLaunchKernel(k, dim3(unsigned(blocks)), dim3(kWave), args, lds, s);
 }
 
 }  // namespace dipsim
