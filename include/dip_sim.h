@@ -128,12 +128,13 @@ typedef struct {
   int32_t pool_slots;        /* variant 8: end-time slots per rank pool, else 0  */
   int32_t check_kernel;      /* variants 8, 9: 1 wave per candidate, 2 tiles,
                                 else 0                                         */
-  int32_t greedy_inbox;      /* dip_sim_greedy: stages a rank's inbox holds in
-                                its first launch (0: not configured; -1: that
-                                launch is skipped); grows when many overflow  */
-  int32_t greedy_lds_bytes;  /* dip_sim_greedy: LDS per block of its launch    */
-  int64_t greedy_retry_ring_bytes; /* dip_sim_greedy: device memory holding the
-                                second launch's inboxes where LDS cannot, else 0 */
+  int32_t greedy_inbox;      /* dip_sim_greedy: the inbox size (0: not configured;
+                                -1: most candidates go on into device memory at
+                                the largest size); grows when many do          */
+  int32_t greedy_lds_bytes;  /* dip_sim_greedy: LDS per block of its launch for
+                                large batches                                  */
+  int64_t greedy_retry_ring_bytes; /* dip_sim_greedy: device memory held for the
+                                stages beyond the inboxes in LDS               */
 } dip_sim_info;
 
 /* Host-only checks, no device access: the same checks create / evaluate run
@@ -240,23 +241,25 @@ int dip_sim_argmin(dip_sim *h, const int32_t *makespan, const uint8_t *flags,
  * prioritise.  A group holds ops of one kind, at most one per rank; the data
  * edges must be acyclic.  1 <= n_groups <= 65535, and at most 2048 groups of
  * either kind.  DIP_E_TOPO if a rule is broken, DIP_E_UNSUPPORTED if the
- * groups or the per-candidate tables do not fit the kernel.  Where a rank's
- * whole inboxes do not fit in LDS, the handle allocates device memory for
- * them (up to 1 GiB; dip_sim_info.greedy_retry_ring_bytes).  Replaces any
+ * groups or the per-candidate tables do not fit the kernel.  Stages beyond
+ * the inboxes in LDS lie in device memory of the handle's (up to 1 GiB, sized
+ * by the candidates in flight at once; dip_sim_info.greedy_retry_ring_bytes),
+ * allocated here where a rank's whole inboxes do not fit in LDS, else by the
+ * first dip_sim_greedy call that needs more.  Replaces any
  * earlier grouping; the next dip_sim_greedy call must then pass costs. */
 int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_group);
 
-/* Stages each rank's forward and backward inbox holds in dip_sim_greedy's
- * first launch (a candidate that overflows one is simulated again by the
- * second launch, whose inboxes hold a whole rank): k a power of two from 1 to
- * 256 fixes it; k = 0 restores the default, 8 to start with and doubled by
- * a later call when more than 1/64 of a call's candidates overflowed, and,
- * once more than half of a call's candidates overflow the largest inboxes
- * that fit in LDS, later calls skip the first launch and give every
- * candidate to the second.
+/* Size of each rank's forward and backward inbox of stages that start later:
+ * up to k / 2 of them lie in LDS beside the earliest, the rest in device
+ * memory.  k a power of two from 1 to 256 fixes it; k = 0 restores the
+ * default, 8 to start with and doubled by a later call when more than 1/64
+ * of the candidates since the last look went on into device memory, as long
+ * as the LDS holds it without losing resident waves; once more than half
+ * do at the largest such size, it stays small (greedy_inbox -1).
  * Results do not depend on k.  DIP_E_STATE before dip_sim_configure_greedy,
- * DIP_E_INVAL for another k, DIP_E_UNSUPPORTED if the inboxes do not fit in
- * LDS.  Reset by dip_sim_configure_greedy. */
+ * DIP_E_INVAL for another k, DIP_E_UNSUPPORTED if inboxes of k stages for a
+ * whole wave's candidates do not fit a block's LDS.  Reset by
+ * dip_sim_configure_greedy. */
 int dip_sim_set_greedy_inbox(dip_sim *h, int32_t k);
 
 /* Build and score one candidate per priority vector.

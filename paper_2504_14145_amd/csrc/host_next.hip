@@ -33,12 +33,14 @@ static bool greedy_layout(const dip_sim *h, int kl, bool wide, bool joins_dev,
   L->kl = kl;
   L->joins_dev = joins_dev;
   const int64_t ring = P * (2 * nwd + 1) * 8;
-  const int64_t msg = ring + P * (2 * int64_t(kl) + 1) * 8;
+  const int64_t meta = align16(ring + P * (2 * int64_t(kl) + 1) * 8);
+  const int64_t msg = meta + P * 32;
   const int64_t join = msg + (int64_t(16) << h->gr_rwl);
   const int64_t head =
       align16(std::max<int64_t>(4 * ((G + 3) & ~int64_t(3)), join + (joins_dev ? 0 : 8 * J)));
   const int64_t tab = align16(2 * G);
   L->off_ring = int32_t(ring);
+  L->off_meta = int32_t(meta);
   L->off_msg = int32_t(msg);
   L->off_join = int32_t(join);
   L->off_qof = int32_t(head);
@@ -261,10 +263,23 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
     const int64_t seen = int64_t(uint32_t(*h->h_gr_seen - h->gr_seen_last));
     h->gr_seen_last = *h->h_gr_seen;
     if (!h->gr_K_fixed && !h->gr_direct && seen * 64 > h->gr_seen_n) {
+      // (below two waves a SIMD a larger ring is not worth its waves: 2,001
+      // candidates on 32 ranks took 5.9 ms with 4 entries in LDS and all
+      // waves resident, 10.7 ms with 8 in two rounds of waves)
+      const dip_sim::GrLaunch dense = h->gr_dense, wide = h->gr_wide;
+      bool grown = false;
       if (h->gr_K < 256 && greedy_inbox_fits(h, 2 * h->gr_K, h->gr_rwl)) {
         h->gr_K *= 2;
-        (void)greedy_plan(h);
-      } else if (seen * 2 > h->gr_seen_n) {
+        grown = greedy_plan(h) &&
+                h->gr_dense.blocks_per_cu >= std::min(dense.blocks_per_cu, 8) &&
+                h->gr_wide.blocks_per_cu >= std::min(wide.blocks_per_cu, 8);
+        if (!grown) {
+          h->gr_K /= 2;
+          h->gr_dense = dense;
+          h->gr_wide = wide;
+        }
+      }
+      if (!grown && seen * 2 > h->gr_seen_n) {
         h->gr_direct = true;
         (void)greedy_plan(h);
       }
@@ -317,6 +332,7 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
   a.kg = h->gr_kg;
   a.cand_bytes = L.cand_bytes;
   a.off_ring = L.off_ring;
+  a.off_meta = L.off_meta;
   a.off_msg = L.off_msg;
   a.off_join = L.off_join;
   a.off_qof = L.off_qof;

@@ -205,7 +205,8 @@ struct dip_sim {
   struct GrLaunch {
     int kl = 4, blocks_per_cu = 0;
     bool joins_dev = false;            // join accumulators in device memory
-    int32_t cand_bytes = 0, off_ring = 0, off_msg = 0, off_join = 0, off_qof = 0, off_gof = 0;
+    int32_t cand_bytes = 0, off_ring = 0, off_meta = 0, off_msg = 0, off_join = 0, off_qof = 0,
+            off_gof = 0;
     int64_t lds = 0;
   } gr_dense, gr_wide;                 // 64 >> rwl candidates a wave; one
   int32_t gr_kg = 1;                   // device ring entries per rank and kind

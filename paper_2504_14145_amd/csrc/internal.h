@@ -357,7 +357,7 @@ struct GreedyArgs {
   int32_t nwd;              // 64-bit words of a priority-rank bitmap
   int32_t kl, kg;           // ring entries per rank and kind in LDS (a power of two), in dring
   int32_t cand_bytes;       // LDS per candidate, 16-aligned
-  int32_t off_ring, off_msg, off_join, off_qof, off_gof;   // within a candidate
+  int32_t off_ring, off_meta, off_msg, off_join, off_qof, off_gof;   // within a candidate
   uint64_t *dring;          // [resident candidate slots][P][2][kg]
   uint32_t *joins_dev;      // [resident candidate slots][J][2], or null: in LDS
   uint32_t *spill_count;    // candidates that put stages in dring (running count)

@@ -40,13 +40,18 @@
 //         next few in LDS, the rest in device memory (one region per
 //         resident candidate slot, as large as the rank's stage count, so it
 //         never fills).  97 % of the time a ring is empty or holds one stage.
+// With (start, q) as one 64-bit number, a kind's best stage is the lesser of
+// (max(ts, t_last), first of S) and the ring's first entry, and the rank's
+// choice the lesser of its two kinds, unless the kinds alternate.
 // A committing lane changes its own queue only.  What its stage completes
-// goes to the target ranks as messages, one per sender and pass: the sender
-// writes {t_start, q, kind} into its slot and sets its bit in the target's
-// mask; each target takes its messages in turn.
+// goes to the target ranks as messages, one per sender and pass.  In a wave
+// of one candidate they are read out of the senders' registers and written
+// into the targets'; in a wave of several, the sender writes its message into
+// its slot in LDS and sets its bit in the target's mask, and each target
+// takes its messages in turn.
 //
-// What bounds it: latency and vector issue of a round's serial chain (choice,
-// record, reductions, commit, messages); bandwidth is a few percent.
+// What bounds it: latency and issue of a round's serial chain (choice,
+// record, reduction, commit, messages); bandwidth is a few percent.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -63,20 +68,24 @@ constexpr uint32_t kNone = 0xffffu;        // no priority rank
 constexpr uint32_t kNever = 0xffffffffu;   // no time
 constexpr uint64_t kNoEntry = ~uint64_t(0);
 
+// one lane's value through a DPP move, `id` where no lane feeds it (every
+// lane is fed here; with the operation's identity the move and the operation
+// become one instruction)
 template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) {
-  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, false));
+__device__ __forceinline__ uint32_t dpp(uint32_t id, uint32_t v) {
+  return uint32_t(__builtin_amdgcn_update_dpp(int(id), int(v), CTRL, 0xf, 0xf, false));
 }
 
 // min / max over aligned runs of 2^WL lanes: quad permutations, then the
 // half-row and row mirrors (each lane meets the other half), then shuffles
 template <int WL, bool MAX>
 __device__ __forceinline__ uint32_t run_reduce(uint32_t v) {
+  constexpr uint32_t id = MAX ? 0u : 0xffffffffu;
   auto op = [](uint32_t x, uint32_t y) { return MAX ? max(x, y) : min(x, y); };
-  if constexpr (WL >= 1) v = op(v, dpp<0xb1>(v));    // quad_perm [1,0,3,2]
-  if constexpr (WL >= 2) v = op(v, dpp<0x4e>(v));    // quad_perm [2,3,0,1]
-  if constexpr (WL >= 3) v = op(v, dpp<0x141>(v));   // row_half_mirror
-  if constexpr (WL >= 4) v = op(v, dpp<0x140>(v));   // row_mirror
+  if constexpr (WL >= 1) v = op(v, dpp<0xb1>(id, v));    // quad_perm [1,0,3,2]
+  if constexpr (WL >= 2) v = op(v, dpp<0x4e>(id, v));    // quad_perm [2,3,0,1]
+  if constexpr (WL >= 3) v = op(v, dpp<0x141>(id, v));   // row_half_mirror
+  if constexpr (WL >= 4) v = op(v, dpp<0x140>(id, v));   // row_mirror
   if constexpr (WL >= 5) v = op(v, uint32_t(__shfl_xor(int(v), 16)));
   if constexpr (WL >= 6) v = op(v, uint32_t(__shfl_xor(int(v), 32)));
   return v;
@@ -85,8 +94,19 @@ __device__ __forceinline__ uint32_t run_reduce(uint32_t v) {
 // the same over a candidate's 2^GWL lanes, whose ranks are the first 2^RWL
 template <int RWL, int GWL, bool MAX>
 __device__ __forceinline__ uint32_t group_reduce(uint32_t v) {
+  if constexpr (GWL == 6 && RWL >= 4) {
+    // rows of 16 lanes, then their results as uniform values
+    v = run_reduce<4, MAX>(v);
+    uint32_t u = uint32_t(__builtin_amdgcn_readlane(int(v), 0));
+#pragma unroll
+    for (int i = 1; i < (1 << (RWL - 4)); ++i) {
+      const uint32_t x = uint32_t(__builtin_amdgcn_readlane(int(v), 16 * i));
+      u = MAX ? max(u, x) : min(u, x);
+    }
+    return u;
+  }
   v = run_reduce<RWL, MAX>(v);
-  if constexpr (GWL == 6 && RWL < 6) v = uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
+  if constexpr (GWL == 6) v = uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
   return v;
 }
 
@@ -98,158 +118,166 @@ __device__ __forceinline__ uint64_t group_bits(uint64_t m, int grp) {
   return (m >> (grp << GWL)) & low;
 }
 
-// Where a rank's rings lie beyond their first entry: KL entries (a power of
-// two) a kind in LDS, KG entries a kind in device memory.
-struct RingMem {
-  uint64_t *lds, *dev;
-  uint32_t kl, kg;
+// LDS accesses below are to the lane's own words unless said otherwise.
+struct RingMeta {
+  uint32_t h, n;       // head and count of the entries in LDS
+  uint32_t gh, gn;     // and in device memory
 };
 
-// One kind's queue of one rank (registers of its lane).
-struct Queue {
-  uint64_t *bits;      // S, by priority rank
-  uint64_t nz;         // its non-zero words
-  uint32_t first;      // its first member, kNone if empty
-  uint32_t ts;         // the members' t_start when that is >= t_last
-  uint64_t fr;         // the ring's first entry (t_start << 32 | q), or kNoEntry
-  uint32_t h, n;       // head and count of its entries in LDS
-  uint32_t gh, gn;     // and in device memory
-  RingMem m;
+// One rank's queues.  What every round needs lies in registers, by kind;
+// the rings beyond their first entries are touched in few rounds.
+struct Queues {
+  uint32_t first[2];   // S's first member, kNone if empty
+  uint32_t ts[2];      // its members' t_start when that is >= t_last; kNever if empty
+  uint64_t nz[2];      // its non-zero words
+  uint64_t fr[2];      // the ring's first entry (t_start << 32 | q), or kNoEntry
+  uint64_t *bits;      // [2][nwd] S, by priority rank
+  uint64_t *ring;      // [2][kl] the ring's next entries
+  RingMeta *meta;      // [2]
+  uint64_t *dev;       // [2][kg] the ring's tail
+  uint32_t nwd, kl, kg;
 
-  __device__ __forceinline__ void clear(uint64_t *b, const RingMem &mem) {
-    bits = b;
-    m = mem;
-    nz = 0;
-    first = kNone;
-    ts = 0;
-    fr = kNoEntry;
-    h = n = gh = gn = 0;
+  template <class T>
+  static __device__ __forceinline__ T get(const T (&v)[2], uint32_t kind) {
+    return kind ? v[1] : v[0];
   }
-  __device__ __forceinline__ void set(uint32_t q) {
+  template <class T>
+  static __device__ __forceinline__ void put(T (&v)[2], uint32_t kind, T x) {
+    v[0] = kind ? v[0] : x;
+    v[1] = kind ? x : v[1];
+  }
+  __device__ __forceinline__ uint64_t *words(uint32_t kind) const {
+    return bits + (kind ? nwd : 0u);
+  }
+  // the kind's best stage as start << 32 | q, all ones if none is queued
+  __device__ __forceinline__ uint64_t best(int kind, uint32_t t_last) const {
+    const uint32_t t = max(ts[kind], t_last);
+    const uint64_t s = (uint64_t(t) << 32) | first[kind];
+    const uint64_t x = fr[kind] < s ? fr[kind] : s;
+    return x;
+  }
+  // (t, q) into S, which it joins
+  __device__ __forceinline__ void join(uint32_t kind, uint32_t t, uint32_t q) {
     const uint32_t k = q >> 6;
-    bits[k] |= uint64_t(1) << (q & 63u);
-    nz |= uint64_t(1) << k;
-    first = min(first, q);
+    atomicOr(reinterpret_cast<unsigned long long *>(words(kind) + k),
+             static_cast<unsigned long long>(uint64_t(1) << (q & 63u)));
+    put(nz, kind, get(nz, kind) | (uint64_t(1) << k));
+    const uint32_t s = get(ts, kind);
+    put(ts, kind, s == kNever ? t : s);
+    put(first, kind, min(get(first, kind), q));
   }
-  // takes the first member out
-  __device__ __forceinline__ void drop_first() {
-    uint32_t k = first >> 6;
-    uint64_t w = bits[k];
+  // S's first member leaves
+  __device__ __forceinline__ void drop_first(uint32_t kind) {
+    uint64_t *b = words(kind);
+    uint32_t k = get(first, kind) >> 6;
+    uint64_t w = b[k];
     w &= w - 1;
-    bits[k] = w;
+    b[k] = w;
+    uint32_t f = k * 64u + uint32_t(__builtin_ctzll(w));
     if (w == 0) {
-      nz &= nz - 1;
-      if (nz == 0) {
-        first = kNone;
-        return;
+      const uint64_t z = get(nz, kind) & (get(nz, kind) - 1);
+      put(nz, kind, z);
+      f = kNone;
+      if (z == 0) {
+        put(ts, kind, kNever);
+      } else {
+        k = uint32_t(__builtin_ctzll(z));
+        f = k * 64u + uint32_t(__builtin_ctzll(b[k]));
       }
-      k = uint32_t(__builtin_ctzll(nz));
-      w = bits[k];
     }
-    first = k * 64u + uint32_t(__builtin_ctzll(w));
+    put(first, kind, f);
   }
-  __device__ __forceinline__ uint32_t dev_at(uint32_t i) const {
-    const uint32_t x = gh + i;
-    return x >= m.kg ? x - m.kg : x;
-  }
+  __device__ __forceinline__ uint32_t wrap(uint32_t x) const { return x >= kg ? x - kg : x; }
   // x into the sorted ring; true if an entry went to device memory
-  __device__ __forceinline__ bool ring_insert(uint64_t x) {
-    if (x < fr) {
-      const uint64_t y = fr;
-      fr = x;
-      if (y == kNoEntry) return false;
-      x = y;
+  __device__ bool ring_insert(uint32_t kind, uint64_t x) {
+    const uint64_t f = get(fr, kind);
+    if (x < f) {
+      put(fr, kind, x);
+      if (f == kNoEntry) return false;
+      x = f;
     }
-    const uint32_t mask = m.kl - 1u;
+    uint64_t *l = ring + (kind ? kl : 0u), *g = dev + (kind ? kg : 0u);
+    RingMeta m = meta[kind];
+    const uint32_t mask = kl - 1u;
     bool spilled = false;
-    if (gn > 0 || n >= m.kl) {
+    if (m.gn > 0 || m.n >= kl) {
       // (entries in device memory only ever follow a non-empty LDS part)
       spilled = true;
-      const uint64_t back = m.lds[(h + n - 1u) & mask];
+      const uint64_t back = l[(m.h + m.n - 1u) & mask];
       if (back <= x) {
-        uint32_t i = gn;
+        uint32_t i = m.gn;
         for (; i > 0; --i) {
-          const uint64_t p = m.dev[dev_at(i - 1u)];
+          const uint64_t p = g[wrap(m.gh + i - 1u)];
           if (p <= x) break;
-          m.dev[dev_at(i)] = p;
+          g[wrap(m.gh + i)] = p;
         }
-        m.dev[dev_at(i)] = x;
-        ++gn;
+        g[wrap(m.gh + i)] = x;
+        meta[kind].gn = m.gn + 1u;
         return true;
       }
       // the last entry in LDS makes room
-      gh = gh == 0 ? m.kg - 1u : gh - 1u;
-      m.dev[gh] = back;
-      ++gn;
-      --n;
+      m.gh = m.gh == 0 ? kg - 1u : m.gh - 1u;
+      g[m.gh] = back;
+      ++m.gn;
+      --m.n;
     }
-    uint32_t i = n;
+    uint32_t i = m.n;
     for (; i > 0; --i) {
-      const uint64_t p = m.lds[(h + i - 1u) & mask];
+      const uint64_t p = l[(m.h + i - 1u) & mask];
       if (p <= x) break;
-      m.lds[(h + i) & mask] = p;
+      l[(m.h + i) & mask] = p;
     }
-    m.lds[(h + i) & mask] = x;
-    ++n;
+    l[(m.h + i) & mask] = x;
+    ++m.n;
+    meta[kind] = m;
     return spilled;
   }
-  __device__ __forceinline__ void ring_pop() {
-    if (n == 0) {
-      fr = kNoEntry;
+  __device__ void ring_pop(uint32_t kind) {
+    RingMeta m = meta[kind];
+    if (m.n == 0) {
+      put(fr, kind, kNoEntry);
       return;
     }
-    const uint32_t mask = m.kl - 1u;
-    fr = m.lds[h & mask];
-    h = (h + 1u) & mask;
-    --n;
-    if (n == 0 && gn > 0) {
-      for (; n < m.kl && gn > 0; ++n, --gn) {
-        m.lds[(h + n) & mask] = m.dev[gh];
-        gh = dev_at(1u);
+    uint64_t *l = ring + (kind ? kl : 0u), *g = dev + (kind ? kg : 0u);
+    const uint32_t mask = kl - 1u;
+    put(fr, kind, l[m.h & mask]);
+    m.h = (m.h + 1u) & mask;
+    --m.n;
+    if (m.n == 0)
+      for (; m.n < kl && m.gn > 0; ++m.n, --m.gn) {
+        l[(m.h + m.n) & mask] = g[m.gh];
+        m.gh = wrap(m.gh + 1u);
       }
-    }
+    meta[kind] = m;
   }
   // whether a stage at t joins S: S is empty, or both lie before t_last, or
   // it starts with S's run
-  __device__ __forceinline__ bool joins(uint32_t t, uint32_t t_last) const {
-    return first == kNone || (ts < t_last && t < t_last) || t == ts;
+  __device__ __forceinline__ bool joins(uint32_t kind, uint32_t t, uint32_t t_last) const {
+    const uint32_t s = get(ts, kind);
+    return max(s, t) < t_last || t == s || s == kNever;
   }
-  __device__ __forceinline__ void join(uint32_t t, uint32_t q) {
-    if (first == kNone) ts = t;
-    set(q);
-  }
-  // a stage arrives; true if an entry went to device memory
-  __device__ __forceinline__ bool arrive(uint32_t t, uint32_t q, uint32_t t_last) {
-    if (joins(t, t_last)) {
-      join(t, q);
-      return false;
-    }
-    if (ts < t_last || t > ts) return ring_insert((uint64_t(t) << 32) | q);
+  // a stage that does not join S arrives; true if an entry went to device memory
+  __device__ bool arrive_late(uint32_t kind, uint32_t t, uint32_t q, uint32_t t_last) {
+    const uint32_t s = get(ts, kind);
+    if (s < t_last || t > s) return ring_insert(kind, (uint64_t(t) << 32) | q);
     // S is a run of later stages: they go to the ring, the new one takes S
     bool spilled = false;
     do {
-      spilled |= ring_insert((uint64_t(ts) << 32) | first);
-      drop_first();
-    } while (first != kNone);
-    ts = t;
-    set(q);
+      spilled |= ring_insert(kind, (uint64_t(s) << 32) | get(first, kind));
+      drop_first(kind);
+    } while (get(first, kind) != kNone);
+    join(kind, t, q);
     return spilled;
   }
   // ring entries that now belong to S
-  __device__ __forceinline__ void pull(uint32_t t_last) {
-    while (fr != kNoEntry && joins(uint32_t(fr >> 32), t_last)) {
-      join(uint32_t(fr >> 32), uint32_t(fr) & 0xffffu);
-      ring_pop();
+  __device__ void pull(uint32_t kind, uint32_t t_last) {
+    for (;;) {
+      const uint64_t f = get(fr, kind);
+      if (f == kNoEntry || !joins(kind, uint32_t(f >> 32), t_last)) break;
+      join(kind, uint32_t(f >> 32), uint32_t(f) & 0xffffu);
+      ring_pop(kind);
     }
   }
-  __device__ __forceinline__ uint32_t least() const { return first == kNone ? kNever : ts; }
-};
-
-// One rank's choice: start time, priority rank, kind (0 forward, 1 backward)
-// and whether it is the kind's first ring entry.
-struct Choice {
-  uint32_t tau, q, kind;
-  bool ring;
 };
 
 }  // namespace
@@ -269,8 +297,6 @@ __global__ __launch_bounds__(64) void greedy_kernel(GreedyArgs a) {
   unsigned char *cb = lds + int64_t(grp) * a.cand_bytes;
   int32_t *prio = reinterpret_cast<int32_t *>(cb);               // set-up only ...
   // ... then the bitmaps, rings, messages and joins
-  uint64_t *bits0 = reinterpret_cast<uint64_t *>(cb) + int64_t(rk) * (2 * a.nwd + 1);
-  uint64_t *ring0 = reinterpret_cast<uint64_t *>(cb + a.off_ring) + int64_t(rk) * (2 * a.kl + 1);
   uint64_t *msg = reinterpret_cast<uint64_t *>(cb + a.off_msg);       // [RW] one per sender
   uint64_t *mask = msg + RW;                                          // [RW] senders per target
   uint16_t *qof = reinterpret_cast<uint16_t *>(cb + a.off_qof);       // group -> priority rank
@@ -278,9 +304,14 @@ __global__ __launch_bounds__(64) void greedy_kernel(GreedyArgs a) {
   const int64_t slot0 = int64_t(blockIdx.x) * GW + grp;
   uint32_t *jtab = reinterpret_cast<uint32_t *>(cb + a.off_join);     // {latest, arrived}
   uint32_t *jdev = a.joins_dev + slot0 * 2 * a.J;                     // in their place
-  uint64_t *dev0 = a.dring + (slot0 * P + rk) * 2 * int64_t(a.kg);
-  const RingMem memF{ring0, dev0, uint32_t(a.kl), uint32_t(a.kg)};
-  const RingMem memB{ring0 + a.kl, dev0 + a.kg, uint32_t(a.kl), uint32_t(a.kg)};
+  Queues qu;
+  qu.nwd = uint32_t(a.nwd);
+  qu.kl = uint32_t(a.kl);
+  qu.kg = uint32_t(a.kg);
+  qu.bits = reinterpret_cast<uint64_t *>(cb) + int64_t(rk) * (2 * a.nwd + 1);
+  qu.ring = reinterpret_cast<uint64_t *>(cb + a.off_ring) + int64_t(rk) * (2 * a.kl + 1);
+  qu.meta = reinterpret_cast<RingMeta *>(cb + a.off_meta) + 2 * rk;
+  qu.dev = a.dring + (slot0 * P + rk) * 2 * int64_t(a.kg);
 
   const int64_t n_slots = int64_t(gridDim.x) * GW;
   for (int64_t cand = slot0;; cand += n_slots) {
@@ -353,155 +384,154 @@ __global__ __launch_bounds__(64) void greedy_kernel(GreedyArgs a) {
       }
     }
     wave_sync();
-    Queue qF, qB;
-    qF.clear(bits0, memF);
-    qB.clear(bits0 + a.nwd, memB);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      qu.first[k] = kNone;
+      qu.ts[k] = kNever;
+      qu.nz[k] = 0;
+      qu.fr[k] = kNoEntry;
+    }
     if (has) {
       if (a.joins_dev)
         for (int j = r; j < 2 * a.J; j += GL) jdev[j] = 0;
       else
         for (int j = r; j < 2 * a.J; j += GL) jtab[j] = 0;
-      if (r < RW) mask[r] = 0;
     }
+    if (r < RW) mask[r] = 0;         // (also of a group without a candidate)
     if (real) {
-      for (int i = 0; i < 2 * a.nwd; ++i) bits0[i] = 0;
+      for (int i = 0; i < 2 * a.nwd; ++i) qu.bits[i] = 0;
+      qu.meta[0] = qu.meta[1] = RingMeta{0u, 0u, 0u, 0u};
       // the stages without predecessors: t_start 0
       const int32_t *src_list = a.src + P + 1;
       for (int s = a.src[r]; s < a.src[r + 1]; ++s) {
-        const int g = src_list[s];
-        if (g >> 16)
-          qB.join(0u, qof[g & 0xffff]);
-        else
-          qF.join(0u, qof[g]);
+        const uint32_t g = uint32_t(src_list[s]);
+        qu.join(g >> 16, 0u, qof[g & 0xffffu]);
       }
     }
     if (a.joins_dev) __threadfence();
     wave_sync();
 
     uint32_t t_last = 0, last_kind = 0, n_emit = 0;
-    uint32_t rec_key = kNever;
+    uint32_t rec_q = kNone;
     int4 q0 = make_int4(0, 0, 0, 0), q1 = q0;
     int32_t live = 0, peak = 0;
     bool spilled = false, stuck = false, bad = false;
     const int32_t capr = real ? a.cap[r] : -1;
-    const int64_t row = real ? cand * a.stride + a.rank_off[r] : 0;
+    int16_t *const row = a.out_orders + (real ? cand * a.stride + a.rank_off[r] : 0);
     const uint32_t n_own = real ? uint32_t(a.rank_off[r + 1] - a.rank_off[r]) : 0u;
     int32_t left = has ? a.n_stages : 0;      // stages of the candidate to commit
+    if constexpr (GWL == 6) left = __builtin_amdgcn_readfirstlane(left);
 
-    while (__any(left > 0)) {
-      // ---- 1. this rank's choice
-      // the best stage of each kind able to start at tau: S's first, or the
-      // ring's first when it starts at tau too (beside an S before t_last)
-      const uint32_t tB = qB.least();
-      auto decide = [&](bool fw) {
-        Choice c;
-        const uint32_t tF = fw ? qF.least() : kNever;
-        const uint32_t tmin = min(tF, tB);
-        c.tau = max(t_last, tmin);
-        uint32_t bF = tF <= c.tau && fw ? qF.first : kNone;
-        uint32_t bB = tB <= c.tau ? qB.first : kNone;
-        const bool inF = fw && uint32_t(qF.fr >> 32) == c.tau && (uint32_t(qF.fr) & 0xffffu) < bF;
-        const bool inB = uint32_t(qB.fr >> 32) == c.tau && (uint32_t(qB.fr) & 0xffffu) < bB;
-        if (inF) bF = uint32_t(qF.fr) & 0xffffu;
-        if (inB) bB = uint32_t(qB.fr) & 0xffffu;
-        const bool alt = tF < t_last && tB < t_last;               // 1F1B
-        c.kind = alt ? (last_kind ^ 1u) : (bF < bB ? 0u : 1u);
-        c.q = tmin == kNever ? kNone : (c.kind ? bB : bF);
-        c.ring = c.kind ? inB : inF;
-        return c;
+    while (GWL == 6 ? left > 0 : bool(__any(left > 0))) {
+      // ---- 1. this rank's choice (lanes without a rank, and candidates that
+      // are done, have empty queues)
+      const uint64_t bF = qu.best(0, t_last), bB = qu.best(1, t_last);
+      const bool alt = max(qu.ts[0], qu.ts[1]) < t_last;            // 1F1B
+      uint32_t kind = alt ? (last_kind ^ 1u) : (bF < bB ? 0u : 1u);
+      uint64_t c = kind ? bB : bF;
+      uint32_t tau = uint32_t(c >> 32), q = uint32_t(c) & 0xffffu;
+      // its record {cost, act, local id | successors << 16, second
+      // successor's index}, {first successor}, kept while the choice stays
+      // the same
+      auto fetch = [&]() {
+        const uint32_t at = (uint32_t(gof[q]) * uint32_t(P) + uint32_t(r)) * 32u;
+        const int4 *rp =
+            reinterpret_cast<const int4 *>(reinterpret_cast<const unsigned char *>(a.rec) + at);
+        q0 = rp[0];
+        q1 = rp[1];
+        rec_q = q;
       };
-      // the record of a choice: {cost, act, local id | successors << 16,
-      // second successor's index}, {first successor}; kept while the choice
-      // stays the same
-      auto fetch = [&](const Choice &c) {
-        if (c.q != rec_key) {
-          const int4 *rp = a.rec + (int64_t(gof[c.q]) * P + r) * 2;
-          q0 = rp[0];
-          q1 = rp[1];
-          rec_key = c.q;
-        }
-      };
-      Choice ce = decide(true);
-      const bool act = left > 0 && r < P;
-      if (!act) ce.q = kNone;
-      Choice cd = ce;
-      if (ce.q != kNone) {
-        fetch(ce);
-        if (a.has_cap && ce.kind == 0 && capr >= 0 && live + q0.y > capr) {
-          cd = decide(false);                   // forward queue disabled
-          if (cd.q != kNone) fetch(cd);
+      if (q != rec_q && q != kNone) fetch();
+      uint32_t key = tau, tau_e = tau;
+      if (a.has_cap) {
+        if (q != kNone && kind == 0 && capr >= 0 && live + q0.y > capr) {
+          // the forward queue is disabled: the best backward, if there is one
+          kind = 1;
+          c = bB;
+          key = tau = uint32_t(c >> 32);
+          q = uint32_t(c) & 0xffffu;
+          if (q != kNone) fetch();
         }
       }
 
-      // ---- 2. who commits: the rank of the least t_min, and every rank
-      // whose t_min lies before the least end
-      uint32_t key = cd.q != kNone ? cd.tau : kNever;
-      const uint32_t end = cd.tau + uint32_t(q0.x);
-      uint32_t m = group_reduce<RWL, GWL, false>(key);
-      const uint32_t e_min = group_reduce<RWL, GWL, false>(cd.q != kNone ? end : kNever);
-      bool forced = false;
-      if (__any(left > 0 && m == kNever)) {
-        const uint32_t key_e = ce.q != kNone ? ce.tau : kNever;
-        const uint32_t m2 = group_reduce<RWL, GWL, false>(key_e);
-        if (m == kNever) {
-          forced = true;
-          m = m2;
-          key = key_e;
+      // ---- 2. who commits: every rank whose start lies before the least
+      // end, else the first rank of the least start (a stage without cost)
+      const uint32_t end = tau + uint32_t(q0.x);
+      const uint32_t e_min = group_reduce<RWL, GWL, false>(q != kNone ? end : kNever);
+      bool com = key < e_min;
+      uint64_t coms = group_bits<GWL>(__ballot(com), grp);
+      if (GWL == 6 ? coms == 0 : bool(__any(left > 0 && coms == 0))) {
+        const bool none = left > 0 && coms == 0;
+        uint32_t m = group_reduce<RWL, GWL, false>(key);
+        // every rank held back by its cap: the cap is lifted for one decision
+        const bool lift = none && m == kNever;
+        if (__any(lift)) {
+          const uint32_t m2 = group_reduce<RWL, GWL, false>(tau_e);
+          if (lift) {
+            m = m2;
+            key = tau_e;
+          }
+        }
+        if (none && m == kNever) {              // only a cyclic data graph gets here
+          stuck = true;
+          left = 0;
+        }
+        const uint64_t mine = group_bits<GWL>(__ballot(none && m != kNever && key == m), grp);
+        const bool win = mine != 0 && r == int(__builtin_ctzll(mine));
+        if (win && lift) {
+          // the first choice again
+          kind = bF < bB ? 0u : 1u;
+          if (alt) kind = last_kind ^ 1u;
+          c = kind ? bB : bF;
+          tau = uint32_t(c >> 32);
+          q = uint32_t(c) & 0xffffu;
+          fetch();
+        }
+        com = com || win;
+        if (none) coms = group_bits<GWL>(__ballot(win), grp);
+        if constexpr (GWL == 6) {
+          left = __builtin_amdgcn_readfirstlane(left);
+          if (coms == 0) break;
         }
       }
-      if (left > 0 && m == kNever) {            // only a cyclic data graph gets here
-        stuck = true;
-        left = 0;
-      }
-      const uint64_t mine = group_bits<GWL>(__ballot(act && m != kNever && key == m), grp);
-      const bool win = mine != 0 && r == int(__builtin_ctzll(mine));
-      const bool com = win || (!forced && key < e_min);
-      const uint64_t coms = group_bits<GWL>(__ballot(com), grp);
       left -= int32_t(__builtin_popcountll(coms));
 
       // ---- 3. commits: each lane's own queue, order and memory
       uint32_t ns = 0, t_end = 0;
       if (com) {
-        Choice c = cd;
-        if (forced) {
-          c = ce;
-          fetch(c);
-        }
-        t_end = c.tau + uint32_t(q0.x);
+        t_end = tau + uint32_t(q0.x);
         t_last = t_end;
-        last_kind = c.kind;
-        if (c.kind) {
-          if (c.ring)
-            qB.ring_pop();
-          else
-            qB.drop_first();
-        } else {
-          if (c.ring)
-            qF.ring_pop();
-          else
-            qF.drop_first();
+        last_kind = kind;
+        if (uint32_t(Queues::get(qu.fr, kind)) == q)
+          qu.ring_pop(kind);
+        else
+          qu.drop_first(kind);
+        if ((qu.fr[0] & qu.fr[1]) != kNoEntry) {
+          qu.pull(0u, t_last);
+          qu.pull(1u, t_last);
         }
-        qF.pull(t_last);
-        qB.pull(t_last);
-        live += c.kind ? -q0.y : q0.y;
-        if (c.kind == 0) peak = max(peak, live);
+        live += kind ? -q0.y : q0.y;
+        peak = kind ? peak : max(peak, live);
         if (n_emit < n_own) {
-          if (a.out_orders) a.out_orders[row + n_emit] = int16_t(q0.z & 0xffff);
+          if (a.out_orders) row[n_emit] = int16_t(q0.z & 0xffff);
         } else {
           bad = true;     // more commits than stages: never with consistent tables
         }
         ++n_emit;
         ns = uint32_t(q0.z) >> 16;
-        rec_key = kNever;
+        rec_q = kNone;
       }
 
       // ---- 4. the stages these commits complete join their ranks' queues:
       // pass s sends every committed stage's successor s
       for (uint32_t s = 0; __any(s < ns); ++s) {
         bool send = s < ns;
+        uint32_t w = 0, t = 0;
         if (send) {
-          const int4 e = s == 0 ? q1 : a.succ[q0.w + int32_t(s) - 1];
-          uint32_t t = t_end + uint32_t(e.y);
+          int4 e = q1;
+          if (s > 0) e = a.succ[q0.w + int32_t(s) - 1];
+          w = uint32_t(e.x);
+          t = t_end + uint32_t(e.y);
           if (e.z >= 0) {
             // (every lane's maximum lands before any lane's count: the lanes
             // take each of the two steps together)
@@ -519,32 +549,51 @@ __global__ __launch_bounds__(64) void greedy_kernel(GreedyArgs a) {
               if (send) t = jb[0];
             }
           }
+        }
+        // a stage arrives: word w (group, kind), start t
+        auto deliver = [&](uint32_t aw, uint32_t at) {
+          const uint32_t ak = (aw >> 16) & 1u, aq = qof[aw & 0xffffu];
+          if (qu.joins(ak, at, t_last))
+            qu.join(ak, at, aq);
+          else
+            spilled |= qu.arrive_late(ak, at, aq, t_last);
+        };
+        if constexpr (GWL == 6) {
+          uint64_t sends = __ballot(send), to = 0;
+          uint32_t aw = 0, at = 0;
+          while (sends) {
+            const int i = __builtin_ctzll(sends);
+            sends &= sends - 1;
+            const uint32_t sw = uint32_t(__builtin_amdgcn_readlane(int(w), i));
+            const uint32_t st = uint32_t(__builtin_amdgcn_readlane(int(t), i));
+            const uint32_t tr = (sw >> 17) & 63u;
+            if ((to >> tr) & 1u) {              // a second message for a rank
+              if ((to >> lane) & 1u) deliver(aw, at);
+              to = 0;
+            }
+            to |= uint64_t(1) << tr;
+            aw = uint32_t(lane) == tr ? sw : aw;
+            at = uint32_t(lane) == tr ? st : at;
+          }
+          if (__builtin_amdgcn_inverse_ballot_w64(to)) deliver(aw, at);
+        } else {
           if (send) {
-            const uint32_t w = uint32_t(e.x);
-            const uint32_t tr = (w >> 17) & 63u, tk = (w >> 16) & 1u;
-            msg[r] = (uint64_t(t) << 32) | (tk << 16) | qof[w & 0xffffu];
-            atomicOr(reinterpret_cast<unsigned long long *>(mask + tr),
+            msg[r] = (uint64_t(t) << 32) | w;
+            atomicOr(reinterpret_cast<unsigned long long *>(mask + ((w >> 17) & 63u)),
                      static_cast<unsigned long long>(uint64_t(1) << r));
           }
-        }
-        wave_lds_order();
-        uint64_t from = 0;
-        if (act) {
-          from = mask[r];
+          wave_lds_order();
+          uint64_t from = mask[r];
           if (from) mask[r] = 0;
-        }
-        while (__any(from != 0)) {
-          if (from) {
-            const uint64_t x = msg[__builtin_ctzll(from)];
-            from &= from - 1;
-            const uint32_t t = uint32_t(x >> 32), q = uint32_t(x) & 0xffffu;
-            if (uint32_t(x) & 0x10000u)
-              spilled |= qB.arrive(t, q, t_last);
-            else
-              spilled |= qF.arrive(t, q, t_last);
+          while (__any(from != 0)) {
+            if (from) {
+              const uint64_t x = msg[__builtin_ctzll(from)];
+              from &= from - 1;
+              deliver(uint32_t(x), uint32_t(x >> 32));
+            }
           }
+          wave_lds_order();
         }
-        wave_lds_order();
       }
     }
 
