@@ -11,7 +11,9 @@
 // row order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "dip_sim.h"
 
@@ -106,6 +108,164 @@ __global__ __launch_bounds__(256) void cost_table_kernel(dip_op_table t, int64_t
   }
 }
 
+// The same for up to kRegKinds kinds: a lane keeps the coefficients of CPL
+// configurations in registers.  A row's kind is uniform, so its coefficients
+// are picked by scalar branches to that kind's copy of the six operations;
+// reading them from LDS (24 bytes a lane and row) bounds the kernel above.
+// A block of four waves keeps 64 CPL configurations (brought in through LDS,
+// coalesced: lanes reading their own strided rows took as long as all the
+// arithmetic) and takes every gridDim.x-th chunk of CH items, its waves one
+// chunk at a time, since items differ in length by two orders of magnitude.
+// Rows come through the scalar cache, eight at a time.
+// 16,384 configurations x 1,280 items (93,904 rows): 0.99 -> 0.55 ms; 16
+// configurations of 1,360 items 127 -> 33 us.  The float64 instructions issue
+// every 4.8 cycles at best (0.28 ms of it here); the scalar branches, loads
+// and kind bytes of a row take the rest.
+constexpr int kRegKinds = 8;
+constexpr int kRegWaves = 4;
+
+// calls f with the constant equal to k, lo <= k < hi
+template <int LO, int HI, class F>
+__device__ __forceinline__ void with_kind(uint32_t k, const F &f) {
+  if constexpr (HI - LO == 1) {
+    f(std::integral_constant<int, LO>{});
+    // (a mark of its own keeps the copies apart: merged, they would move the
+    // coefficients into common registers first)
+    asm volatile("; operator kind %0" ::"n"(LO));
+  } else {
+    constexpr int kMid = LO + (HI - LO) / 2;
+    if (k < uint32_t(kMid))
+      with_kind<LO, kMid>(k, f);
+    else
+      with_kind<kMid, HI>(k, f);
+  }
+}
+
+template <int NK, int CPL, int CH>
+__global__ __launch_bounds__(64 * kRegWaves) void cost_table_reg_kernel(
+    dip_op_table t, int64_t n_configs, const double *coef, int32_t *out) {
+#pragma clang fp contract(off)
+  constexpr int kConfigs = 64 * CPL;
+  __shared__ double cs[kConfigs * NK * 3];
+  __shared__ int32_t next;
+  const int lane = threadIdx.x & 63;
+  const int64_t b0 = int64_t(blockIdx.y) * kConfigs;
+  const int nb = int(n_configs - b0 < kConfigs ? n_configs - b0 : kConfigs);   // >= 1
+  for (int j = threadIdx.x; j < nb * NK * 3; j += 64 * kRegWaves) cs[j] = coef[b0 * NK * 3 + j];
+  if (threadIdx.x == 0) next = 0;
+  __syncthreads();
+  double c[NK][3][CPL];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) {
+    const int b = min(lane + 64 * j, nb - 1);
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int x = 0; x < 3; ++x) c[k][x][j] = cs[b * (NK * 3) + 3 * k + x];
+  }
+  // the table is read-only for the whole launch: the constant address space
+  // sends its uniform reads through the scalar cache
+  using ConstWord = const __attribute__((address_space(4))) uint32_t;
+  using ConstInt = const __attribute__((address_space(4))) int32_t;
+  using ConstDouble = const __attribute__((address_space(4))) double;
+  const uintptr_t kaddr = reinterpret_cast<uintptr_t>(t.kind);
+  ConstWord *kw = reinterpret_cast<ConstWord *>(kaddr & ~uintptr_t(3));
+  ConstInt *ptr = reinterpret_cast<ConstInt *>(reinterpret_cast<uintptr_t>(t.item_ptr));
+  ConstDouble *nf = reinterpret_cast<ConstDouble *>(reinterpret_cast<uintptr_t>(t.n_fop));
+  ConstDouble *nm = reinterpret_cast<ConstDouble *>(reinterpret_cast<uintptr_t>(t.n_mem));
+  ConstDouble *nn = reinterpret_cast<ConstDouble *>(reinterpret_cast<uintptr_t>(t.n_net));
+  const uint32_t k0 = uint32_t(kaddr & 3);
+  const int32_t n_chunks = (t.n_items + CH - 1) / CH;
+  // whether a chunk's entries of a configuration are one aligned vector
+  const bool vec = CH == 4 && t.n_items % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  for (;;) {
+    int32_t ck = 0;
+    if (lane == 0) ck = atomicAdd(&next, 1);
+    ck = __builtin_amdgcn_readfirstlane(ck) * int32_t(gridDim.x) + int32_t(blockIdx.x);
+    if (ck >= n_chunks) break;
+    int32_t val[CPL][CH] = {};
+    for (int e = 0; e < CH; ++e) {
+      const int32_t i = ck * CH + e;
+      if (i >= t.n_items) break;
+      const int32_t r0 = max(ptr[i], 0), r1 = min(ptr[i + 1], t.n_rows);
+      double s[CPL];
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) s[j] = 0.0;
+      bool bad = false;
+      auto row = [&](uint32_t k, double f, double m, double n) {
+        with_kind<0, NK>(k, [&](auto kind) {
+          constexpr int kk = decltype(kind)::value;
+#pragma unroll
+          for (int j = 0; j < CPL; ++j) {
+            const double a = c[kk][0][j] * f, b = c[kk][1][j] * m, d = c[kk][2][j] * n;
+            s[j] = s[j] + fmax(fmax(a, b), d);
+          }
+        });
+      };
+      int32_t r = r0;
+      // (the kind bytes of eight rows as in the kernel above; a kind out of
+      // range marks the item and is priced as the last one)
+      for (; r + 7 < r1; r += 8) {
+        const uint32_t at = k0 + uint32_t(r), sh = (at & 3u) * 8u;
+        const uint64_t wa = kw[at >> 2], wb = kw[(at >> 2) + 1], wc = kw[(at + 7) >> 2];
+        const uint64_t k8 = uint64_t(uint32_t((wa | (wb << 32)) >> sh)) |
+                            (uint64_t(uint32_t((wb | (wc << 32)) >> sh)) << 32);
+        // a byte's top bit is set by adding 128 - NK when its low seven bits
+        // reach NK, or is set already
+        constexpr uint64_t kLow = 0x7f7f7f7f7f7f7f7full;
+        bad |= ((((k8 & kLow) + (0x8080808080808080ull - NK * 0x0101010101010101ull)) | k8) & ~kLow) != 0;
+        double f[8], m[8], n[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          f[j] = nf[r + j];
+          m[j] = nm[r + j];
+          n[j] = nn[r + j];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) row(uint32_t(k8 >> (8 * j)) & 0xffu, f[j], m[j], n[j]);
+      }
+      for (; r < r1; ++r) {
+        const uint32_t at = k0 + uint32_t(r);
+        const uint32_t k = (kw[at >> 2] >> ((at & 3u) * 8u)) & 0xffu;
+        bad |= k >= uint32_t(NK);
+        row(k, nf[r], nm[r], nn[r]);
+      }
+#pragma unroll
+      for (int j = 0; j < CPL; ++j) {
+        const double us = ceil(s[j] * 1e6);
+        const int32_t x = (bad || !(us <= 2147483647.0)) ? -1 : int32_t(us);
+        for (int q = 0; q < CH; ++q) val[j][q] = q == e ? x : val[j][q];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      const int b = lane + 64 * j;
+      int32_t *o = out + (b0 + b) * t.n_items + ck * CH;
+      if (b < nb && vec)
+        *reinterpret_cast<int4 *>(o) = make_int4(val[j][0], val[j][CH > 1 ? 1 : 0],
+                                                 val[j][CH > 2 ? 2 : 0], val[j][CH > 3 ? 3 : 0]);
+      for (int e = 0; e < CH; ++e)
+        if (b < nb && !vec && ck * CH + e < t.n_items) o[e] = val[j][e];
+    }
+  }
+}
+
+template <int CPL, int CH>
+void launch_reg(const dim3 &grid, hipStream_t s, const dip_op_table &t, int64_t n_configs,
+                const double *coef, int32_t *out) {
+  const dim3 block(64 * kRegWaves);
+  switch (t.n_kinds) {
+    case 1: cost_table_reg_kernel<1, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 2: cost_table_reg_kernel<2, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 3: cost_table_reg_kernel<3, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 4: cost_table_reg_kernel<4, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 5: cost_table_reg_kernel<5, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 6: cost_table_reg_kernel<6, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    case 7: cost_table_reg_kernel<7, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+    default: cost_table_reg_kernel<8, CPL, CH><<<grid, block, 0, s>>>(t, n_configs, coef, out); break;
+  }
+}
+
 }  // namespace
 
 extern "C" int dip_cost_tables(const dip_op_table *t, int64_t n_configs, const double *coef,
@@ -126,6 +286,34 @@ extern "C" int dip_cost_tables(const dip_op_table *t, int64_t n_configs, const d
   const int64_t gy = (n_configs + kConfigsPerBlock - 1) / kConfigsPerBlock;
   if (gx > INT32_MAX || gy > 65535) return DIP_E_INVAL;
   const dim3 grid{unsigned(gx), unsigned(gy), 1u};
+  if (t->n_kinds <= kRegKinds) {
+    // four configurations a lane from 257 up (two waves a SIMD; 4,000 of them
+    // take 172 us, at two a lane 209), two from 65 (four waves; 100 of them
+    // 39 us, at four a lane 49), else one; the blocks that are resident at once, so that each
+    // brings its coefficients in once, and items by fours where every wave
+    // still gets several chunks
+    const int cpl = n_configs > 256 ? 4 : n_configs > 64 ? 2 : 1;
+    const int64_t ry = (n_configs + 64 * cpl - 1) / (64 * cpl);
+    if (ry <= 65535) {
+      const int64_t resident = cpl == 4 ? 512 : 1024;
+      const bool four = int64_t(t->n_items) * ry >= 16 * kRegWaves * resident;
+      const int64_t chunks = four ? (int64_t(t->n_items) + 3) / 4 : t->n_items;
+      const int64_t rx = std::max<int64_t>(
+          1, std::min<int64_t>((chunks + kRegWaves - 1) / kRegWaves, (resident + ry - 1) / ry));
+      const dim3 rgrid{unsigned(rx), unsigned(ry), 1u};
+      hipStream_t s = static_cast<hipStream_t>(stream);
+      if (cpl == 4)
+        four ? launch_reg<4, 4>(rgrid, s, *t, n_configs, coef, out)
+             : launch_reg<4, 1>(rgrid, s, *t, n_configs, coef, out);
+      else if (cpl == 2)
+        four ? launch_reg<2, 4>(rgrid, s, *t, n_configs, coef, out)
+             : launch_reg<2, 1>(rgrid, s, *t, n_configs, coef, out);
+      else
+        four ? launch_reg<1, 4>(rgrid, s, *t, n_configs, coef, out)
+             : launch_reg<1, 1>(rgrid, s, *t, n_configs, coef, out);
+      return hipGetLastError() == hipSuccess ? DIP_OK : DIP_E_HIP;
+    }
+  }
   if (t->n_kinds <= kLdsKinds)
     hipLaunchKernelGGL(cost_table_kernel<true>, grid, dim3(256),
                        size_t(t->n_kinds) * 3 * kConfigsPerBlock * 8, static_cast<hipStream_t>(stream),
