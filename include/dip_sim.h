@@ -156,8 +156,8 @@ int dip_sim_create(const dip_topology *topo, dip_sim **out);
  * check kernel (permutation, peak memory, cap) followed by the pool kernel,
  * which hands end times between ranks through per-rank pools of a few
  * slots, and by a general kernel for the candidates whose pools filled up.
- * Variant 9 (the automatic choice where it fits: variant 8's topology limits,
- * a power-of-two rank count and at most 8,192 ops per rank): the same check,
+ * Variant 9 (the automatic choice where it fits: variant 8's topology limits
+ * and at most 8,192 ops per rank): the same check,
  * then the simulation kernel with compact op records and the pools in LDS,
  * a second pass of it with 16 slots per pool over the candidates whose pools
  * filled, a third with 32 slots, and a general kernel for those that filled

@@ -16,8 +16,7 @@
 //                 the pool kernel: compact op records resident in LDS and the
 //                 orders staged through per-lane LDS rings, then a second
 //                 pass with 16 pool slots before the general kernel.  It
-//                 needs a power-of-two rank count, at most 8192 ops per rank,
-//                 and per call costs below 2^20 and latencies below 2^11
+//                 needs at most 8192 ops per rank, and per call costs below 2^20 and latencies below 2^11
 //                 (checked whenever costs change; a call outside them runs
 //                 variant 8).
 #pragma once

@@ -105,7 +105,7 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
     const int32_t p = h->pred_op[k];
     const int32_t r = h->rank_of[g], rp = h->rank_of[p];
     const int32_t d = (p - h->rank_off[rp]) - (g - h->rank_off[r]);
-    const uint32_t dr = uint32_t((rp - r + P) % P);
+    const uint32_t dr = uint32_t(rp - r) & uint32_t((1 << h->pwl) - 1);
     return dr | ((uint32_t(d) & 0x3fffu) << 6) | (uint32_t(c->edge_comm[k]) << 20) |
            (last ? kSimLast : 0u);
   };

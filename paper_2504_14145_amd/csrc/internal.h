@@ -244,7 +244,7 @@ hipError_t launch_pool(int pwl, int slots, bool tab, int blocks, int wpb, size_t
 //   w1 = the edge word of its only predecessor, or, with several, the index
 //        of its first edge word in the extra-edge table (the rest follow, the
 //        last one marked)
-// Edge word: (pred rank - own rank) mod P (bits 0-5) | pred local id - own
+// Edge word: (pred rank - own rank) mod PW, the group's lanes (bits 0-5) | pred local id - own
 //   local id (6-19, two's complement) | latency (20-30) | last (31).
 constexpr uint32_t kSimCostBits = 20;
 constexpr uint32_t kSimCostMax = (1u << kSimCostBits) - 1;
@@ -260,7 +260,7 @@ constexpr int kSimPage = 16;
 constexpr int kSimMaxPages = 4096;
 
 // Per-candidate LDS state of the simulation kernel, for a group of PW lanes
-// (one per rank; the kernel requires P == PW):
+// (the first P of them play the ranks):
 //   tags   [S / 8][PW][8] 16-bit (local id + 1 of the op whose end time a pool
 //          slot holds; slots 8h .. 8h + 7 of all ranks together, 16 bytes per
 //          rank, so that a group's 16-byte tag reads tile the banks; with

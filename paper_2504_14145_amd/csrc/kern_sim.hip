@@ -1,6 +1,6 @@
 // kern_sim.hip -- timing simulation of candidate schedules, one wavefront
-// holding 64 / PW candidates, lane r of a candidate's group playing rank r
-// (the number of ranks P is a power of two, PW = P).
+// holding 64 / PW candidates (PW the rank count's next power of two), lane r
+// of a candidate's group playing rank r; lanes past the last rank never live.
 //
 // What is simulated (Sec. 5.2 and 6.1): every rank runs its ops one at a
 // time in its given order, each op as soon as the rank is free and the
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
 
     // ---- reads: the predecessor's pool, my counts, the next id
     // (the predecessor's rank: the rank difference sits in the edge word's
-    // low bits, and P == PW)
+    // low bits, modulo PW)
     const uint32_t pr = (ce + rr) & uint32_t(PW - 1);
     const uint32_t pool = gbase + kPools + pr * kPool;
     const uint32_t p_tags = gbase + pr * kTagRank;

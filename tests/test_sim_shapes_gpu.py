@@ -1,0 +1,59 @@
+"""GPU parity of the simulation kernel on rank counts that leave lanes of a
+candidate's group without a rank, and on batches from one candidate up, with
+orders that deadlock, fill pools and exceed caps."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2504_14145_amd as dip
+
+DEV = "cuda:0"
+
+
+def instance(P, M, v, seed):
+    rng = np.random.default_rng([P, M, v, seed])
+    inst = W.pipeline_instance(P, M, rng.integers(0, 50, (P * v, M)), comm=int(rng.integers(0, 9)),
+                               act=2, v=v, mem_cap=M + 2)
+    return W.compile_instance(inst), rng
+
+
+def rows_of(prob, n, rng):
+    """List schedules, a third of them with swaps, a third random permutations."""
+    gen = W.OrderGenerator(prob, W.MODE_LIST, 3, 0, 11, 0)
+    rows = gen.generate(0, n)
+    for c in range(0, n, 3):
+        for r in range(prob.n_ranks):
+            a, b = int(prob.rank_off[r]), int(prob.rank_off[r + 1])
+            rows[c, a:b] = rng.permutation(b - a)
+    return rows
+
+
+def compare(prob, rows, configure=None):
+    want = O.evaluate(prob, rows, threads=16)
+    sim = dip.Sim(prob)
+    if configure:
+        configure(sim)
+    out = sim.evaluate(torch.from_numpy(rows).to(DEV))
+    torch.cuda.synchronize()
+    assert sim.info["variant"] == 9
+    for got, exp in zip(out, (want.makespan, want.bubble, want.peak, want.flags)):
+        np.testing.assert_array_equal(got.cpu().numpy(), exp)
+    sim.close()
+
+
+@pytest.mark.parametrize("P", [3, 5, 7, 12, 17, 24, 33, 48, 63])
+@pytest.mark.parametrize("M,v", [(1, 1), (9, 1), (6, 3)])
+def test_any_rank_count(P, M, v):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    prob, rng = instance(P, M, v, 1)
+    rows = rows_of(prob, 150, rng)
+    print(f"P={P} M={M} v={v} N={prob.n_total}", flush=True)
+    for slots in (4, 0, 16):
+        compare(prob, rows, lambda s: s.configure_pool(slots))
