@@ -420,6 +420,7 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
     };
     const int64_t *retry_list = sx->list_a;
     const uint32_t *retry_count = counts;
+    int last_slots = 0;   // pool slots of the last pass that ran
     h->last_stream = stream;
     h->last_general = 0;
     if (h->variant == 9 && h->sim_costs_ok) {
@@ -437,16 +438,43 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       a.lane_info = reinterpret_cast<const int32_t *>(h->d_sim_lane);
       a.state_base = uint32_t(h->sim_state_base);
       a.P = h->P;
-      a.wpb = h->sim_wpb;
       a.retry = sx->list_a;
       a.retry_count = counts;
       a.round_limit = round_limit;
-      const int64_t per_block = int64_t(h->sim_wpb) * h->G;
-      const int blocks =
-          int(std::min<int64_t>((n_cand + per_block - 1) / per_block, h->sim_max_blocks));
+      // The first pass's shape.  A rank that publishes at most S end times
+      // never fills a pool of S slots: where 16 slots are that many and the
+      // batch fits the groups resident with them, they run at once, since
+      // nothing is left for the later passes then (1,024 candidates of 16 ops
+      // a rank: six launches instead of three, 39 against 25 us with the
+      // argmin).
+      int slots = h->pool_slots, wpb = h->sim_wpb, max_blocks = h->sim_max_blocks;
+      int64_t lds = h->sim_lds;
+      if (h->forced_pool_slots == 0 && slots < 16 && h->sim2_ok && h->sim_max_pub > slots &&
+          h->sim_max_pub <= 16 && n_cand <= int64_t(h->sim2_max_blocks) * h->sim2_wpb * h->G) {
+        slots = 16;
+        wpb = h->sim2_wpb;
+        max_blocks = h->sim2_max_blocks;
+        lds = h->sim2_lds;
+      }
+      int64_t per_block = int64_t(wpb) * h->G;
+      int blocks = int(std::min<int64_t>((n_cand + per_block - 1) / per_block, max_blocks));
+      if (n_cand <= int64_t(max_blocks) * per_block && h->forced_wpb == 0) {
+        // a batch within the resident groups spreads over the CUs; the waves
+        // of a block are what its share needs, and what copies the table in
+        // some eight steps
+        const int64_t tab = int64_t(h->sim_tab_vec) * 16;
+        const int64_t share = (n_cand + h->n_cu - 1) / h->n_cu;
+        const int w = int(std::min<int64_t>(wpb, std::max<int64_t>(share, (tab + 8191) / 8192)));
+        lds -= int64_t(wpb - w) * h->G * sim_group_bytes(1 << h->pwl, slots);
+        wpb = w;
+        per_block = int64_t(w) * h->G;
+        blocks = int(std::min<int64_t>(n_cand, std::max<int64_t>(h->n_cu, (n_cand + per_block - 1) / per_block)));
+        a.spread = 1;
+      }
+      a.wpb = wpb;
       a.static_end = static_end_for(int64_t(blocks) * per_block);
-      DIP_HIP(launch_sim(h->pwl, h->pool_slots, h->sim_paged, blocks, h->sim_wpb,
-                         size_t(h->sim_lds), stream, a));
+      DIP_HIP(launch_sim(h->pwl, slots, h->sim_paged, blocks, wpb, size_t(lds), stream, a));
+      const bool can_fill = h->sim_max_pub > slots;   // pools of the first pass
       DIP_HIP(mark(2));
       // The candidates whose pools filled, again with 16 and then 32 slots
       // per pool (deadlocked orders fill small pools too; larger ones tell
@@ -470,12 +498,14 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
         }
         return DIP_OK;
       };
-      if ((rc = pass(h->sim2_ok, 16, h->sim2_wpb, h->sim2_max_blocks, h->sim2_lds, 2)) != DIP_OK)
+      if ((rc = pass(h->sim2_ok && can_fill, 16, h->sim2_wpb, h->sim2_max_blocks, h->sim2_lds, 2)) != DIP_OK)
         return rc;
       DIP_HIP(mark(3));
-      if ((rc = pass(h->sim3_ok, 32, h->sim3_wpb, h->sim3_max_blocks, h->sim3_lds, 4)) != DIP_OK)
+      if ((rc = pass(h->sim3_ok && h->sim_max_pub > (can_fill && h->sim2_ok ? 16 : slots), 32,
+                     h->sim3_wpb, h->sim3_max_blocks, h->sim3_lds, 4)) != DIP_OK)
         return rc;
       DIP_HIP(mark(4));
+      last_slots = h->last_general == 4 ? 32 : h->last_general == 2 ? 16 : slots;
     } else {
       PoolArgs a{};
       a.orders = orders;
@@ -507,6 +537,14 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       DIP_HIP(mark(2));
     }
 
+    // nothing is left when no rank publishes more than the last pass's pools
+    // hold (a candidate is put on the list for full pools only; its rounds
+    // never reach round_limit, since every round before a stall fires an op or
+    // reads an item)
+    if (last_slots > 0 && h->sim_max_pub <= last_slots) {
+      DIP_HIP(mark(h->prof_n));
+      return DIP_OK;
+    }
     GeneralArgs f{};
     f.orders = orders;
     f.n_cand = n_cand;

@@ -80,6 +80,7 @@ struct dip_sim {
   std::vector<int32_t> self_pred;      // [N] its local id + 1, 0 if none
   int32_t *d_selfp = nullptr;
   bool sim_drop_self = false;          // the current sim tables dropped them
+  int32_t sim_max_pub = 0;             // most ops of one rank whose end time is read
   std::vector<int32_t> last_cost, last_comm, last_act;   // the last costs (host copies)
   std::vector<int32_t> n_cons;         // [N] consumers of each op
   bool pool_ok = false;                // topology fits the pool kernel

@@ -98,6 +98,12 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
   for (int32_t g = 0; g < h->N; ++g)
     for (int32_t k = h->pred_ptr[g]; k < h->pred_ptr[g + 1]; ++k)
       if (!dropped(g, k)) ++readers[h->pred_op[k]];
+  h->sim_max_pub = 0;
+  for (int r = 0; r < P; ++r) {
+    int32_t pub = 0;
+    for (int32_t g = h->rank_off[r]; g < h->rank_off[r + 1]; ++g) pub += readers[g] > 0 ? 1 : 0;
+    h->sim_max_pub = std::max(h->sim_max_pub, pub);
+  }
   std::vector<uint32_t> rec(size_t(h->N) * 2), extra;
   extra.reserve(size_t(std::max(h->sim_n_extra, 1)));
   std::vector<int32_t> kept;

@@ -322,6 +322,8 @@ struct SimArgs {
                              // go to fixed successors, the rest are handed out on
                              // demand through retry_count[1]; INT64_MAX: none
   uint32_t round_limit;      // rounds one candidate may take
+  int32_t spread;            // neighbouring candidates go to different blocks (a
+                             // list always does so)
 };
 bool sim_slots_ok(int slots);
 const void *sim_kernel_ptr(int pwl, int slots, bool paged);

@@ -237,7 +237,6 @@ __global__ __launch_bounds__(64 * kRegWaves) void cost_table_reg_kernel(
         for (int q = 0; q < CH; ++q) val[j][q] = q == e ? x : val[j][q];
       }
     }
-#pragma unroll
     for (int j = 0; j < CPL; ++j) {
       const int b = lane + 64 * j;
       int32_t *o = out + (b0 + b) * t.n_items + ck * CH;

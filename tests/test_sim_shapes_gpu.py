@@ -57,3 +57,19 @@ def test_any_rank_count(P, M, v):
     print(f"P={P} M={M} v={v} N={prob.n_total}", flush=True)
     for slots in (4, 0, 16):
         compare(prob, rows, lambda s: s.configure_pool(slots))
+
+
+@pytest.mark.parametrize("P,M,v", [(4, 8, 1), (4, 9, 1), (4, 16, 1), (4, 17, 1), (4, 33, 1),
+                                   (8, 20, 3), (16, 5, 2), (64, 8, 1), (64, 30, 1)])
+@pytest.mark.parametrize("n", [1, 3, 65, 257, 2500])
+def test_small_batches_and_pool_bounds(P, M, v, n):
+    """Batches within the resident groups (spread over the blocks), and rank
+    publishing counts below, at and above the pools' sizes (8, 16 and 32
+    slots), where the later passes are left out or run."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    prob, rng = instance(P, M, v, 2)
+    rows = rows_of(prob, n, rng)
+    print(f"P={P} M={M} v={v} n={n}", flush=True)
+    compare(prob, rows)
+    compare(prob, rows, lambda s: s.configure_pool(4))
