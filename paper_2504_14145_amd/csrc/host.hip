@@ -73,7 +73,19 @@ void release_rollouts(dip_sim *h) {
   h->rl_ok = false;
 }
 
+void release_selected(dip_sim *h) {
+  if (h->d_sel_x) (void)hipFree(h->d_sel_x);
+  if (h->d_sel_list) (void)hipFree(h->d_sel_list);
+  if (h->d_sel_count) (void)hipFree(h->d_sel_count);
+  h->d_sel_x = nullptr;
+  h->d_sel_list = nullptr;
+  h->d_sel_count = nullptr;
+  h->sel_rows = 0;
+  h->sel_planned = false;
+}
+
 void release_memopt(dip_sim *h) {
+  release_selected(h);
   if (h->d_mo_pair_off) (void)hipFree(h->d_mo_pair_off);
   if (h->d_mo_lid_pair) (void)hipFree(h->d_mo_lid_pair);
   if (h->d_mo_time) (void)hipFree(h->d_mo_time);

@@ -309,6 +309,11 @@ int run_tile_check(dip_sim *h, const int16_t *orders, int64_t n_cand, int32_t *o
   const int blocks = int(std::min<int64_t>(tiles, int64_t(T.blocks_per_cu) * h->n_cu));
   DIP_HIP(launch_tile_check(std::max(blocks, 1), T.nw, size_t(T.lds), stream, c));
   if (!h->to_ok) return DIP_OK;
+  return run_order_check(h, orders, n_cand, out_ms, out_bub, out_flags, stream);
+}
+
+int run_order_check(dip_sim *h, const int16_t *orders, int64_t n_cand, int32_t *out_ms,
+                    int32_t *out_bub, uint8_t *out_flags, hipStream_t stream) {
   OrderCheckArgs o{};
   o.orders = orders;
   o.n_cand = n_cand;
@@ -429,10 +434,11 @@ int apply_pick(dip_sim *h, const Pick &p, int *variant, int *wpb, int *max_block
 // Launch shape of the simulation kernel for the current table image and a
 // pool size: the waves per block (one table copy per block) that keep the
 // most waves resident per CU, fewer blocks on ties.  false if nothing fits.
-bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out) {
+bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out,
+               bool sel) {
   const int64_t tab = int64_t(h->sim_tab_vec) * 16;
-  const int64_t grp = sim_group_bytes(1 << h->pwl, slots);
-  const void *k = sim_kernel_ptr(h->pwl, slots, h->sim_paged);
+  const int64_t grp = sim_group_bytes(1 << h->pwl, slots, sel);
+  const void *k = sim_kernel_ptr(h->pwl, slots, h->sim_paged, sel);
   int best_w = 0, best_nb = 0;
   for (int w = 16; w >= 1; --w) {
     if (forced_wpb && w != forced_wpb) continue;
@@ -471,6 +477,7 @@ bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks,
 // fit.
 int sim_plan(dip_sim *h) {
   h->sim_costs_ok = false;
+  h->sel_planned = false;
   h->sim2_ok = false;
   h->sim3_ok = false;
   h->sim_state_base = int64_t(h->sim_tab_vec) * 16;

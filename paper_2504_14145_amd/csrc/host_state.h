@@ -106,6 +106,16 @@ struct dip_sim {
   int sim2_wpb = 1, sim2_max_blocks = 1;
   int64_t sim2_lds = 0;
   int64_t *d_retry2 = nullptr;         // candidates the second pass could not hold
+  // re-timed simulation of a memory selection: 8-slot pools, then 32
+  bool sel_planned = false;            // the shapes below are the current costs'
+  bool sel_ok = false;
+  int sel_wpb[2] = {1, 1}, sel_max_blocks[2] = {1, 1};
+  int64_t sel_lds[2] = {0, 0};
+  int64_t sel_total = 0;               // op costs, latencies and largest extra times together
+  int32_t *d_sel_x = nullptr;          // [sel_rows][stride] extra costs
+  int64_t *d_sel_list = nullptr;       // two retry lists of sel_rows
+  uint32_t *d_sel_count = nullptr;     // [kRetryCounters]
+  int64_t sel_rows = 0;
   // third pass over what the earlier ones could not hold, with 32-slot pools
   bool sim3_ok = false;
   int sim3_wpb = 1, sim3_max_blocks = 1;
@@ -285,7 +295,10 @@ int ensure_retry(dip_sim *h, int64_t n);
 Pick best_of(dip_sim *h, int v_lo, int v_hi, int forced_wpb);
 int apply_pick(dip_sim *h, const Pick &p, int *variant, int *wpb, int *max_blocks,
                int64_t *lds);
-bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out);
+bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out,
+               bool sel = false);
+int run_order_check(dip_sim *h, const int16_t *orders, int64_t n_cand, int32_t *out_ms,
+                    int32_t *out_bub, uint8_t *out_flags, hipStream_t stream);
 int sim_plan(dip_sim *h);
 int choose_config(dip_sim *h);
 int64_t sim_tab_bound(const dip_sim *h);
@@ -299,6 +312,7 @@ bool greedy_plan(dip_sim *h);
 void release_rollout_memopt(dip_sim *h);
 void release_rollouts(dip_sim *h);
 void release_memopt(dip_sim *h);
+void release_selected(dip_sim *h);
 void release_greedy(dip_sim *h);
 void release(dip_sim *h);
 

@@ -273,6 +273,12 @@ constexpr int kSimMaxPages = 4096;
 //          (and an 8-byte pad)
 constexpr int64_t kSimBlockIds = 8;
 constexpr int64_t kSimRingBytes = 40;
+// with extra costs (SimArgs::xcost) a lane's ring also holds its two blocks'
+// extra costs, 4 bytes an op (and an 8-byte pad)
+constexpr int64_t kSimRingExtra = 72;
+__host__ __device__ constexpr int64_t sim_ring_bytes(bool sel) {
+  return kSimRingBytes + (sel ? kSimRingExtra : 0);
+}
 __host__ __device__ constexpr int64_t sim_count_words(int slots) { return (slots + 7) / 8; }
 __host__ __device__ constexpr int64_t sim_tag_bytes(int pw, int slots) { return int64_t(pw) * 2 * slots; }
 __host__ __device__ constexpr int64_t sim_pool_bytes(int slots) {
@@ -288,8 +294,8 @@ __host__ __device__ constexpr int64_t sim_ring_offset(int pw, int slots) {
 // padded so that the group's size in words is congruent to PW modulo the 32
 // banks (4 words below 4 lanes): the same word of consecutive groups then
 // falls in different banks
-__host__ __device__ constexpr int64_t sim_group_bytes(int pw, int slots) {
-  const int64_t raw = sim_ring_offset(pw, slots) + int64_t(pw) * kSimRingBytes;
+__host__ __device__ constexpr int64_t sim_group_bytes(int pw, int slots, bool sel = false) {
+  const int64_t raw = sim_ring_offset(pw, slots) + int64_t(pw) * sim_ring_bytes(sel);
   const int64_t want = pw >= 32 ? 0 : 4 * (pw < 4 ? 4 : pw);   // residue modulo 128 bytes
   int64_t x = (raw + 15) / 16 * 16;
   while (x % 128 != want) x += 16;
@@ -324,11 +330,43 @@ struct SimArgs {
   uint32_t round_limit;      // rounds one candidate may take
   int32_t spread;            // neighbouring candidates go to different blocks (a
                              // list always does so)
+  // re-timed simulation (a kernel of its own, chosen by `sel` below): each
+  // op's cost beyond its record's, laid out as the orders; out_bub holds the
+  // rank's sum of them on entry
+  const int32_t *xcost;
 };
 bool sim_slots_ok(int slots);
-const void *sim_kernel_ptr(int pwl, int slots, bool paged);
+// sel: the re-timed simulation, with 8 or 32 slots
+const void *sim_kernel_ptr(int pwl, int slots, bool paged, bool sel = false);
 hipError_t launch_sim(int pwl, int slots, bool paged, int blocks, int wpb, size_t lds,
-                      hipStream_t s, const SimArgs &a);
+                      hipStream_t s, const SimArgs &a, bool sel = false);
+
+// ---------------------------------------------------------------- selection check
+// Schedules under a memory selection before their re-timed simulation:
+// permutation and choice check, peak memory and cap flag from the chosen
+// memories, each op's extra cost along the order, and its sum per rank (see
+// kern_selcheck.hip).
+struct SelCheckArgs {
+  const int16_t *orders;
+  int64_t n_cand;
+  int64_t stride;
+  const uint8_t *choice;     // [n_cand][n_pairs]
+  int32_t n_pairs;
+  const int32_t *lid_pair;   // [N] pair index on its rank | kind << 31
+  const int32_t *pair_off;   // [P+1]
+  const int64_t *cand_time;  // [n_pairs][kMemoptMaxCands]
+  const int32_t *cand_mem;
+  const uint32_t *cand_key;
+  const int32_t *rank_off;   // [P+1]
+  const int32_t *cap;        // [P]
+  int32_t P;
+  int32_t bm_words;          // words of a rank's op-id bitmap
+  int32_t *xcost;            // [n_cand][stride] out
+  int32_t *out_ms, *out_bub, *out_peak;   // out_bub: the extra costs' sums
+  uint8_t *out_flags;
+  uint32_t *retry_count;     // [kRetryCounters] zeroed
+};
+hipError_t launch_selcheck(int waves, hipStream_t s, const SelCheckArgs &a);
 
 // ---------------------------------------------------------------- greedy
 // Dual-queue stage interleaving (see kern_greedy.hip).  Groups are numbered

@@ -135,7 +135,9 @@ __device__ __forceinline__ uint32_t tag_weighted_misses(const uint32_t (&tw)[S /
   return sum;
 }
 
-template <int PWL, int S, bool PAGED>
+// SEL: the re-timed simulation of a memory selection, where every op has an
+// extra cost of its own in its candidate; they are staged as the ids are.
+template <int PWL, int S, bool PAGED, bool SEL = false>
 __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   constexpr int PW = 1 << PWL;
   constexpr int G = kWave / PW;
@@ -145,7 +147,8 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   constexpr uint32_t kTagRank = S == 4 ? 8u : 16u;   // a rank's tag bytes in one tag array
   constexpr uint32_t kEndAt = 4u * uint32_t(kC);      // end times after a pool's counts
   constexpr uint32_t kRing = uint32_t(sim_ring_offset(PW, S));
-  constexpr uint32_t kGroup = uint32_t(sim_group_bytes(PW, S));
+  constexpr uint32_t kGroup = uint32_t(sim_group_bytes(PW, S, SEL));
+  constexpr uint32_t kRingBytes = uint32_t(sim_ring_bytes(SEL));
   static_assert(S == 4 || S == 8 || S == 16 || S == 32, "pool size");
 
   // the tables into LDS, once per block
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   const uint32_t rr = on ? uint32_t(r) : 0u;
   const uint32_t my_pool = gbase + kPools + rr * kPool;
   const uint32_t my_tags = gbase + rr * kTagRank;
-  const uint32_t my_ring = gbase + kRing + rr * uint32_t(kSimRingBytes);
+  const uint32_t my_ring = gbase + kRing + rr * kRingBytes;
   int rb = 0, nr = 0, busy_r = 0, recb = 0;
   if (on) {
     const int4 li = reinterpret_cast<const int4 *>(a.lane_info)[r];
@@ -192,6 +195,11 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   };
   const uint32_t my_ring_abs = lds_abs(my_ring);
   auto ring_id = [&](uint32_t pos) { return lds16_at(shl_add<1>(pos & 15u, my_ring_abs)); };
+  // (SEL) the ring's extra costs: block b at kSimRingBytes + 32 (b & 1)
+  auto ring_x = [&](uint32_t pos) -> uint32_t {
+    if constexpr (SEL) return lds32(my_ring + uint32_t(kSimRingBytes) + 4u * (pos & 15u));
+    return 0u;
+  };
 
   // candidates: positions k < n of the batch, or of the list in list mode
   const int64_t n_todo = a.list ? int64_t(*a.list_count) : a.n_cand;
@@ -216,7 +224,24 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   uint32_t ce = 0, xi = 0;      // its current edge word; index of its next extra edge
   uint32_t lb = 0;         // next absolute order block to load
   uint4 blk{};             // a loaded block waiting to be stored
+  uint4 xb0{}, xb1{};      // (SEL) its extra costs
+  uint32_t curx = 0;       // (SEL) the current op's extra cost
   const int16_t *row = a.orders;
+  const int32_t *xrow = a.xcost;
+  auto load_x = [&](uint32_t b) {
+    if constexpr (SEL) {
+      const uint4 *q = reinterpret_cast<const uint4 *>(xrow + int64_t(b) * kSimBlockIds);
+      xb0 = q[0];
+      xb1 = q[1];
+    }
+  };
+  auto store_x = [&](uint32_t b) {
+    if constexpr (SEL) {
+      const uint32_t at = my_ring + uint32_t(kSimRingBytes) + (b & 1u) * 32u;
+      store_block(at, xb0);
+      store_block(at + 16u, xb1);
+    }
+  };
 
   // wave-uniform lane masks
   uint64_t m_live = 0;     // lanes running an op sequence
@@ -265,11 +290,17 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
     // the first two blocks of the section into the ring
     const uint32_t b0 = uint32_t(rb) / uint32_t(kSimBlockIds);
     const uint32_t bn = min(b0 + 1u, blk_last);
-    for (uint32_t b = b0; b <= bn; ++b) store_block(my_ring + (b & 1u) * 16u, load_block(row, b));
+    if constexpr (SEL) xrow = a.xcost + cand * a.stride;
+    for (uint32_t b = b0; b <= bn; ++b) {
+      store_block(my_ring + (b & 1u) * 16u, load_block(row, b));
+      load_x(b);
+      store_x(b);
+    }
     lb = bn + 1u;
     apos1 = uint32_t(rb) + 1u;
     const uint32_t id0 = ring_id(uint32_t(rb));
     set_current(id0, rec_of(id0));
+    curx = ring_x(uint32_t(rb));
   };
 
   start_candidate(0);
@@ -287,6 +318,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
     if (phase == 3u && m_blk) {
       if (lane_in(m_blk)) {
         store_block(my_ring + (lb & 1u) * 16u, blk);
+        store_x(lb);
         ++lb;
       }
       m_blk = 0;
@@ -320,6 +352,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
     const uint32_t idn = ring_id(apos1);
     // the next op's record, read ahead (used by the lanes that advance)
     const uint2 nrec = rec_of(idn);
+    const uint32_t nx = ring_x(apos1);
 
     // the matching slot (tags are unique within a pool)
     const uint32_t wsum = tag_weighted_misses<S>(tw, want);
@@ -351,7 +384,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
     const uint64_t m_fire = m_ready & (~m_need | ballot(has_free));
     const uint64_t m_held = m_ready & ~m_fire;
     const bool fire = lane_in(m_fire);
-    const uint32_t en = max(tfree, acc_n) + (cur0 & kSimCostMax);
+    const uint32_t en = max(tfree, acc_n) + (cur0 & kSimCostMax) + (SEL ? curx : 0u);
 
     // ---- writes: release what was read, publish what was produced
     if (found) {
@@ -387,6 +420,7 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
     }
     if (adv) {   // the next op becomes current
       set_current(idn, nrec);
+      if constexpr (SEL) curx = nx;
       ++apos1;
     }
     m_npend = ((m_npend & ~m_fire) | (m_found & m_last & ~m_fire) |
@@ -401,7 +435,10 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
       const uint32_t next_blk = (apos1 + uint32_t(kSimBlockIds) - 1u) / uint32_t(kSimBlockIds);
       const bool load = lane_in(m_live) && lb <= min(next_blk, blk_last);
       m_blk = ballot(load);
-      if (load) blk = load_block(row, lb);
+      if (load) {
+        blk = load_block(row, lb);
+        load_x(lb);
+      }
     }
 
     // ---- verdicts, every 8 rounds (a group that finished or stalled waits
@@ -452,7 +489,9 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
             a.retry[k] = cand;
           }
         } else if (on) {
-          a.out_bub[cand * a.P + r] = stalled ? -1 : int32_t(T) - busy_r;
+          int32_t busy = busy_r;
+          if constexpr (SEL) busy += a.out_bub[cand * a.P + r];
+          a.out_bub[cand * a.P + r] = stalled ? -1 : int32_t(T) - busy;
           if (r == 0) {
             a.out_ms[cand] = stalled ? -1 : int32_t(T);
             if (stalled) a.out_flags[cand] = uint8_t(fl | DIP_FLAG_DEADLOCK);
@@ -471,50 +510,60 @@ __global__ __launch_bounds__(1024) void sim_kernel(SimArgs a) {
   }
 }
 
-template <int S, bool PAGED>
+template <int S, bool PAGED, bool SEL>
 const void *ptr_s(int pwl) {
   switch (pwl) {
-    case 0: return reinterpret_cast<const void *>(sim_kernel<0, S, PAGED>);
-    case 1: return reinterpret_cast<const void *>(sim_kernel<1, S, PAGED>);
-    case 2: return reinterpret_cast<const void *>(sim_kernel<2, S, PAGED>);
-    case 3: return reinterpret_cast<const void *>(sim_kernel<3, S, PAGED>);
-    case 4: return reinterpret_cast<const void *>(sim_kernel<4, S, PAGED>);
-    case 5: return reinterpret_cast<const void *>(sim_kernel<5, S, PAGED>);
-    default: return reinterpret_cast<const void *>(sim_kernel<6, S, PAGED>);
+    case 0: return reinterpret_cast<const void *>(sim_kernel<0, S, PAGED, SEL>);
+    case 1: return reinterpret_cast<const void *>(sim_kernel<1, S, PAGED, SEL>);
+    case 2: return reinterpret_cast<const void *>(sim_kernel<2, S, PAGED, SEL>);
+    case 3: return reinterpret_cast<const void *>(sim_kernel<3, S, PAGED, SEL>);
+    case 4: return reinterpret_cast<const void *>(sim_kernel<4, S, PAGED, SEL>);
+    case 5: return reinterpret_cast<const void *>(sim_kernel<5, S, PAGED, SEL>);
+    default: return reinterpret_cast<const void *>(sim_kernel<6, S, PAGED, SEL>);
   }
 }
 
-template <int S, bool PAGED>
+template <int S, bool PAGED, bool SEL>
 void launch_s(int pwl, dim3 grid, dim3 block, size_t lds, hipStream_t s, const SimArgs &a) {
   switch (pwl) {
-    case 0: sim_kernel<0, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    case 1: sim_kernel<1, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    case 2: sim_kernel<2, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    case 3: sim_kernel<3, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    case 4: sim_kernel<4, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    case 5: sim_kernel<5, S, PAGED><<<grid, block, lds, s>>>(a); break;
-    default: sim_kernel<6, S, PAGED><<<grid, block, lds, s>>>(a); break;
+    case 0: sim_kernel<0, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    case 1: sim_kernel<1, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    case 2: sim_kernel<2, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    case 3: sim_kernel<3, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    case 4: sim_kernel<4, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    case 5: sim_kernel<5, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
+    default: sim_kernel<6, S, PAGED, SEL><<<grid, block, lds, s>>>(a); break;
   }
 }
 
 template <bool PAGED>
-const void *ptr_p(int pwl, int slots) {
+const void *ptr_p(int pwl, int slots, bool sel) {
   switch (slots) {
-    case 4: return ptr_s<4, PAGED>(pwl);
-    case 16: return ptr_s<16, PAGED>(pwl);
-    case 32: return ptr_s<32, PAGED>(pwl);
-    default: return ptr_s<8, PAGED>(pwl);
+    case 4: return ptr_s<4, PAGED, false>(pwl);
+    case 16: return ptr_s<16, PAGED, false>(pwl);
+    case 32: return sel ? ptr_s<32, PAGED, true>(pwl) : ptr_s<32, PAGED, false>(pwl);
+    default: return sel ? ptr_s<8, PAGED, true>(pwl) : ptr_s<8, PAGED, false>(pwl);
   }
 }
 
 template <bool PAGED>
 void launch_p(int pwl, int slots, dim3 grid, dim3 block, size_t lds, hipStream_t s,
-              const SimArgs &a) {
+              const SimArgs &a, bool sel) {
   switch (slots) {
-    case 4: launch_s<4, PAGED>(pwl, grid, block, lds, s, a); break;
-    case 16: launch_s<16, PAGED>(pwl, grid, block, lds, s, a); break;
-    case 32: launch_s<32, PAGED>(pwl, grid, block, lds, s, a); break;
-    default: launch_s<8, PAGED>(pwl, grid, block, lds, s, a); break;
+    case 4: launch_s<4, PAGED, false>(pwl, grid, block, lds, s, a); break;
+    case 16: launch_s<16, PAGED, false>(pwl, grid, block, lds, s, a); break;
+    case 32:
+      if (sel)
+        launch_s<32, PAGED, true>(pwl, grid, block, lds, s, a);
+      else
+        launch_s<32, PAGED, false>(pwl, grid, block, lds, s, a);
+      break;
+    default:
+      if (sel)
+        launch_s<8, PAGED, true>(pwl, grid, block, lds, s, a);
+      else
+        launch_s<8, PAGED, false>(pwl, grid, block, lds, s, a);
+      break;
   }
 }
 
@@ -522,17 +571,17 @@ void launch_p(int pwl, int slots, dim3 grid, dim3 block, size_t lds, hipStream_t
 
 bool sim_slots_ok(int slots) { return slots == 4 || slots == 8 || slots == 16; }
 
-const void *sim_kernel_ptr(int pwl, int slots, bool paged) {
-  return paged ? ptr_p<true>(pwl, slots) : ptr_p<false>(pwl, slots);
+const void *sim_kernel_ptr(int pwl, int slots, bool paged, bool sel) {
+  return paged ? ptr_p<true>(pwl, slots, sel) : ptr_p<false>(pwl, slots, sel);
 }
 
 hipError_t launch_sim(int pwl, int slots, bool paged, int blocks, int wpb, size_t lds,
-                      hipStream_t s, const SimArgs &a) {
+                      hipStream_t s, const SimArgs &a, bool sel) {
   const dim3 grid(blocks), block(wpb * kWave);
   if (paged)
-    launch_p<true>(pwl, slots, grid, block, lds, s, a);
+    launch_p<true>(pwl, slots, grid, block, lds, s, a, sel);
   else
-    launch_p<false>(pwl, slots, grid, block, lds, s, a);
+    launch_p<false>(pwl, slots, grid, block, lds, s, a, sel);
   return hipGetLastError();
 }
 
