@@ -11,7 +11,7 @@ SOURCES = [os.path.join(CSRC, f) for f in
            ("host.hip", "host_plan.hip", "host_tables.hip", "host_next.hip", "host_check.cpp",
             "kern_general.hip", "kern_check.hip", "kern_pool.hip", "kern_sim.hip",
             "kern_greedy.hip", "kern_rollout.hip", "kern_costmodel.hip", "kern_memopt.hip",
-            "kern_argmin.hip", "kern_selcheck.hip")]
+            "kern_argmin.hip", "kern_selcheck.hip", "kern_direct.hip")]
 LIB = os.path.join(HERE, "libdip_sim.so")
 INCLUDE = os.path.join(ROOT, "include")
 

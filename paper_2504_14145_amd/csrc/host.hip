@@ -128,21 +128,14 @@ void release_greedy(dip_sim *h) {
 void release(dip_sim *h) {
   if (!h) return;
   (void)hipDeviceSynchronize();
-  if (h->d_rec) (void)hipFree(h->d_rec);
-  if (h->d_edge) (void)hipFree(h->d_edge);
-  if (h->d_md) (void)hipFree(h->d_md);
+  if (h->d_cost_buf) (void)hipFree(h->d_cost_buf);
   if (h->d_selfp) (void)hipFree(h->d_selfp);
   if (h->d_oc_ranks) (void)hipFree(h->d_oc_ranks);
-  if (h->d_sim_tab) (void)hipFree(h->d_sim_tab);
-  if (h->d_sim_lane) (void)hipFree(h->d_sim_lane);
   if (h->d_rank_off) (void)hipFree(h->d_rank_off);
-  if (h->d_busy) (void)hipFree(h->d_busy);
   if (h->d_cap) (void)hipFree(h->d_cap);
   if (h->tc.d_plan) (void)hipFree(h->tc.d_plan);
   if (h->d_scratch_gen) (void)hipFree(h->d_scratch_gen);
   if (h->d_scratch_fb) (void)hipFree(h->d_scratch_fb);
-  if (h->d_pool_rec) (void)hipFree(h->d_pool_rec);
-  if (h->d_pool_edge) (void)hipFree(h->d_pool_edge);
   if (h->d_retry) (void)hipFree(h->d_retry);
   if (h->d_retry2) (void)hipFree(h->d_retry2);
   if (h->d_retry_count) (void)hipFree(h->d_retry_count);
@@ -247,34 +240,41 @@ int dip_sim_create(const dip_topology *t, dip_sim **out) {
   (void)hipGetLastError();
   h->d_static = static_scratch_on_current_device();
   if (!h->d_static) return hip_fail(g_last_hip);
-  if ((e = hipMalloc(&h->d_rec, size_t(h->N) * 16)) != hipSuccess) return hip_fail(e);
-  if ((e = hipMalloc(&h->d_edge, size_t(std::max(h->E, 1)) * 8)) != hipSuccess) return hip_fail(e);
-  if ((e = hipMalloc(&h->d_md, size_t(h->N) * 4)) != hipSuccess) return hip_fail(e);
   if (h->self_ok) {
     if ((e = hipMalloc(&h->d_selfp, size_t(h->N) * 4)) != hipSuccess) return hip_fail(e);
     if ((e = hipMemcpy(h->d_selfp, h->self_pred.data(), size_t(h->N) * 4,
                        hipMemcpyHostToDevice)) != hipSuccess)
       return hip_fail(e);
   }
-  if (h->pool_ok) {
-    if ((e = hipMalloc(&h->d_pool_rec, size_t(h->N) * 16)) != hipSuccess) return hip_fail(e);
-    if ((e = hipMalloc(&h->d_pool_edge, size_t(std::max(h->n_extra, 1)) * 8)) != hipSuccess)
-      return hip_fail(e);
-  }
+  // every table that follows the costs in one buffer, laid out as it is staged
   if (h->sim_ok) {
     h->sim_tab_cap = sim_tab_bound(h);
-    if ((e = hipMalloc(&h->d_sim_tab, size_t(h->sim_tab_cap))) != hipSuccess) return hip_fail(e);
-    if ((e = hipMalloc(&h->d_sim_lane, size_t(h->P) * 16)) != hipSuccess) return hip_fail(e);
+    h->dir_fits = h->N <= kDirectMaxOps &&
+                  h->G * direct_group_bytes(h->N, 1 << h->pwl, false) <= h->lds_block_max;
+  }
+  {
+    const StageLayout L = stage_layout(h);
+    h->stage_bytes = L.total;
+    if ((e = hipMalloc(&h->d_cost_buf, size_t(L.total))) != hipSuccess) return hip_fail(e);
+    unsigned char *d = h->d_cost_buf;
+    h->d_rec = reinterpret_cast<int4 *>(d + L.rec);
+    h->d_edge = reinterpret_cast<int2 *>(d + L.edge);
+    h->d_busy = reinterpret_cast<int32_t *>(d + L.busy);
+    h->d_md = reinterpret_cast<int32_t *>(d + L.md);
+    h->d_pool_rec = reinterpret_cast<int4 *>(d + L.prec8);
+    h->d_pool_edge = reinterpret_cast<int2 *>(d + L.pedge);
+    h->d_sim_lane = reinterpret_cast<int4 *>(d + L.slane);
+    h->d_dir_lane = reinterpret_cast<int4 *>(d + L.dlane);
+    h->d_sim_tab = reinterpret_cast<uint4 *>(d + L.stab);
+    h->d_dir_tab = reinterpret_cast<uint4 *>(d + L.dtab);
   }
   if ((e = hipMalloc(&h->d_rank_off, size_t(h->P + 1) * 4)) != hipSuccess) return hip_fail(e);
-  if ((e = hipMalloc(&h->d_busy, size_t(h->P) * 4)) != hipSuccess) return hip_fail(e);
   if ((e = hipMalloc(&h->d_cap, size_t(h->P) * 4)) != hipSuccess) return hip_fail(e);
   if ((e = hipMemcpy(h->d_rank_off, h->rank_off.data(), size_t(h->P + 1) * 4,
                      hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e);
   if ((e = hipMemcpy(h->d_cap, h->cap.data(), size_t(h->P) * 4, hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(e);
-  h->stage_bytes = stage_layout(h).total;
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&h->h_stage), size_t(h->stage_bytes),
                          hipHostMallocDefault)) != hipSuccess)
     return hip_fail(e);
@@ -435,6 +435,16 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
     int last_slots = 0;   // pool slots of the last pass that ran
     h->last_stream = stream;
     h->last_general = 0;
+    // a batch whose candidates are all resident at once with every end time in
+    // LDS takes the direct kernel (8 ranks: 4,096 candidates 72 us, through
+    // the pools 117; twice the resident ones, 126 both)
+    if (h->forced_variant == 0 && h->forced_pool_slots == 0 && n_cand <= direct_slots(h, false)) {
+      rc = run_direct(h, false, orders, n_cand, nullptr, out_makespan, out_bubble, out_flags,
+                      counts + 1, nullptr, nullptr, stream);
+      if (rc != DIP_OK) return rc;
+      for (int i = 2; i <= 5; ++i) DIP_HIP(mark(i));
+      return DIP_OK;
+    }
     if (h->variant == 9 && h->sim_costs_ok) {
       SimArgs a{};
       a.orders = orders;
@@ -554,6 +564,13 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
     // never reach round_limit, since every round before a stall fires an op or
     // reads an item)
     if (last_slots > 0 && h->sim_max_pub <= last_slots) {
+      DIP_HIP(mark(h->prof_n));
+      return DIP_OK;
+    }
+    if (last_slots > 0 && direct_slots(h, false) > 0) {
+      rc = run_direct(h, false, orders, n_cand, nullptr, out_makespan, out_bubble, out_flags,
+                      nullptr, retry_list, retry_count, stream);
+      if (rc != DIP_OK) return rc;
       DIP_HIP(mark(h->prof_n));
       return DIP_OK;
     }

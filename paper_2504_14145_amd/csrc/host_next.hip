@@ -743,6 +743,8 @@ int dip_sim_memopt(dip_sim *h, const int16_t *orders, int64_t n_cand, int64_t *o
 // its times stay within int32 whatever is selected.
 static void plan_selected(dip_sim *h) {
   h->sel_planned = true;
+  h->dir_wpb[1] = 0;
+  if (h->dir_ok) (void)direct_shape(h, true);
   int64_t total = 0;
   for (int32_t x : h->last_cost) total += x;
   for (int32_t x : h->last_comm) total += x;
@@ -783,8 +785,10 @@ static bool ensure_selected(dip_sim *h, int64_t rows, hipStream_t stream) {
 }
 
 // The re-timed evaluate through the simulation kernel: check (with each op's
-// extra cost along the order), own-rank order, 8-slot pools, 32-slot pools for
-// those that filled, and the general kernel for what is left.
+// extra cost along the order), own-rank order, then the direct kernel where
+// every schedule is resident with it, else 8-slot pools and the direct kernel
+// for those that filled (32-slot pools and the general kernel where it does
+// not fit).
 static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t stream) {
   int32_t max_nr = 0;
   for (int32_t n : h->n_ops) max_nr = std::max(max_nr, n);
@@ -821,6 +825,13 @@ static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t
       const int rc = run_order_check(h, orders, n, ms, bub, flags, stream);
       if (rc != DIP_OK) return rc;
     }
+    const int64_t direct = direct_slots(h, true);
+    if (n <= direct) {
+      const int rc = run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, h->d_sel_count + 1,
+                                nullptr, nullptr, stream);
+      if (rc != DIP_OK) return rc;
+      continue;
+    }
     SimArgs a{};
     a.orders = orders;
     a.n_cand = n;
@@ -847,6 +858,14 @@ static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t
         a.spread ? n : (n + per_block - 1) / per_block, h->sel_max_blocks[0]));
     DIP_HIP(launch_sim(h->pwl, 8, h->sim_paged, blocks, a.wpb, size_t(h->sel_lds[0]), stream, a, true));
     if (h->sim_max_pub <= 8) continue;
+    if (direct > 0) {
+      // (selections come with orders of many live items: under a binding cap
+      // on 16 x 2 lanes every one of them fills 32 slots too)
+      const int rc = run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, nullptr,
+                                h->d_sel_list, h->d_sel_count, stream);
+      if (rc != DIP_OK) return rc;
+      continue;
+    }
     a.list = h->d_sel_list;
     a.list_count = h->d_sel_count;
     a.retry = h->d_sel_list + h->sel_rows;

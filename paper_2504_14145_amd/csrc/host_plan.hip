@@ -431,45 +431,118 @@ int apply_pick(dip_sim *h, const Pick &p, int *variant, int *wpb, int *max_block
   return DIP_OK;
 }
 
-// Launch shape of the simulation kernel for the current table image and a
-// pool size: the waves per block (one table copy per block) that keep the
-// most waves resident per CU, fewer blocks on ties.  false if nothing fits.
-bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out,
-               bool sel) {
-  const int64_t tab = int64_t(h->sim_tab_vec) * 16;
-  const int64_t grp = sim_group_bytes(1 << h->pwl, slots, sel);
-  const void *k = sim_kernel_ptr(h->pwl, slots, h->sim_paged, sel);
-  int best_w = 0, best_nb = 0;
+// The waves per block (each block holds `tab` bytes of tables, each wave
+// `wave` bytes) that keep the most waves of a kernel resident per CU, the most
+// per block on ties: the counts in the order of what the LDS and 32 waves a CU
+// allow, so that the occupancy is asked for few of them.  false if nothing fits.
+static bool best_shape(const dip_sim *h, const void *k, int64_t tab, int64_t wave, int forced_wpb,
+                       int *wpb, int *blocks_per_cu) {
+  int order[16], bound[17];
+  int n = 0;
+  int64_t most = 0;
   for (int w = 16; w >= 1; --w) {
-    if (forced_wpb && w != forced_wpb) continue;
-    const int64_t lds = tab + int64_t(w) * h->G * grp;
-    if (lds > h->lds_block_max) continue;
-    if (lds > 65536 &&
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess) {
-      (void)hipGetLastError();
-      continue;
-    }
+    const int64_t lds = tab + w * wave;
+    if ((forced_wpb && w != forced_wpb) || lds > h->lds_block_max) continue;
+    bound[w] = int(std::min<int64_t>(h->lds_block_max / std::max<int64_t>(lds, 1), 32 / w)) * w;
+    order[n++] = w;
+    most = std::max(most, lds);
+  }
+  std::stable_sort(order, order + n, [&](int x, int y) { return bound[x] > bound[y]; });
+  if (most > 65536 && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          int(most)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  int best_w = 0, best_nb = 0;
+  for (int i = 0; i < n && bound[order[i]] >= best_nb * best_w; ++i) {
+    const int w = order[i];
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, w * kWave, size_t(lds)) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, w * kWave, size_t(tab + w * wave)) !=
+        hipSuccess) {
       (void)hipGetLastError();
       continue;
     }
-    if (nb > 0 && nb * w > best_nb * best_w) {
+    if (nb > 0 && (nb * w > best_nb * best_w || (nb * w == best_nb * best_w && w > best_w))) {
       best_w = w;
       best_nb = nb;
     }
   }
-  if (best_w == 0) return false;
-  const int64_t lds = tab + int64_t(best_w) * h->G * grp;
-  if (lds > 65536 &&
-      hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
   *wpb = best_w;
-  *max_blocks = best_nb * h->n_cu;
-  *lds_out = lds;
+  *blocks_per_cu = best_nb;
+  return best_w > 0;
+}
+
+// Launch shape of the simulation kernel for the current table image and a
+// pool size (one table copy per block).  false if nothing fits.
+bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks, int64_t *lds_out,
+               bool sel) {
+  const int64_t tab = int64_t(h->sim_tab_vec) * 16;
+  const int64_t wave = h->G * sim_group_bytes(1 << h->pwl, slots, sel);
+  int w = 0, nb = 0;
+  if (!best_shape(h, sim_kernel_ptr(h->pwl, slots, h->sim_paged, sel), tab, wave, forced_wpb, &w, &nb))
+    return false;
+  *wpb = w;
+  *max_blocks = nb * h->n_cu;
+  *lds_out = tab + w * wave;
   return true;
+}
+
+// Launch shape of the direct kernel for the current tables.
+bool direct_shape(dip_sim *h, bool sel) {
+  int w = 0, nb = 0;
+  const bool ok = best_shape(h, direct_kernel_ptr(h->pwl, h->dir_paged, sel),
+                             int64_t(h->dir_tab_vec) * 16,
+                             h->G * direct_group_bytes(h->N, 1 << h->pwl, sel), 0, &w, &nb);
+  h->dir_wpb[sel] = w;
+  h->dir_max_blocks[sel] = nb * h->n_cu;
+  return ok;
+}
+
+int64_t direct_slots(const dip_sim *h, bool sel) {
+  return h->dir_ok && h->variant == 9 ? int64_t(h->dir_max_blocks[sel]) * h->dir_wpb[sel] * h->G : 0;
+}
+
+int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, const int32_t *xcost,
+               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, uint32_t *next_cand,
+               const int64_t *list, const uint32_t *list_count, hipStream_t stream) {
+  DirectArgs a{};
+  a.list = list;
+  a.list_count = list_count;
+  a.orders = orders;
+  a.n_cand = n_cand;
+  a.stride = h->stride;
+  a.out_ms = out_ms;
+  a.out_bub = out_bub;
+  a.out_flags = out_flags;
+  a.tab = h->d_dir_tab;
+  a.tab_vec = h->dir_tab_vec;
+  a.off_pmap = h->dir_off_pmap;
+  a.off_extra = h->dir_off_extra;
+  a.lane_info = reinterpret_cast<const int32_t *>(h->d_dir_lane);
+  a.group_bytes = uint32_t(direct_group_bytes(h->N, 1 << h->pwl, sel));
+  a.off_ring = uint32_t(direct_ring_offset(h->N));
+  a.end_vec = a.off_ring / 16;
+  a.P = h->P;
+  a.xcost = xcost;
+  a.next_cand = next_cand;
+  // a batch within the resident groups spreads over the CUs; the waves of a
+  // block are what its share needs, and what copies the table in some eight
+  // steps
+  const int64_t tab = int64_t(h->dir_tab_vec) * 16;
+  int wpb = h->dir_wpb[sel];
+  int64_t blocks = h->dir_max_blocks[sel];
+  if (n_cand <= blocks * wpb * h->G) {
+    const int64_t share = (n_cand + h->n_cu - 1) / h->n_cu;
+    wpb = int(std::min<int64_t>(wpb, std::max<int64_t>(share, (tab + 8191) / 8192)));
+    blocks = std::min<int64_t>(
+        n_cand, std::max<int64_t>(h->n_cu, (n_cand + wpb * h->G - 1) / (int64_t(wpb) * h->G)));
+  }
+  a.wpb = wpb;
+  const int64_t slots = blocks * wpb * h->G;
+  a.static_end = !list && n_cand >= 4 * slots ? slots * ((n_cand / 10 * 9) / slots) : INT64_MAX;
+  const int64_t lds = tab + int64_t(wpb) * h->G * int64_t(a.group_bytes);
+  DIP_HIP(launch_direct(h->pwl, h->dir_paged, sel, int(blocks), wpb, size_t(lds), stream, a));
+  return DIP_OK;
 }
 
 // The passes' shapes (the configured pools, then 16 and 32 slots for the

@@ -16,7 +16,8 @@
 //                 the pool kernel: compact op records resident in LDS and the
 //                 orders staged through per-lane LDS rings, then a second
 //                 pass with 16 pool slots before the general kernel.  It
-//                 needs at most 8192 ops per rank, and per call costs below 2^20 and latencies below 2^11
+//                 needs at most 8192 ops per rank, and per call costs below
+//                 2^20 and latencies below 2^11
 //                 (checked whenever costs change; a call outside them runs
 //                 variant 8).
 #pragma once
@@ -93,7 +94,7 @@ struct dip_sim {
   bool sim_costs_ok = false;           // the last costs fit its records
   bool sim_paged = false;              // records stored as deduplicated pages
   int32_t sim_n_extra = 0;             // extra-edge words (edges of multi-predecessor ops)
-  int64_t sim_tab_cap = 0;             // bytes of d_sim_tab
+  int64_t sim_tab_cap = 0;             // bytes of d_sim_tab (and of d_dir_tab)
   int32_t sim_tab_vec = 0;             // 16-byte units of the current table image
   uint32_t sim_off_pmap = 0, sim_off_extra = 0;
   uint4 *d_sim_tab = nullptr;          // LDS image: records, page map, extra edges
@@ -106,6 +107,15 @@ struct dip_sim {
   int sim2_wpb = 1, sim2_max_blocks = 1;
   int64_t sim2_lds = 0;
   int64_t *d_retry2 = nullptr;         // candidates the second pass could not hold
+  // direct kernel: the same tables with its edge words; plain and re-timed
+  bool dir_fits = false;               // one wave's end times fit a block's LDS
+  bool dir_ok = false;                 // its tables hold the current costs and fit
+  bool dir_paged = false;
+  int32_t dir_tab_vec = 0;
+  uint32_t dir_off_pmap = 0, dir_off_extra = 0;
+  uint4 *d_dir_tab = nullptr;
+  int4 *d_dir_lane = nullptr;
+  int dir_wpb[2] = {0, 0}, dir_max_blocks[2] = {0, 0};
   // re-timed simulation of a memory selection: 8-slot pools, then 32
   bool sel_planned = false;            // the shapes below are the current costs'
   bool sel_ok = false;
@@ -158,6 +168,8 @@ struct dip_sim {
   int64_t scratch_fb_bytes = 0;
   int fb_blocks = 1;
   // device tables
+  unsigned char *d_cost_buf = nullptr; // holds the tables that follow the costs (busy, md, pool,
+                                       // sim and direct tables too), as staged
   int4 *d_rec = nullptr;               // general records [N]
   int2 *d_edge = nullptr;              // general edges [E]
   int32_t *d_md = nullptr;             // memory deltas [N] (+act at F, -act at B)
@@ -268,7 +280,7 @@ struct Pick {
 };
 
 struct StageLayout {
-  int64_t rec, edge, busy, md, prec8, pedge, stab, slane, total;
+  int64_t rec, edge, busy, md, prec8, pedge, stab, slane, dtab, dlane, total;
 };
 
 GenBytes general_bytes(const dip_sim *h, int v);
@@ -300,12 +312,20 @@ bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks,
 int run_order_check(dip_sim *h, const int16_t *orders, int64_t n_cand, int32_t *out_ms,
                     int32_t *out_bub, uint8_t *out_flags, hipStream_t stream);
 int sim_plan(dip_sim *h);
+bool direct_shape(dip_sim *h, bool sel);
+// resident candidates of the direct kernel, 0 where it does not run the
+// current costs
+int64_t direct_slots(const dip_sim *h, bool sel);
+// its launch on n candidates, or on a list of at most n; their check has run
+int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, const int32_t *xcost,
+               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, uint32_t *next_cand,
+               const int64_t *list, const uint32_t *list_count, hipStream_t stream);
 int choose_config(dip_sim *h);
 int64_t sim_tab_bound(const dip_sim *h);
 StageLayout stage_layout(const dip_sim *h);
 int upload_greedy_records(dip_sim *h, const dip_costs *c, hipStream_t stream);
 int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const StageLayout &L,
-                      hipStream_t stream);
+                      int64_t *end);
 int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream);
 bool greedy_inbox_fits(const dip_sim *h, int64_t K, int pwl);
 bool greedy_plan(dip_sim *h);

@@ -27,8 +27,10 @@ StageLayout stage_layout(const dip_sim *h) {
   L.md = off; off += align16(int64_t(h->N) * 4);
   L.prec8 = off; off += h->pool_ok ? align16(int64_t(h->N) * 16) : 0;
   L.pedge = off; off += h->pool_ok ? align16(int64_t(std::max(h->n_extra, 1)) * 8) : 0;
-  L.stab = off; off += h->sim_ok ? sim_tab_bound(h) : 0;
   L.slane = off; off += h->sim_ok ? align16(int64_t(h->P) * 16) : 0;
+  L.dlane = off; off += h->dir_fits ? align16(int64_t(h->P) * 16) : 0;
+  L.stab = off; off += h->sim_ok ? h->sim_tab_cap : 0;
+  L.dtab = off; off += h->dir_fits ? h->sim_tab_cap : 0;
   L.total = off;
   return L;
 }
@@ -72,49 +74,27 @@ int upload_greedy_records(dip_sim *h, const dip_costs *c, hipStream_t stream) {
   return DIP_OK;
 }
 
-// The simulation kernel's tables for these costs (see kern_sim.hip and
-// internal.h for the record and edge-word formats): records relative to their
-// op, stored directly when small, else as pages of kSimPage records of one
-// rank with equal pages kept once; then the extra edges.  Leaves
-// sim_costs_ok false (evaluate then runs variant 8) when a cost or latency is
-// outside the record's fields or the tables do not fit in LDS.
-int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const StageLayout &L,
-                      hipStream_t stream) {
-  h->sim_costs_ok = false;
-  for (int32_t g = 0; g < h->N; ++g)
-    if (uint32_t(c->op_cost[g]) > kSimCostMax) return DIP_OK;
-  for (int32_t e = 0; e < h->E; ++e)
-    if (uint32_t(c->edge_comm[e]) > kSimCommMax) return DIP_OK;
+struct TableImage {
+  bool paged = false;
+  uint32_t off_pmap = 0, off_extra = 0;
+  int64_t bytes = 0;
+};
+
+// The LDS image of a table of records and edges, with the kernel's own edge
+// words: records relative to their op, stored directly when small, else as
+// pages of kSimPage records of one rank with equal pages kept once; then the
+// extra edges; and the lanes' {first op, ops, busy time, record base}.  false
+// when it takes more than cap bytes (the extra edges may lie past them while
+// it is measured: the caller's area holds sim_tab_bound).
+template <class Dropped, class Word>
+static bool table_image(const dip_sim *h, const dip_costs *c, const int32_t *busy,
+                        const std::vector<int32_t> &readers, const Dropped &dropped,
+                        const Word &edge_word, int64_t cap, unsigned char *img, int32_t *lane,
+                        TableImage *T) {
   const int32_t P = h->P;
-  // an edge between two ops of one rank with zero latency holds by the order
-  // alone once the check kernel has verified that the predecessor comes first
-  // (it flags the candidate deadlocked otherwise): dropped, its producer then
-  // publishes no end time for it
-  h->sim_drop_self = order_checked(h);
-  auto dropped = [&](int32_t g, int32_t k) {
-    return h->sim_drop_self && h->rank_of[h->pred_op[k]] == h->rank_of[g] && c->edge_comm[k] == 0;
-  };
-  std::vector<int32_t> readers(size_t(h->N), 0);
-  for (int32_t g = 0; g < h->N; ++g)
-    for (int32_t k = h->pred_ptr[g]; k < h->pred_ptr[g + 1]; ++k)
-      if (!dropped(g, k)) ++readers[h->pred_op[k]];
-  h->sim_max_pub = 0;
-  for (int r = 0; r < P; ++r) {
-    int32_t pub = 0;
-    for (int32_t g = h->rank_off[r]; g < h->rank_off[r + 1]; ++g) pub += readers[g] > 0 ? 1 : 0;
-    h->sim_max_pub = std::max(h->sim_max_pub, pub);
-  }
   std::vector<uint32_t> rec(size_t(h->N) * 2), extra;
   extra.reserve(size_t(std::max(h->sim_n_extra, 1)));
   std::vector<int32_t> kept;
-  auto edge_word = [&](int32_t g, int32_t k, bool last) {
-    const int32_t p = h->pred_op[k];
-    const int32_t r = h->rank_of[g], rp = h->rank_of[p];
-    const int32_t d = (p - h->rank_off[rp]) - (g - h->rank_off[r]);
-    const uint32_t dr = uint32_t(rp - r) & uint32_t((1 << h->pwl) - 1);
-    return dr | ((uint32_t(d) & 0x3fffu) << 6) | (uint32_t(c->edge_comm[k]) << 20) |
-           (last ? kSimLast : 0u);
-  };
   for (int32_t g = 0; g < h->N; ++g) {
     kept.clear();
     for (int32_t k = h->pred_ptr[g]; k < h->pred_ptr[g + 1]; ++k)
@@ -131,8 +111,6 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
       rec[2 * g + 1] = 0;
     }
   }
-  unsigned char *img = h->h_stage + L.stab;
-  int32_t *lane = reinterpret_cast<int32_t *>(h->h_stage + L.slane);
   const int64_t direct = align16(int64_t(h->N) * 8);
   int64_t off_pmap = 0, recs_bytes = direct;
   std::vector<uint16_t> pmap;
@@ -182,20 +160,85 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
   const int64_t off_extra = recs_bytes;
   if (!extra.empty()) std::memcpy(img + off_extra, extra.data(), extra.size() * 4);
   const int64_t total = off_extra + align16(int64_t(std::max<size_t>(extra.size(), 1)) * 4);
-  if (total > L.slane - L.stab || total > h->sim_tab_cap) return DIP_OK;
+  if (total > cap) return false;
   for (int r = 0; r < P; ++r) {
     lane[4 * r] = h->rank_off[r];
     lane[4 * r + 1] = h->n_ops[r];
     lane[4 * r + 2] = busy[r];
     lane[4 * r + 3] = recb[r];
   }
-  h->sim_paged = paged;
-  h->sim_off_pmap = uint32_t(off_pmap);
-  h->sim_off_extra = uint32_t(off_extra);
-  h->sim_tab_vec = int32_t(total / 16);
-  DIP_HIP(hipMemcpyAsync(h->d_sim_tab, img, size_t(total), hipMemcpyHostToDevice, stream));
-  DIP_HIP(hipMemcpyAsync(h->d_sim_lane, lane, size_t(P) * 16, hipMemcpyHostToDevice, stream));
-  return sim_plan(h);
+  T->paged = paged;
+  T->off_pmap = uint32_t(off_pmap);
+  T->off_extra = uint32_t(off_extra);
+  T->bytes = total;
+  return true;
+}
+
+// The simulation kernel's and the direct kernel's tables for these costs (see
+// internal.h for the record and edge-word formats).  Leaves sim_costs_ok
+// false (evaluate then runs variant 8) when a cost or latency is outside the
+// record's fields or the tables do not fit in LDS.
+// They are staged; *end moves to the end of what is to be copied.
+int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const StageLayout &L,
+                      int64_t *end) {
+  h->sim_costs_ok = false;
+  h->dir_ok = false;
+  for (int32_t g = 0; g < h->N; ++g)
+    if (uint32_t(c->op_cost[g]) > kSimCostMax) return DIP_OK;
+  for (int32_t e = 0; e < h->E; ++e)
+    if (uint32_t(c->edge_comm[e]) > kSimCommMax) return DIP_OK;
+  const int32_t P = h->P;
+  // an edge between two ops of one rank with zero latency holds by the order
+  // alone once the check kernel has verified that the predecessor comes first
+  // (it flags the candidate deadlocked otherwise): dropped, its producer then
+  // publishes no end time for it
+  h->sim_drop_self = order_checked(h);
+  auto dropped = [&](int32_t g, int32_t k) {
+    return h->sim_drop_self && h->rank_of[h->pred_op[k]] == h->rank_of[g] && c->edge_comm[k] == 0;
+  };
+  std::vector<int32_t> readers(size_t(h->N), 0);
+  for (int32_t g = 0; g < h->N; ++g)
+    for (int32_t k = h->pred_ptr[g]; k < h->pred_ptr[g + 1]; ++k)
+      if (!dropped(g, k)) ++readers[h->pred_op[k]];
+  h->sim_max_pub = 0;
+  for (int r = 0; r < P; ++r) {
+    int32_t pub = 0;
+    for (int32_t g = h->rank_off[r]; g < h->rank_off[r + 1]; ++g) pub += readers[g] > 0 ? 1 : 0;
+    h->sim_max_pub = std::max(h->sim_max_pub, pub);
+  }
+  const int64_t cap = h->sim_tab_cap;
+  TableImage T, D;
+  auto edge_word = [&](int32_t g, int32_t k, bool last) {
+    const int32_t p = h->pred_op[k];
+    const int32_t r = h->rank_of[g], rp = h->rank_of[p];
+    const int32_t d = (p - h->rank_off[rp]) - (g - h->rank_off[r]);
+    const uint32_t dr = uint32_t(rp - r) & uint32_t((1 << h->pwl) - 1);
+    return dr | ((uint32_t(d) & 0x3fffu) << 6) | (uint32_t(c->edge_comm[k]) << 20) |
+           (last ? kSimLast : 0u);
+  };
+  if (!table_image(h, c, busy, readers, dropped, edge_word, cap, h->h_stage + L.stab,
+                   reinterpret_cast<int32_t *>(h->h_stage + L.slane), &T))
+    return DIP_OK;
+  h->sim_paged = T.paged;
+  h->sim_off_pmap = T.off_pmap;
+  h->sim_off_extra = T.off_extra;
+  h->sim_tab_vec = int32_t(T.bytes / 16);
+  if (h->dir_fits) {
+    auto direct_word = [&](int32_t g, int32_t k, bool last) {
+      return (uint32_t(h->pred_op[k] - g) & 0x1ffffu) | (uint32_t(c->edge_comm[k]) << 17) |
+             (last ? kSimLast : 0u);
+    };
+    h->dir_ok = table_image(h, c, busy, readers, dropped, direct_word, cap, h->h_stage + L.dtab,
+                            reinterpret_cast<int32_t *>(h->h_stage + L.dlane), &D);
+    h->dir_paged = D.paged;
+    h->dir_off_pmap = D.off_pmap;
+    h->dir_off_extra = D.off_extra;
+    h->dir_tab_vec = int32_t(D.bytes / 16);
+  }
+  *end = h->dir_ok ? L.dtab + D.bytes : L.stab + T.bytes;
+  const int rc = sim_plan(h);
+  h->dir_ok = h->dir_ok && h->sim_costs_ok && direct_shape(h, false);
+  return rc;
 }
 
 int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream) {
@@ -227,15 +270,8 @@ int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream) {
     for (int32_t g = h->rank_off[r]; g < h->rank_off[r + 1]; ++g) s += c->op_cost[g];
     busy[r] = int32_t(s);
   }
-  DIP_HIP(hipMemcpyAsync(h->d_rec, rec, size_t(h->N) * 16, hipMemcpyHostToDevice, stream));
-  if (h->E > 0)
-    DIP_HIP(hipMemcpyAsync(h->d_edge, edge, size_t(h->E) * 8, hipMemcpyHostToDevice, stream));
-  DIP_HIP(hipMemcpyAsync(h->d_busy, busy, size_t(h->P) * 4, hipMemcpyHostToDevice, stream));
-  {
-    int32_t *md = reinterpret_cast<int32_t *>(h->h_stage + L.md);
-    for (int32_t g = 0; g < h->N; ++g) md[g] = rec[g].y;
-    DIP_HIP(hipMemcpyAsync(h->d_md, md, size_t(h->N) * 4, hipMemcpyHostToDevice, stream));
-  }
+  int32_t *md = reinterpret_cast<int32_t *>(h->h_stage + L.md);
+  for (int32_t g = 0; g < h->N; ++g) md[g] = rec[g].y;
   if (h->pool_ok) {
     // pool records {cost, first edge's comm, first edge word | readers << 24,
     // item tag or 0 | index of the op's extra edges << 16}; edge words are
@@ -258,14 +294,13 @@ int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream) {
                         int32_t(uint32_t(tag) | (uint32_t(xi) << 16)));
       for (int32_t k = 1; k < np; ++k) pe[xi++] = make_int2(int32_t(word(b + k, k == np - 1)), c->edge_comm[b + k]);
     }
-    DIP_HIP(hipMemcpyAsync(h->d_pool_rec, pr, size_t(h->N) * 16, hipMemcpyHostToDevice, stream));
-    if (h->n_extra > 0)
-      DIP_HIP(hipMemcpyAsync(h->d_pool_edge, pe, size_t(h->n_extra) * 8, hipMemcpyHostToDevice, stream));
   }
+  int64_t end = L.slane;
   if (h->sim_ok) {
-    rc = upload_sim_tables(h, c, busy, L, stream);
+    rc = upload_sim_tables(h, c, busy, L, &end);
     if (rc != DIP_OK) return rc;
   }
+  DIP_HIP(hipMemcpyAsync(h->d_cost_buf, h->h_stage, size_t(end), hipMemcpyHostToDevice, stream));
   if (h->gr_ok) {
     rc = upload_greedy_records(h, c, stream);
     if (rc != DIP_OK) return rc;

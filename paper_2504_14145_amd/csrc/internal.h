@@ -10,7 +10,7 @@ namespace dipsim {
 
 constexpr int kWave = 64;
 
-__host__ __device__ inline int64_t align16(int64_t x) { return (x + 15) & ~int64_t(15); }
+__host__ __device__ constexpr int64_t align16(int64_t x) { return (x + 15) & ~int64_t(15); }
 
 // ---------------------------------------------------------------- general
 // General kernel: any DAG (predecessors walked through the CSR), tables
@@ -340,6 +340,44 @@ bool sim_slots_ok(int slots);
 const void *sim_kernel_ptr(int pwl, int slots, bool paged, bool sel = false);
 hipError_t launch_sim(int pwl, int slots, bool paged, int blocks, int wpb, size_t lds,
                       hipStream_t s, const SimArgs &a, bool sel = false);
+
+// ---------------------------------------------------------------- direct
+// Timing simulation with every end time of a candidate in LDS (see
+// kern_direct.hip).  Records as the simulation kernel's; edge word:
+//   pred global index - own global index (bits 0-16, two's complement) |
+//   latency (17-27) | last (31).
+// LDS: the table image, then per group: end times [N] (16-aligned), order
+// rings.
+constexpr int32_t kDirectMaxOps = 65535;
+__host__ __device__ constexpr int64_t direct_ring_offset(int32_t N) { return align16(int64_t(N) * 4); }
+__host__ __device__ constexpr int64_t direct_group_bytes(int32_t N, int pw, bool sel) {
+  // (an odd number of 16-byte units, so that the groups' equal words fall in
+  // different banks)
+  const int64_t units = (direct_ring_offset(N) + int64_t(pw) * sim_ring_bytes(sel) + 15) / 16;
+  return (units | 1) * 16;
+}
+struct DirectArgs {
+  const int16_t *orders;
+  int64_t n_cand;
+  int64_t stride;
+  int32_t *out_ms;
+  int32_t *out_bub;
+  uint8_t *out_flags;        // the check kernel's verdicts, extended here
+  const uint4 *tab;          // LDS image of the tables: records, page map, extra edges
+  int32_t tab_vec;           // its size in 16-byte units
+  uint32_t off_pmap, off_extra;
+  const int32_t *lane_info;  // [P][4] {first global op, ops, busy time, record base}
+  uint32_t group_bytes, off_ring, end_vec;   // end_vec: 16-byte units of the end times
+  int32_t P, wpb;
+  uint32_t *next_cand;       // candidates handed out on demand, past static_end
+  int64_t static_end;        // (a multiple of the resident groups, or INT64_MAX)
+  const int32_t *xcost;      // as SimArgs::xcost
+  const int64_t *list;       // list mode, as SimArgs
+  const uint32_t *list_count;
+};
+const void *direct_kernel_ptr(int pwl, bool paged, bool sel);
+hipError_t launch_direct(int pwl, bool paged, bool sel, int blocks, int wpb, size_t lds,
+                         hipStream_t s, const DirectArgs &a);
 
 // ---------------------------------------------------------------- selection check
 // Schedules under a memory selection before their re-timed simulation:

@@ -73,3 +73,33 @@ def test_small_batches_and_pool_bounds(P, M, v, n):
     print(f"P={P} M={M} v={v} n={n}", flush=True)
     compare(prob, rows)
     compare(prob, rows, lambda s: s.configure_pool(4))
+
+
+@pytest.mark.parametrize("P,M,n", [(4, 90, 20000), (8, 70, 9000), (64, 40, 3000)])
+def test_pools_that_fill_in_large_batches(P, M, n):
+    """Batches beyond the resident groups whose first ranks run far ahead of
+    the last one (all forwards first, the last rank's in reverse): every pool
+    size fills, and the candidates end in the kernel that keeps all end times,
+    started over a list; a part of the batch deadlocks there."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng([P, M, n])
+    prob = W.compile_instance(W.pipeline_instance(P, M, rng.integers(1, 50, (P, M)), comm=2, act=1, mem_cap=2 * M))
+    base = W.OrderGenerator(prob, W.MODE_LIST, 2, 0, 3, 0).generate(0, 64)
+    fwd_first = np.concatenate([np.argsort(prob.op_kind[a:b], kind="stable") for a, b in
+                                zip(prob.rank_off[:-1], prob.rank_off[1:])])
+    last = fwd_first[int(prob.rank_off[P - 1]):]
+    last[:M] = last[:M][::-1].copy()                       # needs the last forward first
+    base[1::2] = fwd_first.astype(base.dtype)
+    for c in range(5, 64, 8):
+        a, b = int(prob.rank_off[P - 1]), int(prob.rank_off[P])
+        base[c, a:b] = rng.permutation(b - a)
+    rows = np.ascontiguousarray(base[np.arange(n) % 64])
+    print(f"P={P} M={M} n={n}", flush=True)
+    want = O.evaluate(prob, base, threads=16)
+    sim = dip.Sim(prob)
+    out = sim.evaluate(torch.from_numpy(rows).to(DEV))
+    torch.cuda.synchronize()
+    for got, exp in zip(out, (want.makespan, want.bubble, want.peak, want.flags)):
+        np.testing.assert_array_equal(got.cpu().numpy(), exp[np.arange(n) % 64])
+    sim.close()
