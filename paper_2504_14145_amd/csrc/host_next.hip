@@ -538,6 +538,35 @@ int dip_sim_rollouts(dip_sim *h, const int32_t *prefix, int32_t depth, int64_t n
                                 out_makespan, out_flags, inout_best_key, stream_);
 }
 
+// Launch shapes of the memory selection, for groups of 16 and of 64 lanes:
+// the waves per block that leave the most problems resident on a CU (the
+// rank's tables are shared by a block, so more waves take less LDS each).
+static void plan_memopt(dip_sim *h) {
+  const int32_t mp = std::max(h->mo_max_pairs, 1);
+  for (int g = 0; g < 2; ++g) {
+    const int lanes = g ? 64 : 16;
+    const void *k = memopt_group_ptr(lanes, mp);
+    int best = 0;
+    h->mo_waves[g] = 0;
+    for (int w = 1; k && w <= 8; w *= 2) {
+      const int64_t lds = memopt_group_lds(mp, w * 64 / lanes);
+      int nb = 0;
+      if (lds > h->lds_block_max) break;
+      if ((lds > 65536 && hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              int(h->lds_block_max)) != hipSuccess) ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, w * kWave, size_t(lds)) != hipSuccess) {
+        (void)hipGetLastError();
+        break;
+      }
+      if (nb * w >= best && nb > 0) {
+        best = nb * w;
+        h->mo_waves[g] = w;
+      }
+    }
+    h->mo_slots[g] = int64_t(best) * (kWave / lanes) * h->n_cu;
+  }
+}
+
 int dip_sim_configure_memopt(dip_sim *h, const int32_t *slot_layers, const int64_t *layer_time,
                              const int64_t *layer_mem, int32_t n_strategies, int32_t n_candidates,
                              int32_t bb_nodes) {
@@ -684,6 +713,7 @@ int dip_sim_configure_memopt(dip_sim *h, const int32_t *slot_layers, const int64
   h->mo_pair_extra = pair_extra;
   h->mo_max_extra = 0;
   for (int64_t x : pair_extra) h->mo_max_extra = std::max(h->mo_max_extra, x);
+  plan_memopt(h);
   h->mo_ok = true;
   return DIP_OK;
 }
@@ -719,15 +749,14 @@ int dip_sim_memopt(dip_sim *h, const int16_t *orders, int64_t n_cand, int64_t *o
   a.max_pairs = std::max(h->mo_max_pairs, 1);
   (void)hipGetLastError();
   if (a.max_pairs <= 512) {
-    // a wave per (schedule, rank), pairs in registers; four waves per block
-    // where their LDS fits, else two, else one
-    int waves = 4;
-    while (waves > 1 && memopt_wave_lds(a.max_pairs, waves) > 65536) waves /= 2;
-    int ppl = 1;
-    while (64 * ppl < a.max_pairs) ppl *= 2;
-    if ((n_cand + waves - 1) / waves > INT32_MAX || h->P > 65535) return DIP_E_INVAL;
-    if (memopt_wave_lds(a.max_pairs, waves) > 65536) return DIP_E_UNSUPPORTED;
-    DIP_HIP(launch_memopt_wave(ppl, waves, static_cast<hipStream_t>(stream), a));
+    // Four problems a wave once the problems outnumber the resident waves of
+    // one each (131,072 problems of 64 pairs: 2.98 ms against 6.30; 4,096:
+    // 475 us against 363), up to 96 pairs (131,072 of 96: 4.9 ms against 7.7;
+    // of 128: 10.3 against 9.0, the lanes' state having crowded out waves).
+    const int g = h->mo_waves[0] && n_cand * h->P > h->mo_slots[1] ? 0 : 1;
+    if (!h->mo_waves[g]) return DIP_E_UNSUPPORTED;
+    if (n_cand > INT32_MAX || h->P > 65535) return DIP_E_INVAL;
+    DIP_HIP(launch_memopt_group(g ? 64 : 16, h->mo_waves[g], static_cast<hipStream_t>(stream), a));
     return DIP_OK;
   }
   a.bytes_per_thread = int32_t(int64_t(a.max_pairs) * 9);

@@ -256,6 +256,8 @@ struct dip_sim {
   uint8_t *d_rl_mo_status = nullptr, *d_rl_choice = nullptr;
   int64_t rl_mo_cap = 0;
   // per-layer memory optimisation (dip_sim_configure_memopt / dip_sim_memopt)
+  int mo_waves[2] = {0, 0};            // waves per block, groups of 16 and of 64 lanes (0: not run)
+  int64_t mo_slots[2] = {0, 0};        // resident problems of each
   bool mo_ok = false;
   int32_t mo_max_pairs = 0, mo_n_pairs = 0, mo_bb_nodes = 512;
   int64_t mo_max_extra = 0;            // largest slowest-less-fastest time of a pair

@@ -498,11 +498,11 @@ struct MemoptArgs {
   int32_t bytes_per_thread;   // LDS per thread: 9 bytes per pair
 };
 hipError_t launch_memopt(int threads_per_block, hipStream_t s, const MemoptArgs &a);
-// a wave per (schedule, rank), waves_per_block schedules of one rank per block,
-// up to 64 * ppl pairs per rank (ppl 1, 2, 4, 8); LDS per block:
-// (68 + 7 * waves_per_block) bytes per pair
-hipError_t launch_memopt_wave(int ppl, int waves_per_block, hipStream_t s, const MemoptArgs &a);
-size_t memopt_wave_lds(int32_t max_pairs, int waves_per_block);
+// a group of lanes (16 or 64) per (schedule, rank), blocks of one rank; up to
+// 16 * 6 or 64 * 8 pairs per rank; LDS per block of so many groups
+const void *memopt_group_ptr(int lanes, int32_t max_pairs);  // null: too many pairs
+hipError_t launch_memopt_group(int lanes, int waves_per_block, hipStream_t s, const MemoptArgs &a);
+int64_t memopt_group_lds(int32_t max_pairs, int groups_per_block);
 
 // ---------------------------------------------------------------- argmin
 // Least (makespan << 32 | base + index) over unflagged rows into *key, per

@@ -32,15 +32,30 @@
 // schedule, so the host ranks every move of a rank once (exact 128-bit cross
 // products) and hands each a 32-bit key: the least key is the greedy's
 // choice.  Two kernels:
-//   memopt_wave_kernel  a wave per (schedule, rank), lane j owning pairs
-//                       j, j + 64, ... in registers; the most loaded
-//                       checkpoint and the best move are one DPP wave
-//                       reduction each; a block holds schedules of one rank
-//                       and shares that rank's move tables in LDS.  In the
-//                       search, lane j also holds the stack entries of
-//                       depths j, j + 64, ... (candidate, placed time,
-//                       fastest time of the rest), and a checkpoint's load
-//                       is one wave sum over the placed pairs.
+//   memopt_group_kernel a group of 16 or 64 lanes per (schedule, rank), lane
+//                       j owning pairs j, j + G, ...; a block holds schedules
+//                       of one rank and shares that rank's tables in LDS.
+//                       The pairs are numbered once in forward order, where
+//                       a pair is live at a run of checkpoints: loads are
+//                       prefix sums of differences, "live there" is one
+//                       subtraction and one comparison, and in the search
+//                       the load at a depth is the one above it plus the
+//                       placed pair less those whose run ends (a list per
+//                       checkpoint), so that a visit of a depth tries all
+//                       its candidates at once, a lane each.  The search is
+//                       left out where its bound already cuts every first
+//                       placement (the fastest times alone reach it).
+//                       Bound by vector instructions where problems are
+//                       many: 16 lanes, since the state of up to 96 pairs
+//                       fits six registers a lane and the steps' fixed cost
+//                       (three reductions a move) serves four problems.
+//                       Few or large problems are bound by the LDS round
+//                       trips of their serial steps: 64 lanes.  32,768
+//                       schedules of 8 ranks (32 to 68 pairs): 2.5 ms, 10.1
+//                       with a wave per problem, its loads summed over all
+//                       pairs, its search a candidate at a time and its
+//                       tables in device memory; 1,024 rollouts of 16 ranks
+//                       (128 and 196 pairs): 1.0 ms, 2.34.
 //   memopt_kernel       a thread per (schedule, rank), for ranks of more
 //                       than 512 pairs (steps 1 and 2); its state sits in
 //                       LDS, element-major across the block.
@@ -65,11 +80,6 @@ constexpr int kMemoptLagrHalve = 24;   // steps between halvings of the step siz
 // bits of a non-negative value (0 for 0)
 __device__ __forceinline__ int bits64(int64_t x) { return x ? 64 - __clzll(x) : 0; }
 
-__device__ __forceinline__ void lds_sync_wave() {
-  lds_wait();
-  __builtin_amdgcn_wave_barrier();
-}
-
 // min / max of one value over the 64 lanes of a wave, read out of lane 63:
 // the row reduction of dpp_row, then the row broadcasts (lane 15 of each row
 // into the next row, lane 31 into rows 2 and 3), rows outside the mask
@@ -85,23 +95,6 @@ __device__ __forceinline__ uint32_t wave_reduce63(uint32_t v) {
   v = op(v, uint32_t(__builtin_amdgcn_update_dpp(kId, int(v), 0x142, 0xa, 0xf, false)));  // row_bcast:15
   v = op(v, uint32_t(__builtin_amdgcn_update_dpp(kId, int(v), 0x143, 0xc, 0xf, false)));  // row_bcast:31
   return uint32_t(__builtin_amdgcn_readlane(int(v), 63));
-}
-
-// sum of one value over the 64 lanes of a wave (wrapping), the same in every lane
-__device__ __forceinline__ int32_t wave_sum(int32_t v) {
-  v += int32_t(dpp_row<0xb1>(uint32_t(v)));    // quad_perm [1,0,3,2]
-  v += int32_t(dpp_row<0x4e>(uint32_t(v)));    // quad_perm [2,3,0,1]
-  v += int32_t(dpp_row<0x141>(uint32_t(v)));   // row_half_mirror
-  v += int32_t(dpp_row<0x140>(uint32_t(v)));   // row_mirror
-  return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
-         __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
-}
-
-__device__ __forceinline__ int64_t wave_sum64(int64_t v) {
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1)
-    v += (int64_t(__shfl_xor(int(v >> 32), s)) << 32) | uint32_t(__shfl_xor(int(uint32_t(v)), s));
-  return v;
 }
 
 __device__ __forceinline__ void write_out(const MemoptArgs &a, int64_t o, int64_t t, int32_t pk,
@@ -232,518 +225,592 @@ __global__ __launch_bounds__(256) void memopt_kernel(MemoptArgs a) {
 #undef pb
 #undef cur
 
-// ---------------------------------------------------------------- wave per problem
+// ---------------------------------------------------------------- lane group per problem
 
-template <int PPL>
-__global__ __launch_bounds__(256) void memopt_wave_kernel(MemoptArgs a) {
+// Reductions over the G lanes of a group (16: one row of the wave, 64: the
+// wave), the result in every lane.  A group's lanes are all active or none.
+template <int G>
+struct group_ops {
+  static __device__ __forceinline__ uint32_t dpp16(uint32_t v, bool is_max) {
+    auto op = [&](uint32_t x, uint32_t y) { return is_max ? max(x, y) : min(x, y); };
+    v = op(v, dpp_row<0xb1>(v));    // quad_perm [1,0,3,2]
+    v = op(v, dpp_row<0x4e>(v));    // quad_perm [2,3,0,1]
+    v = op(v, dpp_row<0x141>(v));   // row_half_mirror
+    v = op(v, dpp_row<0x140>(v));   // row_mirror
+    return v;
+  }
+  static __device__ __forceinline__ uint32_t max32(uint32_t v) {
+    return G == 64 ? wave_reduce63<true>(v) : dpp16(v, true);
+  }
+  static __device__ __forceinline__ uint32_t min32(uint32_t v) {
+    return G == 64 ? wave_reduce63<false>(v) : dpp16(v, false);
+  }
+  template <int CTRL>
+  static __device__ __forceinline__ int64_t dpp64(int64_t v) {
+    return int64_t((uint64_t(dpp_row<CTRL>(uint32_t(uint64_t(v) >> 32))) << 32) |
+                   dpp_row<CTRL>(uint32_t(v)));
+  }
+  static __device__ __forceinline__ int64_t read64(int64_t v, int l) {
+    return int64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), l))) |
+           (int64_t(__builtin_amdgcn_readlane(int(v >> 32), l)) << 32);
+  }
+  template <class Op>
+  static __device__ __forceinline__ int64_t all64(int64_t v, Op op) {
+    v = op(v, dpp64<0xb1>(v));      // quad_perm [1,0,3,2]
+    v = op(v, dpp64<0x4e>(v));      // quad_perm [2,3,0,1]
+    v = op(v, dpp64<0x141>(v));     // row_half_mirror
+    v = op(v, dpp64<0x140>(v));     // row_mirror
+    if (G == 64) v = op(op(read64(v, 0), read64(v, 16)), op(read64(v, 32), read64(v, 48)));
+    return v;
+  }
+  static __device__ __forceinline__ int64_t sum64(int64_t v) {
+    return all64(v, [](int64_t x, int64_t y) { return x + y; });
+  }
+  static __device__ __forceinline__ int64_t max64(int64_t v) {
+    return all64(v, [](int64_t x, int64_t y) { return max(x, y); });
+  }
+  // lanes of the group where p holds
+  static __device__ __forceinline__ uint64_t ballot(bool p, int lane) {
+    const uint64_t b = __ballot(p);
+    if (G == 64) return b;
+    const uint32_t w = (lane & 32) ? uint32_t(b >> 32) : uint32_t(b);
+    return (w >> (lane & 16)) & 0xffffu;
+  }
+  // inclusive prefix sum; zeros come in at a row's start
+  static __device__ __forceinline__ int32_t scan32(int32_t v, int lane) {
+    v += int32_t(dpp_row<0x111>(uint32_t(v)));   // row_shr:1
+    v += int32_t(dpp_row<0x112>(uint32_t(v)));
+    v += int32_t(dpp_row<0x114>(uint32_t(v)));
+    v += int32_t(dpp_row<0x118>(uint32_t(v)));
+    if (G == 64) {
+      const int32_t r0 = __builtin_amdgcn_readlane(v, 15), r1 = __builtin_amdgcn_readlane(v, 31),
+                    r2 = __builtin_amdgcn_readlane(v, 47);
+      v += lane < 16 ? 0 : lane < 32 ? r0 : lane < 48 ? r0 + r1 : r0 + r1 + r2;
+    }
+    return v;
+  }
+  // the value of the group's last lane
+  static __device__ __forceinline__ int32_t last32(int32_t v, int lane) {
+    return G == 64 ? __builtin_amdgcn_readlane(v, 63) : __shfl(v, lane | 15);
+  }
+  static __device__ __forceinline__ int64_t last64(int64_t v, int lane) {
+    return int64_t(uint32_t(last32(int32_t(uint32_t(v)), lane))) |
+           (int64_t(last32(int32_t(v >> 32), lane)) << 32);
+  }
+  static __device__ __forceinline__ int64_t scan64(int64_t v, int lane) {
+    v += dpp64<0x111>(v);
+    v += dpp64<0x112>(v);
+    v += dpp64<0x114>(v);
+    v += dpp64<0x118>(v);
+    if (G == 64) {
+      const int64_t r0 = read64(v, 15), r1 = read64(v, 31), r2 = read64(v, 47);
+      v += lane < 16 ? 0 : lane < 32 ? r0 : lane < 48 ? r0 + r1 : r0 + r1 + r2;
+    }
+    return v;
+  }
+};
+
+// 105 x >= 100 y for y >= 0: x >= y - y / 21
+__device__ __forceinline__ int64_t gap_bound(int64_t y) { return y - int64_t(uint64_t(y) / 21); }
+
+// LDS bytes of the tables a block shares (per pair of the rank: candidates'
+// times, memories and move keys, the two ends' op entries, candidate count)
+// and of one problem's arrays
+__host__ __device__ constexpr int64_t group_table_bytes(int64_t mp) {
+  return (mp * (kMemoptMaxCands * 16 + 5) + 7) / 8 * 8;
+}
+__host__ __device__ constexpr int64_t group_problem_bytes(int64_t mp) {
+  return (18 * mp + 16 + 7) / 8 * 8;
+}
+
+template <int G, int PPL>
+__global__ __launch_bounds__(512) void memopt_group_kernel(MemoptArgs a) {
   extern __shared__ __align__(16) unsigned char sh[];
+  using R = group_ops<G>;
+  constexpr int C = kMemoptMaxCands;
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int gl = lane & (G - 1);
+  const int gb = threadIdx.x / G;
   const int r = blockIdx.y;
-  const int64_t c = int64_t(blockIdx.x) * nw + wv;
+  const int64_t c = int64_t(blockIdx.x) * (blockDim.x / G) + gb;
   const int32_t pbase = a.pair_off[r];
   const int32_t np = a.pair_off[r + 1] - pbase;
   const int64_t mp = a.max_pairs;
-  // the rank's tables, shared by the block: move keys and freed memory
-  // [pair][candidate], memory of the fastest candidate [pair]
-  uint32_t *tkey = reinterpret_cast<uint32_t *>(sh);
-  int32_t *tdm = reinterpret_cast<int32_t *>(sh + 32 * mp);
-  int32_t *tm0 = reinterpret_cast<int32_t *>(sh + 64 * mp);
-  // this wave's positions of each pair's forward and backward, its pairs in
-  // the order of their forwards, and the final choice of each pair
-  uint16_t *pfa = reinterpret_cast<uint16_t *>(sh + 68 * mp) + int64_t(wv) * 3 * mp;
-  uint16_t *pba = pfa + mp;
-  uint16_t *orda = pba + mp;
-  uint8_t *sela = sh + 68 * mp + 6 * mp * nw + int64_t(wv) * mp;
-  // the certificate's arrays over the checkpoints in forward order: prefix
-  // sums of the multipliers, memory differences, multipliers
-  int64_t *lps = reinterpret_cast<int64_t *>(sh + ((68 + 7 * nw) * mp + 7) / 8 * 8) +
-                 int64_t(wv) * 3 * (mp + 1);
+  const int nq = (np + G - 1) / G;
+  // shared tables
+  int64_t *tt = reinterpret_cast<int64_t *>(sh);
+  int32_t *tm = reinterpret_cast<int32_t *>(sh + 8 * C * mp);
+  uint32_t *tk = reinterpret_cast<uint32_t *>(sh + 12 * C * mp);
+  uint16_t *tw = reinterpret_cast<uint16_t *>(sh + 16 * C * mp);
+  uint8_t *tn = sh + (16 * C + 4) * mp;
+  const int32_t base = a.rank_off[r], nr = a.rank_off[r + 1] - base;
   {
-    const uint32_t *gk = a.move_key + int64_t(pbase) * kMemoptMaxCands;
-    const int32_t *gd = a.move_dm + int64_t(pbase) * kMemoptMaxCands;
-    const int32_t *gm = a.cand_mem + int64_t(pbase) * kMemoptMaxCands;
-    for (int32_t x = threadIdx.x; x < np * kMemoptMaxCands; x += blockDim.x) {
-      tkey[x] = gk[x];
-      tdm[x] = gd[x];
+    const int64_t *gt = a.cand_time + int64_t(pbase) * C;
+    const int32_t *gm = a.cand_mem + int64_t(pbase) * C;
+    const uint32_t *gk = a.move_key + int64_t(pbase) * C;
+    for (int32_t x = threadIdx.x; x < np * C; x += blockDim.x) {
+      tt[x] = gt[x];
+      tm[x] = gm[x];
+      tk[x] = gk[x];
     }
-    for (int32_t i = threadIdx.x; i < np; i += blockDim.x) tm0[i] = gm[i * kMemoptMaxCands];
+    for (int32_t x = threadIdx.x; x < nr; x += blockDim.x) {
+      const uint32_t w = uint32_t(a.lid_pair[base + x]);
+      tw[x] = uint16_t((w & 0x7fffu) | (w >> 31 << 15));
+    }
+    for (int32_t i = threadIdx.x; i < np; i += blockDim.x) {
+      int32_t n = 1;
+      while (n < C && gk[i * C + n - 1] != kMemoptNoMove) ++n;
+      tn[i] = uint8_t(n);
+    }
   }
   __syncthreads();
-  if (c >= a.n_cand) return;                        // whole waves, after the last barrier
-  for (int32_t i = lane; i < np; i += 64) {
-    pfa[i] = 0xffffu;
-    pba[i] = 0xffffu;
+  if (c >= a.n_cand) return;                        // whole groups, after the last barrier
+  // this problem's arrays: 13 bytes a pair that the steps use in turn, then
+  // each pair's first checkpoint (in forward order), how many it is live at,
+  // and its choice
+  unsigned char *ws = sh + group_table_bytes(mp) + gb * group_problem_bytes(mp);
+  uint16_t *plo = reinterpret_cast<uint16_t *>(ws + 13 * mp + 12 + (mp & 1));
+  uint16_t *pln = plo + mp;
+  uint8_t *cur = reinterpret_cast<uint8_t *>(pln + mp);
+  int32_t *acc = reinterpret_cast<int32_t *>(ws);   // [np + 1]
+
+  // ---- forward order of the pairs and the checkpoints each is live at
+  for (int32_t i = gl; i < np; i += G) {
+    plo[i] = 0xffffu;
+    pln[i] = 0xffffu;
+    cur[i] = 0;
   }
-  lds_sync_wave();
-  const int32_t base = a.rank_off[r], nr = a.rank_off[r + 1] - base;
+  for (int32_t d = gl; d <= np; d += G) acc[d] = 0;
+  wave_lds_order();
   const int16_t *row = a.orders + c * a.stride + base;
   bool bad = false;
-  for (int32_t p = lane; p < nr; p += 64) {
-    const int32_t lid = row[p];
-    if (lid < 0 || lid >= nr) {
-      bad = true;
-      continue;
+  int32_t nf = 0;                                   // forwards so far
+  for (int32_t p0 = 0; p0 < nr; p0 += 4 * G) {
+    int32_t lid[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t p = p0 + u * G + gl;
+      lid[u] = p < nr ? int32_t(row[p]) : -1;
     }
-    const uint32_t w = uint32_t(a.lid_pair[base + lid]);
-    ((w >> 31) ? pba : pfa)[w & 0x7fffffffu] = uint16_t(p);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p0 + u * G >= nr) break;
+      const bool in = lid[u] >= 0 && lid[u] < nr;
+      bad |= p0 + u * G + gl < nr && !in;
+      const uint32_t w = in ? tw[lid[u]] : 0u;
+      const bool fwd = in && !(w >> 15);
+      const uint64_t m = R::ballot(fwd, lane);
+      const int32_t before = nf + __popcll(m & ((uint64_t(1) << gl) - 1));
+      if (in) (fwd ? plo : pln)[w & 0x7fffu] = uint16_t(before);
+      nf += __popcll(m);
+    }
   }
-  lds_sync_wave();
-  // every rank op is one end of one pair, so with all nr ids in range a
-  // repeated id leaves some end unfilled
-  for (int32_t i = lane; i < np; i += 64)
-    if (pfa[i] == 0xffffu || pba[i] == 0xffffu) bad = true;
-  const int64_t o = c * a.P + r;
-  if (__any(bad)) {
-    if (lane == 0) write_out(a, o, -1, -1, 2);
-    return;
-  }
-  // own pairs: positions, current candidate, its next move (key, freed
-  // memory), load of the own checkpoint under the fastest candidates
-  uint32_t pf[PPL], pb[PPL], key[PPL];
-  int32_t cur[PPL], dm[PPL], load[PPL];
+  wave_lds_order();
+  // own pairs: forward-order index (with the pair's index above it), length
+  // of the live range (0: its backward comes first), key of its next move
+  uint32_t P[PPL], key[PPL];
+  uint16_t ln[PPL];
+  int32_t load[PPL];
 #pragma unroll
   for (int q = 0; q < PPL; ++q) {
-    const int32_t i = lane + 64 * q;
-    const bool own = i < np;
-    pf[q] = own ? pfa[i] : 0xffffu;
-    pb[q] = own ? pba[i] : 0u;
-    cur[q] = 0;
-    key[q] = own ? tkey[i * kMemoptMaxCands] : kMemoptNoMove;
-    dm[q] = own ? tdm[i * kMemoptMaxCands] : 0;
-    int32_t s = 0;
-    if (own)
-      for (int32_t j = 0; j < np; ++j)
-        if (pfa[j] <= pf[q] && pf[q] <= pba[j]) s += tm0[j];
-    load[q] = s;
+    P[q] = 0xffffffffu;
+    ln[q] = 0;
+    key[q] = kMemoptNoMove;
+    load[q] = 0;
+    const int32_t i = gl + G * q;
+    if (i < np) {
+      const uint32_t x = plo[i], y = pln[i];
+      // every rank op is one end of one pair, so with all nr ids in range a
+      // repeated id leaves some end unfilled
+      if (x == 0xffffu || y == 0xffffu) bad = true;
+      P[q] = uint32_t(i) << 16 | x;
+      ln[q] = uint16_t(y > x ? y - x : 0);
+      key[q] = tk[i * C];
+    }
   }
+  const int64_t o = c * a.P + r;
+  if (R::ballot(bad, lane)) {
+    if (gl == 0) write_out(a, o, -1, -1, 2);
+    return;
+  }
+  // loads under the fastest candidates: sums of differences over the
+  // checkpoints in forward order
+  auto scan_loads = [&]() {
+    int32_t run = 0, top = 0;
+    for (int32_t q = 0; q < nq; ++q) {
+      const int32_t d = gl + G * q;
+      const int32_t v = R::scan32(d < np ? acc[d] : 0, lane) + run;
+      if (d < np) acc[d] = v;
+      top = max(top, v);
+      run = R::last32(v, lane);
+    }
+    return top;
+  };
+#pragma unroll
+  for (int q = 0; q < PPL; ++q) {
+    const int32_t i = gl + G * q;
+    if (i < np) {
+      pln[i] = ln[q];
+      if (ln[q]) {
+        const int32_t x = P[q] & 0xffffu;
+        atomicAdd(acc + x, tm[i * C]);
+        atomicAdd(acc + x + ln[q], -tm[i * C]);
+      }
+    }
+  }
+  wave_lds_order();
+  (void)scan_loads();
+  wave_lds_order();
+#pragma unroll
+  for (int q = 0; q < PPL; ++q)
+    if (gl + G * q < np) load[q] = acc[P[q] & 0xffffu];
+  // checkpoint of slot q within the range of a pair
+  auto covers = [](uint32_t at, uint32_t lo, uint32_t len) {
+    return uint16_t(at - lo) < uint16_t(len);
+  };
+
+  // ---- step 1: the greedy warm start
   const int32_t cap = a.cap[r];
-  bool ok = true;
-  if (cap >= 0) {
+  bool ok = true, moved = false;
+  if (cap >= 0 && np > 0) {
     for (;;) {
-      // most loaded checkpoint (order-preserving unsigned image of the load)
-      uint32_t mx = 0;
+      // most loaded checkpoint, lowest pair index among equal loads
+      int32_t bl = -1;
+      uint32_t bp = 0xffffffffu;
 #pragma unroll
       for (int q = 0; q < PPL; ++q)
-        if (lane + 64 * q < np) mx = max(mx, uint32_t(load[q]) ^ 0x80000000u);
-      mx = wave_reduce63<true>(mx);
-      const int32_t top = int32_t(mx ^ 0x80000000u);
-      if (np == 0 || top <= cap) break;
-      // its forward position: the lowest pair index holding that load
-      uint32_t pfk = 0;
-      bool found = false;
-#pragma unroll
-      for (int q = 0; q < PPL; ++q) {
-        const uint64_t b = __ballot(lane + 64 * q < np && load[q] == top);
-        if (!found && b) {
-          pfk = uint32_t(__builtin_amdgcn_readlane(int(pf[q]), __builtin_ctzll(b)));
-          found = true;
+        if (q < nq) {
+          bp = load[q] > bl ? P[q] : bp;
+          bl = max(bl, load[q]);
         }
-      }
+      const uint32_t top = R::max32(uint32_t(bl));
+      if (int32_t(top) <= cap) break;
+      const uint32_t dk = R::min32(uint32_t(bl) == top ? bp : 0xffffffffu);
       // best move among the pairs live there
       uint32_t m = kMemoptNoMove;
 #pragma unroll
       for (int q = 0; q < PPL; ++q)
-        if (pf[q] <= pfk && pfk <= pb[q]) m = min(m, key[q]);
-      m = wave_reduce63<false>(m);
+        if (q < nq) m = min(m, covers(dk, P[q], ln[q]) ? key[q] : kMemoptNoMove);
+      m = R::min32(m);
       if (m == kMemoptNoMove) {
         ok = false;
         break;
       }
-      const int32_t bi = int32_t(m & ((1u << kMemoptPairBits) - 1));
-      const int qb = bi >> 6, ob = bi & 63;
-      // the moved pair's positions from the wave's tables, its freed memory
-      // from its owner lane
-      const uint32_t spf = pfa[bi], spb = pba[bi];
-      int32_t sdm = 0;
+      moved = true;
+      // every checkpoint the moved pair is live at drops; the pair steps on
+      // (every lane of the group writes the same choice)
+      const uint32_t bi = m & ((1u << kMemoptPairBits) - 1);
+      const uint32_t ci = cur[bi], x = bi * C + ci;
+      const int32_t dm = tm[x] - tm[x + 1];
+      const uint32_t nkey = tk[x + 1];
+      const uint32_t slo = plo[bi], sln = pln[bi];
+      cur[bi] = uint8_t(ci + 1);
 #pragma unroll
       for (int q = 0; q < PPL; ++q)
-        if (q == qb) sdm = dm[q];
-      sdm = __builtin_amdgcn_readlane(sdm, ob);
-      // every checkpoint the moved pair is live at drops; its owner steps on
-#pragma unroll
-      for (int q = 0; q < PPL; ++q) {
-        if (spf <= pf[q] && pf[q] <= spb) load[q] -= sdm;
-        if (q == qb && lane == ob) {
-          const int32_t x = bi * kMemoptMaxCands + ++cur[q];
-          key[q] = tkey[x];
-          dm[q] = tdm[x];
+        if (q < nq) {
+          load[q] -= covers(P[q], slo, sln) ? dm : 0;
+          key[q] = bi == uint32_t(gl + G * q) ? nkey : key[q];
         }
-      }
     }
   }
-  const int64_t *ct = a.cand_time + int64_t(pbase) * kMemoptMaxCands;
-  const int32_t *cmem = a.cand_mem + int64_t(pbase) * kMemoptMaxCands;
-  // the register of slot q of every lane as one value, and its update in one lane
-  auto pick = [](const auto (&v)[PPL], int qd) {
-    auto x = v[0];
-#pragma unroll
-    for (int q = 1; q < PPL; ++q)
-      if (q == qd) x = v[q];
-    return x;
-  };
-  auto own = [&](int q) { return lane + 64 * q < np; };
+  wave_lds_order();
   uint8_t status = ok ? 1 : 0;
-  if (ok && cap >= 0 && np > 0) {
+  if (ok && moved) {
     // ---- step 2: back to faster candidates where every checkpoint allows
     for (bool changed = true; changed;) {
       changed = false;
-      for (int32_t i = 0; i < np; ++i) {
-        const uint32_t spf = pfa[i], spb = pba[i];
-        uint32_t mx = 0;
-#pragma unroll
-        for (int q = 0; q < PPL; ++q)
-          if (own(q) && spf <= pf[q] && pf[q] <= spb) mx = max(mx, uint32_t(load[q]) ^ 0x80000000u);
-        const int64_t top = int32_t(wave_reduce63<true>(mx) ^ 0x80000000u);
-        const int qi = i >> 6, li = i & 63;
-        const int32_t ci = __builtin_amdgcn_readlane(pick(cur, qi), li);
-        const int32_t mc = cmem[i * kMemoptMaxCands + ci];
-        int32_t nj = ci;
-        for (int32_t j = 0; j < ci; ++j)
-          if (top + (cmem[i * kMemoptMaxCands + j] - mc) <= int64_t(cap)) {
-            nj = j;
-            break;
-          }
-        if (nj < ci) {
-          const int32_t add = cmem[i * kMemoptMaxCands + nj] - mc;
-#pragma unroll
-          for (int q = 0; q < PPL; ++q) {
-            if (own(q) && spf <= pf[q] && pf[q] <= spb) load[q] += add;
-            if (q == qi && lane == li) cur[q] = nj;
-          }
-          changed = true;
-        }
-      }
-    }
-
-    // ---- step 3: branch and bound, pairs by forward position
-    // depth of each own pair: the pairs whose forward comes earlier
-#pragma unroll
-    for (int q = 0; q < PPL; ++q)
-      if (own(q)) {
-        int32_t dep = 0;
-        for (int32_t j = 0; j < np; ++j) dep += pfa[j] < pf[q] ? 1 : 0;
-        orda[dep] = uint16_t(lane + 64 * q);
-      }
-    lds_sync_wave();
-    // stack entries of depths lane + 64 q: pair, candidate, placed time
-    // above the depth, fastest time of the pairs from the depth on
-    int32_t dpair[PPL], dch[PPL];
-    int64_t dplaced[PPL], drest[PPL];
-    // own pairs: candidate and memory of the current placement, best choice
-    int32_t pcur[PPL], pmem[PPL], best[PPL];
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-      dpair[q] = own(q) ? orda[lane + 64 * q] : 0;
-      dch[q] = -1;
-      dplaced[q] = 0;
-      drest[q] = 0;
-      pcur[q] = 0;
-      pmem[q] = 0;
-      best[q] = cur[q];
-    }
-    {
-      int64_t rest = 0;
-      for (int32_t d = np - 1; d >= 0; --d) {
-        rest += ct[int32_t(orda[d]) * kMemoptMaxCands];
-#pragma unroll
-        for (int q = 0; q < PPL; ++q)
-          if (q == (d >> 6) && lane == (d & 63)) drest[q] = rest;
-      }
-    }
-    int64_t inc = 0;
-#pragma unroll
-    for (int q = 0; q < PPL; ++q)
-      if (own(q)) inc += ct[(lane + 64 * q) * kMemoptMaxCands + cur[q]];
-    inc = wave_sum64(inc);
-    bool proven = true;
-    uint32_t seen = 0;
-    int32_t d = 0;
-    while (d >= 0) {
-      const int qd = d >> 6, ld = d & 63;
-      const int32_t i = __builtin_amdgcn_readlane(pick(dpair, qd), ld);
-      const int32_t c = __builtin_amdgcn_readlane(pick(dch, qd), ld) + 1;
-      // candidate c of pair i exists when the move into it does
-      const bool has = c < kMemoptMaxCands && (c == 0 || tkey[i * kMemoptMaxCands + c - 1] != kMemoptNoMove);
-      if (!has) {
-#pragma unroll
-        for (int q = 0; q < PPL; ++q)
-          if (q == qd && lane == ld) dch[q] = -1;
-        --d;
-        continue;
-      }
-#pragma unroll
-      for (int q = 0; q < PPL; ++q)
-        if (q == qd && lane == ld) dch[q] = c;
-      if (++seen > uint32_t(a.bb_nodes)) {
-        proven = false;
-        break;
-      }
-      const int64_t t = ct[i * kMemoptMaxCands + c];
-      const int32_t m = cmem[i * kMemoptMaxCands + c];
-      // its checkpoint: the placed pairs (forward earlier) still live there
-      const uint32_t spf = pfa[i];
-      int32_t part = 0;
-#pragma unroll
-      for (int q = 0; q < PPL; ++q)
-        if (own(q) && pf[q] < spf && pb[q] >= spf) part += pmem[q];
-      // (a pair whose backward comes before its forward is live nowhere)
-      const int64_t own_m = pba[i] >= spf ? int64_t(m) : 0;
-      if (own_m + wave_sum(part) > int64_t(cap)) continue;   // a leaner one may fit
-      const int64_t f =
-          int64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(pick(dplaced, qd))), ld))) |
-          (int64_t(__builtin_amdgcn_readlane(int(pick(dplaced, qd) >> 32), ld)) << 32);
-      const int64_t f_t = f + t;
-      int64_t rest = 0;
-      if (d + 1 < np) {
-        const int q1 = (d + 1) >> 6, l1 = (d + 1) & 63;
-        rest = int64_t(uint32_t(__builtin_amdgcn_readlane(int(uint32_t(pick(drest, q1))), l1))) |
-               (int64_t(__builtin_amdgcn_readlane(int(pick(drest, q1) >> 32), l1)) << 32);
-      }
-      if (__int128(105) * (f_t + rest) >= __int128(100) * inc) {   // cut, with the slower ones
-#pragma unroll
-        for (int q = 0; q < PPL; ++q)
-          if (q == qd && lane == ld) dch[q] = kMemoptMaxCands;
-        continue;
-      }
-      const int qi = i >> 6, li = i & 63;
-#pragma unroll
-      for (int q = 0; q < PPL; ++q)
-        if (q == qi && lane == li) {
-          pcur[q] = c;
-          pmem[q] = m;
-        }
-      if (d == np - 1) {   // every pair placed, below the incumbent
-        inc = f_t;
-#pragma unroll
-        for (int q = 0; q < PPL; ++q) best[q] = pcur[q];
-        continue;
-      }
-      const int q1 = (d + 1) >> 6, l1 = (d + 1) & 63;
-#pragma unroll
-      for (int q = 0; q < PPL; ++q)
-        if (q == q1 && lane == l1) dplaced[q] = f_t;
-      ++d;
-    }
-    status = proven ? 1 : 3;
-    // the final choice and its checkpoint loads
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-      cur[q] = best[q];
-      if (own(q)) sela[lane + 64 * q] = uint8_t(cur[q]);
-    }
-    lds_sync_wave();
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-      int32_t s = 0;
-      if (own(q))
-        for (int32_t j = 0; j < np; ++j)
-          if (pfa[j] <= pf[q] && pf[q] <= pba[j]) s += cmem[j * kMemoptMaxCands + sela[j]];
-      load[q] = s;
-    }
-    if (!proven) {
-      // ---- step 4 (after the final choice, whose loads are set): the
-      // Lagrangian certificate.  Multipliers l_k >= 0 (units
-      // of 2^-F time per memory unit), one per checkpoint k (pair k's
-      // forward start).  Each step: a pair's price is the sum of the
-      // multipliers of the checkpoints it is live at; it takes its cheapest
-      // candidate under t * 2^F + m * price (the first on ties); the bound
-      // (times 2^F) is the sum of those values less cap * sum_k l_k, and
-      // proves the incumbent once 1.05 times it reaches the incumbent;
-      // otherwise each multiplier moves by g_k * step / 2^b, b the bits of
-      // max |g| (the magnitude shifted down, the sign kept; kept in [0,
-      // lmax]), g_k being the memory of the taken candidates live at
-      // checkpoint k less the cap, step = s0 / 2^(t / 24).  F = min(20, 60 -
-      // bits(np * tmax)), lmax = 2^60 / 2^bits(np^2 * max(1, mmax, cap)) and
-      // s0 = half the largest (dt << F) / 2^(bits(dm) - 1) over the moves
-      // from each pair's fastest candidate (at least 1, at most lmax) keep
-      // every value below 2^61, with no division.  A pair is live exactly at the
-      // checkpoints whose forward order lies in [its own, the number of
-      // forwards not after its backward), so both sums are differences of
-      // prefix sums over the checkpoints in forward order, kept in the
-      // wave's LDS.  Integer arithmetic: the same values as any other order
-      // of summation.
-      auto has = [&](int32_t i, int32_t j) {
-        return j < kMemoptMaxCands && (j == 0 || tkey[i * kMemoptMaxCands + j - 1] != kMemoptNoMove);
-      };
-      auto shfl64 = [](int64_t v, int src) {
-        return (int64_t(__shfl(int(v >> 32), src)) << 32) | uint32_t(__shfl(int(uint32_t(v)), src));
-      };
-      auto wave_max64 = [](int64_t v) {
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1)
-          v = max(v, (int64_t(__shfl_xor(int(v >> 32), s)) << 32) |
-                         uint32_t(__shfl_xor(int(uint32_t(v)), s)));
-        return v;
-      };
-      // inclusive prefix sum over the 64 lanes
-      auto wave_scan64 = [&](int64_t v) {
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) {
-          const int64_t y = shfl64(v, lane >= s ? lane - s : lane);
-          if (lane >= s) v += y;
-        }
-        return v;
-      };
-      int64_t tmx = 0, mmx = 0, s0 = 0;
-#pragma unroll
-      for (int q = 0; q < PPL; ++q)
-        if (own(q)) {
-          const int32_t i = lane + 64 * q;
-          for (int32_t j = 0; has(i, j); ++j) {
-            tmx = max(tmx, ct[i * kMemoptMaxCands + j]);
-            mmx = max(mmx, int64_t(cmem[i * kMemoptMaxCands + j]));
-          }
-        }
-      tmx = wave_max64(tmx);
-      mmx = wave_max64(mmx);
-      const int F = min(kMemoptLagrF, kMemoptLagrLimitBits - bits64(int64_t(np) * max(tmx, int64_t(1))));
-      const int lb = bits64(int64_t(np) * np * max(max(int64_t(1), mmx), int64_t(cap)));
-      const int64_t lmax = lb <= kMemoptLagrLimitBits ? int64_t(1) << (kMemoptLagrLimitBits - lb) : 0;
-      if (F >= 0 && lmax > 0) {
-#pragma unroll
-        for (int q = 0; q < PPL; ++q)
-          if (own(q)) {
-            const int32_t i = lane + 64 * q;
-            const int64_t t0 = ct[i * kMemoptMaxCands];
-            const int64_t m0 = cmem[i * kMemoptMaxCands];
-            for (int32_t j = 1; has(i, j); ++j)
-              s0 = max(s0, ((ct[i * kMemoptMaxCands + j] - t0) << F) >>
-                               (bits64(m0 - cmem[i * kMemoptMaxCands + j]) - 1));
-          }
-        s0 = min(lmax, max(int64_t(1), wave_max64(s0) >> 1));
-        // own pairs: the forward-order range [lo, hi) of the checkpoints
-        // they are live at
-        int32_t lo[PPL], hi[PPL];
-#pragma unroll
-        for (int q = 0; q < PPL; ++q) {
-          int32_t x = 0, y = 0;
-          if (own(q))
-            for (int32_t j = 0; j < np; ++j) {
-              x += pfa[j] < pf[q] ? 1 : 0;
-              y += pfa[j] <= pb[q] ? 1 : 0;
-            }
-          lo[q] = x;
-          hi[q] = y;
-        }
-        int64_t *ps = lps;                   // [np + 1] prefix sums of the multipliers
-        int64_t *dif = lps + (mp + 1);       // [np + 1] memory differences, then g
-        int64_t *lam = lps + 2 * (mp + 1);   // [np] multipliers, by forward order
-        for (int32_t d = lane; d < np; d += 64) lam[d] = 0;
-        lds_sync_wave();
-        for (int t = 0; t < kMemoptLagrIters; ++t) {
-          // prefix sums of the multipliers; the difference array cleared
-          int64_t carry = 0;
-#pragma unroll
-          for (int q = 0; q < PPL; ++q) {
-            if (64 * q >= np) continue;
-            const int32_t d = lane + 64 * q;
-            const int64_t v = wave_scan64(d < np ? lam[d] : 0) + carry;
-            if (d < np) ps[d + 1] = v;
-            if (d <= np) dif[d] = 0;
-            carry = shfl64(v, 63);
-          }
-          if (lane == 0) ps[0] = 0;
-          if (np % 64 == 0 && lane == 0) dif[np] = 0;
-          lds_sync_wave();
-          int64_t part = 0;
+      for (int32_t q0 = 0; q0 < nq; ++q0) {
+        const int32_t own = gl + G * q0;
+        uint64_t todo = R::ballot(own < np && cur[own < np ? own : 0] > 0, lane);
+        while (todo) {
+          const int32_t i = G * q0 + __builtin_ctzll(todo);
+          todo &= todo - 1;
+          const uint32_t slo = plo[i], sln = pln[i];
+          int32_t mx = 0;
 #pragma unroll
           for (int q = 0; q < PPL; ++q)
-            if (own(q)) {
-              const int32_t i = lane + 64 * q;
-              const int64_t price = hi[q] > lo[q] ? ps[hi[q]] - ps[lo[q]] : 0;
-              int64_t bv = 0;
-              int32_t bm = 0;
-              for (int32_t j = 0; has(i, j); ++j) {
-                const int64_t v = (ct[i * kMemoptMaxCands + j] << F) +
-                                  int64_t(cmem[i * kMemoptMaxCands + j]) * price;
-                if (j == 0 || v < bv) {
+            if (q < nq) mx = covers(P[q], slo, sln) ? max(mx, load[q]) : mx;
+          const uint32_t top = R::max32(uint32_t(mx));
+          const int32_t ci = cur[i];
+          const int32_t mc = tm[i * C + ci], mj = tm[i * C + (gl & (C - 1))];
+          // (a pair whose backward comes before its forward is live nowhere)
+          const uint64_t fit = R::ballot(
+              gl < ci && (sln == 0 || uint32_t(mj) <= uint32_t(cap) - top + uint32_t(mc)), lane);
+          if (fit) {
+            const int32_t nj = __builtin_ctzll(fit);
+            const int32_t add = tm[i * C + nj] - mc;
+#pragma unroll
+            for (int q = 0; q < PPL; ++q)
+              if (q < nq) load[q] += covers(P[q], slo, sln) ? add : 0;
+            cur[i] = uint8_t(nj);
+            changed = true;
+          }
+        }
+      }
+      wave_lds_order();
+    }
+  }
+  int32_t peak = 0;
+#pragma unroll
+  for (int q = 0; q < PPL; ++q) peak = max(peak, load[q]);
+  peak = int32_t(R::max32(uint32_t(peak)));
+  // the incumbent's time, and the least any choice takes
+  int64_t inc = 0, fastest = 0;
+  for (int32_t i = gl; i < np; i += G) {
+    inc += tt[i * C + cur[i]];
+    fastest += tt[i * C];
+  }
+  inc = R::sum64(inc);
+  if (ok && moved) {
+    // ---- step 3: branch and bound, pairs by forward position
+    fastest = R::sum64(fastest);
+    int64_t cut = gap_bound(inc);
+    bool proven = true;
+    // every placement of the first pair is dropped or cut when the fastest
+    // times alone reach the bound (its candidates fit any sensible budget)
+    if (fastest < cut || a.bb_nodes < C) {
+      // by forward order: the pair; the pairs whose live range ends before
+      // the checkpoint (a list); by pair: the list's next, the candidate and
+      // the live memory of the current placement
+      int32_t *head = reinterpret_cast<int32_t *>(ws);          // [np + 1]
+      int32_t *pmem = head + mp + 1;                            // [np]
+      uint16_t *ord = reinterpret_cast<uint16_t *>(pmem + mp);  // [np]
+      uint16_t *nxt = ord + mp;                                 // [np]
+      uint8_t *chp = reinterpret_cast<uint8_t *>(nxt + mp);     // [np]
+      for (int32_t d = gl; d <= np; d += G) head[d] = -1;
+      wave_lds_order();
+      for (int32_t i = gl; i < np; i += G) {
+        ord[plo[i]] = uint16_t(i);
+        if (pln[i]) nxt[i] = uint16_t(atomicExch(head + plo[i] + pln[i], i));
+      }
+      wave_lds_order();
+      bool better = false;
+      uint32_t seen = 0;
+      int32_t d = 0, c0 = 0;          // depth, first candidate to try there
+      int32_t held = 0;               // load of the placed pairs at depth d's checkpoint
+      int64_t f = 0, rest = fastest;  // placed time; fastest time of depths d and on
+      for (;;) {
+        const int32_t i = ord[d];
+        const int32_t n = tn[i];
+        const int32_t mj = pln[i] ? tm[i * C + (gl & (C - 1))] : 0;
+        const int64_t t0 = tt[i * C];
+        const uint64_t fit = R::ballot(gl >= c0 && gl < n && mj <= cap - held, lane);
+        const int32_t cc = fit ? __builtin_ctzll(fit) : n - 1;
+        seen += uint32_t(cc + 1 - c0);   // placements looked at (none when c0 == n)
+        if (seen > uint32_t(a.bb_nodes)) {
+          proven = false;
+          break;
+        }
+        bool back = !fit;
+        if (fit) {
+          const int64_t ft = f + tt[i * C + cc];
+          if (ft + rest - t0 >= cut) {
+            back = true;                 // cut, with the slower ones
+          } else {
+            const int32_t pm = pln[i] ? tm[i * C + cc] : 0;
+            chp[i] = uint8_t(cc);
+            pmem[i] = pm;
+            if (d == np - 1) {           // every pair placed, below the incumbent
+              inc = ft;
+              cut = gap_bound(inc);
+              better = true;
+              wave_lds_order();
+              for (int32_t k = gl; k < np; k += G) cur[k] = chp[k];
+              wave_lds_order();
+              c0 = cc + 1;
+            } else {
+              f = ft;
+              rest -= t0;
+              held += pm;
+              ++d;
+              c0 = 0;
+              for (int32_t k = head[d]; k != -1;) {
+                held -= pmem[k];
+                const int32_t k1 = nxt[k];
+                k = k1 == 0xffff ? -1 : k1;
+              }
+            }
+          }
+        }
+        if (back) {
+          if (d == 0) break;
+          for (int32_t k = head[d]; k != -1;) {
+            held += pmem[k];
+            const int32_t k1 = nxt[k];
+            k = k1 == 0xffff ? -1 : k1;
+          }
+          --d;
+          const int32_t k = ord[d], ck = chp[k];
+          held -= pmem[k];
+          f -= tt[k * C + ck];
+          rest += tt[k * C];
+          c0 = ck + 1;
+        }
+      }
+      status = proven ? 1 : 3;
+      if (better) {                      // the new choice's loads
+        wave_lds_order();
+        for (int32_t k = gl; k <= np; k += G) acc[k] = 0;
+        wave_lds_order();
+        for (int32_t k = gl; k < np; k += G)
+          if (pln[k]) {
+            const int32_t m = tm[k * C + cur[k]];
+            atomicAdd(acc + plo[k], m);
+            atomicAdd(acc + plo[k] + pln[k], -m);
+          }
+        wave_lds_order();
+        peak = int32_t(R::max32(uint32_t(scan_loads())));
+      }
+      if (!proven) {
+        // ---- step 4: the Lagrangian certificate.  Multipliers l_k >= 0
+        // (units of 2^-F time per memory unit), one per checkpoint k (pair
+        // k's forward start).  Each step: a pair's price is the sum of the
+        // multipliers of the checkpoints it is live at; it takes its cheapest
+        // candidate under t * 2^F + m * price (the first on ties); the bound
+        // (times 2^F) is the sum of those values less cap * sum_k l_k, and
+        // proves the incumbent once 1.05 times it reaches the incumbent;
+        // otherwise each multiplier moves by g_k * step / 2^b, b the bits of
+        // max |g| (the magnitude shifted down, the sign kept; kept in [0,
+        // lmax]), g_k being the memory of the taken candidates live at
+        // checkpoint k less the cap, step = s0 / 2^(t / 24).  F = min(20, 60 -
+        // bits(np * tmax)), lmax = 2^60 / 2^bits(np^2 * max(1, mmax, cap)) and
+        // s0 = half the largest (dt << F) / 2^(bits(dm) - 1) over the moves
+        // from each pair's fastest candidate (at least 1, at most lmax) keep
+        // every value below 2^61, with no division.  A pair is live at a run
+        // of checkpoints in forward order, so both sums are differences of
+        // prefix sums over them.  Integer arithmetic: the same values as any
+        // other order of summation.
+        int64_t tmx = 0, mmx = 0, s0 = 0;
+        for (int32_t i = gl; i < np; i += G) {          // candidates ascend in time
+          tmx = max(tmx, tt[i * C + tn[i] - 1]);
+          mmx = max(mmx, int64_t(tm[i * C]));
+        }
+        tmx = R::max64(tmx);
+        mmx = R::max64(mmx);
+        const int F = min(kMemoptLagrF, kMemoptLagrLimitBits - bits64(int64_t(np) * max(tmx, int64_t(1))));
+        const int lb = bits64(int64_t(np) * np * max(max(int64_t(1), mmx), int64_t(cap)));
+        const int64_t lmax = lb <= kMemoptLagrLimitBits ? int64_t(1) << (kMemoptLagrLimitBits - lb) : 0;
+        if (F >= 0 && lmax > 0) {
+          for (int32_t i = gl; i < np; i += G)
+            for (int32_t j = 1; j < tn[i]; ++j)
+              s0 = max(s0, ((tt[i * C + j] - tt[i * C]) << F) >>
+                               (bits64(int64_t(tm[i * C]) - tm[i * C + j]) - 1));
+          s0 = min(lmax, max(int64_t(1), R::max64(s0) >> 1));
+          const int64_t goal = gap_bound(inc << F);
+          // prefix sums of the multipliers (multiplier d is ps[d + 1] - ps[d])
+          // and memory differences, [np + 1] each
+          int64_t *ps = reinterpret_cast<int64_t *>(ws);
+          int32_t *dif = reinterpret_cast<int32_t *>(ps + (mp + 1));
+          wave_lds_order();
+          for (int32_t d = gl; d <= np; d += G) {
+            ps[d] = 0;
+            dif[d] = 0;
+          }
+          for (int t = 0; t < kMemoptLagrIters; ++t) {
+            wave_lds_order();
+            int64_t part = 0;
+            for (int32_t i = gl; i < np; i += G) {
+              const int32_t lo = plo[i], len = pln[i];
+              const int64_t price = ps[lo + len] - ps[lo];
+              int64_t bv = (tt[i * C] << F) + int64_t(tm[i * C]) * price;
+              int32_t bm = tm[i * C];
+              const int32_t n = tn[i];
+              for (int32_t j = 1; j < n; ++j) {
+                const int32_t m = tm[i * C + j];
+                const int64_t v = (tt[i * C + j] << F) + int64_t(m) * price;
+                if (v < bv) {
                   bv = v;
-                  bm = cmem[i * kMemoptMaxCands + j];
+                  bm = m;
                 }
               }
               part += bv;
-              if (hi[q] > lo[q]) {
-                atomicAdd(reinterpret_cast<unsigned long long *>(dif + lo[q]),
-                          static_cast<unsigned long long>(int64_t(bm)));
-                atomicAdd(reinterpret_cast<unsigned long long *>(dif + hi[q]),
-                          static_cast<unsigned long long>(-int64_t(bm)));
+              if (len) {
+                atomicAdd(dif + lo, bm);
+                atomicAdd(dif + lo + len, -bm);
               }
             }
-          const int64_t val = wave_sum64(part) - int64_t(cap) * carry;
-          if (__int128(105) * val >= __int128(100) * (__int128(inc) << F)) {
-            status = 1;
-            break;
-          }
-          lds_sync_wave();
-          // g at every depth: the running sum of the differences less the
-          // cap, written over the differences
-          int64_t gabs = 0, run = 0;
-#pragma unroll
-          for (int q = 0; q < PPL; ++q) {
-            if (64 * q >= np) continue;
-            const int32_t d = lane + 64 * q;
-            const int64_t v = wave_scan64(d < np ? dif[d] : 0) + run;
-            run = shfl64(v, 63);
-            const int64_t g = v - int64_t(cap);
-            if (d < np) {
-              dif[d] = g;
-              gabs = max(gabs, g < 0 ? -g : g);
+            if (R::sum64(part) - int64_t(cap) * ps[np] >= goal) {
+              status = 1;
+              break;
             }
+            wave_lds_order();
+            // the memory live at every checkpoint, written over its differences
+            // (32 bits hold it: the fastest candidates' memories of a rank do)
+            uint32_t gabs = 0;
+            int32_t run = 0;
+            for (int32_t q = 0; q < nq; ++q) {
+              const int32_t d = gl + G * q;
+              const int32_t v = R::scan32(d < np ? dif[d] : 0, lane) + run;
+              run = R::last32(v, lane);
+              if (d < np) {
+                dif[d] = v;
+                gabs = max(gabs, uint32_t(abs(v - cap)));
+              }
+            }
+            const int sft = bits64(R::max32(gabs));
+            if (sft == 0) break;
+            // the multipliers' move and their new prefix sums; the
+            // differences cleared
+            const int64_t step = s0 >> (t / kMemoptLagrHalve);
+            int64_t carry = 0, old = 0;      // new and old prefix sum at the chunk's start
+            for (int32_t q = 0; q < nq; ++q) {
+              const int32_t d = gl + G * q;
+              int64_t lam = 0, at = 0;
+              if (d < np) {
+                at = ps[d + 1];
+                lam = at - (gl == 0 ? old : ps[d]);
+                const int64_t g = dif[d] - cap;
+                const int64_t mv = ((g < 0 ? -g : g) * step) >> sft;
+                lam = min(lmax, max(int64_t(0), lam + (g < 0 ? -mv : mv)));
+              }
+              old = R::last64(at, lane);
+              const int64_t v = R::scan64(lam, lane) + carry;
+              carry = R::last64(v, lane);
+              wave_lds_order();
+              if (d < np) ps[d + 1] = v;
+              if (d <= np) dif[d] = 0;
+            }
+            if (nq * G == np && gl == 0) dif[np] = 0;
           }
-          const int sh = bits64(wave_max64(gabs));
-          if (sh == 0) break;
-          const int64_t step = s0 >> (t / kMemoptLagrHalve);
-          for (int32_t d = lane; d < np; d += 64) {
-            const int64_t g = dif[d];
-            const int64_t mv = ((g < 0 ? -g : g) * step) >> sh;
-            lam[d] = min(lmax, max(int64_t(0), lam[d] + (g < 0 ? -mv : mv)));
-          }
-          lds_sync_wave();   // (the next step rewrites the arrays)
         }
       }
     }
   }
-  int64_t total = 0;
-  uint32_t pk = 0x80000000u;                        // image of load 0
-#pragma unroll
-  for (int q = 0; q < PPL; ++q) {
-    const int32_t i = lane + 64 * q;
-    if (i < np) {
-      total += ct[i * kMemoptMaxCands + cur[q]];
-      pk = max(pk, uint32_t(load[q]) ^ 0x80000000u);
-      if (a.out_choice) a.out_choice[c * a.n_pairs + pbase + i] = uint8_t(cur[q]);
-    }
-  }
-  pk = wave_reduce63<true>(pk);
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1)
-    total += (int64_t(__shfl_xor(int(total >> 32), s)) << 32) |
-             uint32_t(__shfl_xor(int(uint32_t(total)), s));
-  if (lane == 0) write_out(a, o, total, int32_t(pk ^ 0x80000000u), status);
+  if (a.out_choice)
+    for (int32_t i = gl; i < np; i += G) a.out_choice[c * a.n_pairs + pbase + i] = cur[i];
+  if (gl == 0) write_out(a, o, inc, peak, status);
 }
 
 }  // namespace
 
-size_t memopt_wave_lds(int32_t max_pairs, int waves_per_block) {
-  // the rank's tables and the waves' positions and choices, then (8-byte
-  // aligned) each wave's two certificate arrays of max_pairs + 1 words
-  const size_t head = size_t(max_pairs) * (68 + 7 * size_t(waves_per_block));
-  return (head + 7) / 8 * 8 + size_t(waves_per_block) * 24 * (size_t(max_pairs) + 1);
+int64_t memopt_group_lds(int32_t max_pairs, int groups_per_block) {
+  return group_table_bytes(max_pairs) + groups_per_block * group_problem_bytes(max_pairs);
 }
 
-hipError_t launch_memopt_wave(int ppl, int waves_per_block, hipStream_t s, const MemoptArgs &a) {
-  const int64_t bx = (a.n_cand + waves_per_block - 1) / waves_per_block;
-  const size_t lds = memopt_wave_lds(a.max_pairs, waves_per_block);
-  const dim3 grid{unsigned(bx), unsigned(a.P)}, block{unsigned(64 * waves_per_block)};
-  switch (ppl) {
-    case 1: hipLaunchKernelGGL(memopt_wave_kernel<1>, grid, block, lds, s, a); break;
-    case 2: hipLaunchKernelGGL(memopt_wave_kernel<2>, grid, block, lds, s, a); break;
-    case 4: hipLaunchKernelGGL(memopt_wave_kernel<4>, grid, block, lds, s, a); break;
-    case 8: hipLaunchKernelGGL(memopt_wave_kernel<8>, grid, block, lds, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+const void *memopt_group_ptr(int lanes, int32_t max_pairs) {
+  auto ptr = [](void (*k)(MemoptArgs)) { return reinterpret_cast<const void *>(k); };
+  const int n = (max_pairs + lanes - 1) / lanes;
+  if (lanes == 16)
+    return n <= 2   ? ptr(memopt_group_kernel<16, 2>)
+           : n <= 4 ? ptr(memopt_group_kernel<16, 4>)
+           : n <= 6 ? ptr(memopt_group_kernel<16, 6>)
+                    : nullptr;
+  return n <= 1   ? ptr(memopt_group_kernel<64, 1>)
+         : n <= 2 ? ptr(memopt_group_kernel<64, 2>)
+         : n <= 4 ? ptr(memopt_group_kernel<64, 4>)
+         : n <= 8 ? ptr(memopt_group_kernel<64, 8>)
+                  : nullptr;
+}
+
+hipError_t launch_memopt_group(int lanes, int waves_per_block, hipStream_t s, const MemoptArgs &a) {
+  const void *k = memopt_group_ptr(lanes, a.max_pairs);
+  if (!k) return hipErrorInvalidValue;
+  const int per = waves_per_block * 64 / lanes;
+  const dim3 grid{unsigned((a.n_cand + per - 1) / per), unsigned(a.P)};
+  MemoptArgs arg = a;
+  void *args[] = {&arg};
+  return hipLaunchKernel(k, grid, dim3(unsigned(64 * waves_per_block)), args,
+                         size_t(memopt_group_lds(a.max_pairs, per)), s);
 }
 
 hipError_t launch_memopt(int threads_per_block, hipStream_t s, const MemoptArgs &a) {
