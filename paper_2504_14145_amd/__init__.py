@@ -275,7 +275,7 @@ def configure_greedy(h, n_groups: int, op_group) -> int:
 
 
 def set_greedy_inbox(h, k: int) -> int:
-    """Fix the first launch's inbox size (power of two, 1..256); 0: adaptive."""
+    """Fix the inbox size (power of two, 1..256); 0: adaptive."""
     return load().dip_sim_set_greedy_inbox(h, int(k))
 
 
