@@ -546,13 +546,17 @@ int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, cons
 }
 
 // The passes' shapes (the configured pools, then 16 and 32 slots for the
-// candidates whose pools filled); sim_costs_ok false when the first does not
-// fit.
+// candidates whose pools filled) and the direct kernel's, for tables that hold
+// the current costs; sim_costs_ok false when they do not (costs outside the
+// records; an earlier upload's tables then lie in the buffers, or none) or
+// when the first shape does not fit.
 int sim_plan(dip_sim *h) {
   h->sim_costs_ok = false;
+  h->dir_ok = false;
   h->sel_planned = false;
   h->sim2_ok = false;
   h->sim3_ok = false;
+  if (!h->sim_tables_ok) return DIP_OK;
   h->sim_state_base = int64_t(h->sim_tab_vec) * 16;
   if (!sim_shape(h, h->pool_slots, h->forced_variant == 9 ? h->forced_wpb : 0, &h->sim_wpb,
                  &h->sim_max_blocks, &h->sim_lds))
@@ -561,6 +565,7 @@ int sim_plan(dip_sim *h) {
   if (h->pool_slots < 16)
     h->sim2_ok = sim_shape(h, 16, 0, &h->sim2_wpb, &h->sim2_max_blocks, &h->sim2_lds);
   h->sim3_ok = sim_shape(h, 32, 0, &h->sim3_wpb, &h->sim3_max_blocks, &h->sim3_lds);
+  h->dir_ok = h->dir_tables_ok && direct_shape(h, false);
   return DIP_OK;
 }
 
@@ -593,8 +598,10 @@ int choose_config(dip_sim *h) {
     if (h->costs_set) {
       rc = sim_plan(h);
       if (rc != DIP_OK) return rc;
-      // a forced shape the current costs or the LDS do not allow
-      if (h->forced_variant == 9 && !h->sim_costs_ok) return DIP_E_UNSUPPORTED;
+      // a forced shape the LDS does not allow (costs outside the records run
+      // variant 8, as they do when they come after the forced variant)
+      if (h->forced_variant == 9 && h->sim_tables_ok && !h->sim_costs_ok)
+        return DIP_E_UNSUPPORTED;
     }
   }
   return DIP_OK;

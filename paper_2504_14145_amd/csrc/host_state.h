@@ -91,7 +91,8 @@ struct dip_sim {
   int pool_slots = 8, forced_pool_slots = 0;   // slots per rank pool (variants 8, 9)
   // simulation kernel (variant 9)
   bool sim_ok = false;                 // topology fits it
-  bool sim_costs_ok = false;           // the last costs fit its records
+  bool sim_tables_ok = false;          // its tables hold the current costs
+  bool sim_costs_ok = false;           // ... and a launch shape fits: it runs these costs
   bool sim_paged = false;              // records stored as deduplicated pages
   int32_t sim_n_extra = 0;             // extra-edge words (edges of multi-predecessor ops)
   int64_t sim_tab_cap = 0;             // bytes of d_sim_tab (and of d_dir_tab)
@@ -109,7 +110,8 @@ struct dip_sim {
   int64_t *d_retry2 = nullptr;         // candidates the second pass could not hold
   // direct kernel: the same tables with its edge words; plain and re-timed
   bool dir_fits = false;               // one wave's end times fit a block's LDS
-  bool dir_ok = false;                 // its tables hold the current costs and fit
+  bool dir_tables_ok = false;          // its tables hold the current costs
+  bool dir_ok = false;                 // ... and fit, as the simulation kernel's do
   bool dir_paged = false;
   int32_t dir_tab_vec = 0;
   uint32_t dir_off_pmap = 0, dir_off_extra = 0;

@@ -181,8 +181,8 @@ static bool table_image(const dip_sim *h, const dip_costs *c, const int32_t *bus
 // They are staged; *end moves to the end of what is to be copied.
 int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const StageLayout &L,
                       int64_t *end) {
-  h->sim_costs_ok = false;
-  h->dir_ok = false;
+  h->sim_tables_ok = h->sim_costs_ok = false;
+  h->dir_tables_ok = h->dir_ok = false;
   for (int32_t g = 0; g < h->N; ++g)
     if (uint32_t(c->op_cost[g]) > kSimCostMax) return DIP_OK;
   for (int32_t e = 0; e < h->E; ++e)
@@ -219,6 +219,7 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
   if (!table_image(h, c, busy, readers, dropped, edge_word, cap, h->h_stage + L.stab,
                    reinterpret_cast<int32_t *>(h->h_stage + L.slane), &T))
     return DIP_OK;
+  h->sim_tables_ok = true;
   h->sim_paged = T.paged;
   h->sim_off_pmap = T.off_pmap;
   h->sim_off_extra = T.off_extra;
@@ -228,17 +229,16 @@ int upload_sim_tables(dip_sim *h, const dip_costs *c, const int32_t *busy, const
       return (uint32_t(h->pred_op[k] - g) & 0x1ffffu) | (uint32_t(c->edge_comm[k]) << 17) |
              (last ? kSimLast : 0u);
     };
-    h->dir_ok = table_image(h, c, busy, readers, dropped, direct_word, cap, h->h_stage + L.dtab,
-                            reinterpret_cast<int32_t *>(h->h_stage + L.dlane), &D);
+    h->dir_tables_ok = table_image(h, c, busy, readers, dropped, direct_word, cap,
+                                   h->h_stage + L.dtab,
+                                   reinterpret_cast<int32_t *>(h->h_stage + L.dlane), &D);
     h->dir_paged = D.paged;
     h->dir_off_pmap = D.off_pmap;
     h->dir_off_extra = D.off_extra;
     h->dir_tab_vec = int32_t(D.bytes / 16);
   }
-  *end = h->dir_ok ? L.dtab + D.bytes : L.stab + T.bytes;
-  const int rc = sim_plan(h);
-  h->dir_ok = h->dir_ok && h->sim_costs_ok && direct_shape(h, false);
-  return rc;
+  *end = h->dir_tables_ok ? L.dtab + D.bytes : L.stab + T.bytes;
+  return sim_plan(h);
 }
 
 int upload_costs(dip_sim *h, const dip_costs *c, hipStream_t stream) {
