@@ -124,7 +124,7 @@ typedef struct {
   int32_t waves_per_block;
   int32_t lds_bytes;         /* dynamic LDS per block                            */
   int32_t max_blocks;        /* resident blocks the grid is capped at            */
-  int64_t scratch_bytes;     /* device scratch owned by the handle               */
+  int64_t scratch_bytes;     /* device working memory owned by the handle        */
   int32_t pool_slots;        /* variant 8: end-time slots per rank pool, else 0  */
   int32_t check_kernel;      /* variants 8, 9: 1 wave per candidate, 2 tiles,
                                 else 0                                         */
@@ -352,6 +352,9 @@ int dip_sim_rollouts_batch(dip_sim *h, int32_t n_leaves, const int32_t *depths,
  * (Sec. 5.3's multiple-choice knapsack); equal points once, by time.
  * bb_nodes bounds the branch and bound of dip_sim_memopt: the placements it
  * may examine per (schedule, rank), 0 for 512.
+ * Also allocates the working memory of dip_sim_evaluate_selected, which is kept
+ * until the next set-up or dip_sim_destroy: up to 1 GiB of device memory
+ * (counted in dip_sim_info.scratch_bytes), less where the device is short of it.
  * DIP_E_TOPO unless every slot has one forward and one backward on one rank;
  * DIP_E_RANGE for a negative entry, a candidate memory above 2^31 - 1, a
  * candidate time above 2^40, or fastest memories of a rank summing above
@@ -407,6 +410,11 @@ int dip_sim_memopt(dip_sim *h, const int16_t *orders, int64_t n_cand, int64_t *o
  * dip_sim_evaluate call.  Outputs and flags as dip_sim_evaluate's (the peak
  * and the cap flag from the chosen memories); a choice beyond a pair's
  * candidates makes its schedule invalid (DIP_FLAG_INVALID, outputs -1).
+ * Enqueued on stream, without allocating or freeing memory.  Calls on several
+ * streams or threads may share a handle: they use its working memory one after
+ * the other.  A call captured into a HIP graph runs a general kernel that needs
+ * none of that memory (end times in device scratch of the handle's only where a
+ * schedule's do not fit in LDS: replays must then not overlap other calls).
  * DIP_E_STATE before dip_sim_configure_memopt or before any costs,
  * DIP_E_RANGE when a re-timed backward could exceed 2^31 - 1 microseconds,
  * DIP_E_INVAL for null or misaligned pointers. */

@@ -74,6 +74,9 @@ void release_rollouts(dip_sim *h) {
 }
 
 void release_selected(dip_sim *h) {
+  if (h->sel_ev) (void)hipEventDestroy(h->sel_ev);
+  h->sel_ev = nullptr;
+  h->sel_used = false;
   if (h->d_sel_x) (void)hipFree(h->d_sel_x);
   if (h->d_sel_list) (void)hipFree(h->d_sel_list);
   if (h->d_sel_count) (void)hipFree(h->d_sel_count);
@@ -81,7 +84,7 @@ void release_selected(dip_sim *h) {
   h->d_sel_list = nullptr;
   h->d_sel_count = nullptr;
   h->sel_rows = 0;
-  h->sel_planned = false;
+  h->sel_ok = false;
 }
 
 void release_memopt(dip_sim *h) {
@@ -356,7 +359,8 @@ int dip_sim_get_info(const dip_sim *h, dip_sim_info *info) {
   info->waves_per_block = sim ? (h->sim_costs_ok ? h->sim_wpb : 0) : h->wpb;
   info->lds_bytes = int32_t(sim ? (h->sim_costs_ok ? h->sim_lds : 0) : h->lds_bytes);
   info->max_blocks = sim ? (h->sim_costs_ok ? h->sim_max_blocks : 0) : h->max_blocks;
-  info->scratch_bytes = h->scratch_gen_bytes + h->scratch_fb_bytes + h->retry_cap * 8;
+  info->scratch_bytes = h->scratch_gen_bytes + h->scratch_fb_bytes + h->retry_cap * (h->sim_ok ? 16 : 8) +
+                        h->sel_rows * (4 * h->stride + 16);
   info->pool_slots = v >= 8 ? h->pool_slots : 0;
   info->check_kernel = v >= 8 ? check_kind(h) : 0;
   info->greedy_inbox = h->gr_ok ? (h->gr_direct ? -1 : h->gr_K) : 0;

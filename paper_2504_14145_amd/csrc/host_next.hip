@@ -567,6 +567,29 @@ static void plan_memopt(dip_sim *h) {
   }
 }
 
+// The re-timed simulation's working rows: extra costs and two retry lists for
+// up to 131,072 schedules within a GiB of extra costs, which is several
+// resident generations (a larger batch goes through them in steps; with a
+// quarter of that, 4,000 schedules of 34,896 ops took 8.3 ms instead of 4.4,
+// 100,000 of 680 ops 1.41 instead of 1.25).  Less where the memory is short;
+// without any, the general kernel runs.
+static void alloc_selected(dip_sim *h) {
+  int64_t rows = std::max<int64_t>(
+      1, std::min<int64_t>(131072, (int64_t(1) << 30) / (4 * h->stride)));
+  for (;; rows /= 2) {
+    if (hipMalloc(&h->d_sel_x, size_t(rows) * size_t(h->stride) * 4) == hipSuccess &&
+        hipMalloc(&h->d_sel_list, size_t(rows) * 16) == hipSuccess &&
+        hipMalloc(&h->d_sel_count, kRetryCounters * 4) == hipSuccess &&
+        hipEventCreateWithFlags(&h->sel_ev, hipEventDisableTiming) == hipSuccess) {
+      h->sel_rows = rows;
+      return;
+    }
+    (void)hipGetLastError();
+    release_selected(h);
+    if (rows < 64) return;
+  }
+}
+
 int dip_sim_configure_memopt(dip_sim *h, const int32_t *slot_layers, const int64_t *layer_time,
                              const int64_t *layer_mem, int32_t n_strategies, int32_t n_candidates,
                              int32_t bb_nodes) {
@@ -715,6 +738,8 @@ int dip_sim_configure_memopt(dip_sim *h, const int32_t *slot_layers, const int64
   for (int64_t x : pair_extra) h->mo_max_extra = std::max(h->mo_max_extra, x);
   plan_memopt(h);
   h->mo_ok = true;
+  if (h->sim_ok) alloc_selected(h);
+  plan_selected(h);
   return DIP_OK;
 }
 
@@ -768,62 +793,16 @@ int dip_sim_memopt(dip_sim *h, const int16_t *orders, int64_t n_cand, int64_t *o
   return DIP_OK;
 }
 
-// The re-timed simulation's launch shapes for the current costs, and whether
-// its times stay within int32 whatever is selected.
-static void plan_selected(dip_sim *h) {
-  h->sel_planned = true;
-  h->dir_wpb[1] = 0;
-  if (h->dir_ok) (void)direct_shape(h, true);
-  int64_t total = 0;
-  for (int32_t x : h->last_cost) total += x;
-  for (int32_t x : h->last_comm) total += x;
-  for (int64_t x : h->mo_pair_extra) total += x;
-  h->sel_total = total;
-  h->sel_ok = h->variant == 9 && h->sim_costs_ok && h->forced_wpb == 0 && total <= INT32_MAX &&
-              sim_shape(h, 8, 0, &h->sel_wpb[0], &h->sel_max_blocks[0], &h->sel_lds[0], true) &&
-              sim_shape(h, 32, 0, &h->sel_wpb[1], &h->sel_max_blocks[1], &h->sel_lds[1], true);
-}
-
-// Rows of extra costs a call works through at once: a GiB of them.
-static int64_t selected_rows(const dip_sim *h, int64_t n_cand) {
-  return std::min<int64_t>(n_cand, std::max<int64_t>(1, (int64_t(1) << 30) / (4 * h->stride)));
-}
-
-// The buffers for that many rows; false where they are not there and cannot
-// be had (a capture allows no allocation).
-static bool ensure_selected(dip_sim *h, int64_t rows, hipStream_t stream) {
-  if (h->sel_rows >= rows && h->d_sel_count) return true;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
-  const bool planned = h->sel_planned;
-  release_selected(h);
-  h->sel_planned = planned;
-  if (hipMalloc(&h->d_sel_x, size_t(rows) * size_t(h->stride) * 4) != hipSuccess ||
-      hipMalloc(&h->d_sel_list, size_t(rows) * 16) != hipSuccess ||
-      hipMalloc(&h->d_sel_count, kRetryCounters * 4) != hipSuccess) {
-    (void)hipGetLastError();
-    release_selected(h);
-    h->sel_planned = planned;
-    return false;
-  }
-  h->sel_rows = rows;
-  return true;
-}
-
 // The re-timed evaluate through the simulation kernel: check (with each op's
 // extra cost along the order), own-rank order, then the direct kernel where
 // every schedule is resident with it, else 8-slot pools and the direct kernel
 // for those that filled (32-slot pools and the general kernel where it does
 // not fit).
-static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t stream) {
+static int launch_selected(dip_sim *h, const GeneralArgs &all, hipStream_t stream) {
   int32_t max_nr = 0;
   for (int32_t n : h->n_ops) max_nr = std::max(max_nr, n);
-  const int64_t step = selected_rows(h, all.n_cand);
-  for (int64_t c0 = 0; c0 < all.n_cand; c0 += step) {
-    const int64_t n = std::min(step, all.n_cand - c0);
+  for (int64_t c0 = 0; c0 < all.n_cand; c0 += h->sel_rows) {
+    const int64_t n = std::min(h->sel_rows, all.n_cand - c0);
     const int16_t *orders = all.orders + c0 * h->stride;
     int32_t *ms = all.out_ms + c0, *bub = all.out_bub + c0 * h->P, *peak = all.out_peak + c0 * h->P;
     uint8_t *flags = all.out_flags + c0;
@@ -911,15 +890,39 @@ static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t
     f.out_peak = peak;
     f.out_flags = flags;
     f.choice = choice;
-    f.gends = static_cast<int32_t *>(h->d_scratch_fb);
-    f.wpb = 1;
     f.list = a.retry;
     f.list_count = a.retry_count;
     f.tab_bytes = f.ord_bytes = 0;
     f.end_bytes = 0;
-    DIP_HIP(launch_general(h->fb_variant, h->fb_blocks, 1, size_t(h->fb_lds), stream, f));
+    // end times in LDS where a wave's fit; else in the general configuration's
+    // scratch (which then is variant 4 too), as evaluate's own leftovers may
+    // be using theirs on another stream
+    const bool in_lds = h->fb_variant == 3;
+    f.wpb = in_lds ? 1 : h->gen_wpb;
+    DIP_HIP(launch_general(h->fb_variant, in_lds ? h->fb_blocks : h->gen_max_blocks, f.wpb,
+                           size_t(in_lds ? h->fb_lds : h->gen_lds), stream, f));
   }
   return DIP_OK;
+}
+
+// The same behind the calls that used the rows before it.
+static int evaluate_selected_sim(dip_sim *h, const GeneralArgs &all, hipStream_t stream) {
+  std::lock_guard<std::mutex> lock(h->sel_mu);
+  if (h->sel_used && stream != h->sel_stream) DIP_HIP(hipStreamWaitEvent(stream, h->sel_ev, 0));
+  const int rc = launch_selected(h, all, stream);
+  h->sel_used = true;
+  h->sel_stream = stream;
+  DIP_HIP(hipEventRecord(h->sel_ev, stream));
+  return rc;
+}
+
+// whether a captured graph takes the stream's work (or that cannot be told)
+static bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone)
+    return false;
+  (void)hipGetLastError();
+  return true;
 }
 
 int dip_sim_evaluate_selected(dip_sim *h, const int16_t *orders, const uint8_t *choice,
@@ -968,13 +971,12 @@ int dip_sim_evaluate_selected(dip_sim *h, const int16_t *orders, const uint8_t *
   a.cand_key = h->d_mo_key;
   // through the simulation kernel where it runs these costs and the times of
   // any selection fit its 32 bits (the general kernel below took 2.35 ms for
-  // 32,768 schedules on 8 ranks and 3.7 ms for 1,024 on 16 x 2 lanes)
-  if (!h->sel_planned) plan_selected(h);
-  if (h->sel_ok && h->variant == 9 && h->sim_costs_ok &&
-      ensure_selected(h, selected_rows(h, n_cand), static_cast<hipStream_t>(stream))) {
-    (void)hipGetLastError();
+  // 32,768 schedules on 8 ranks and 3.7 ms for 1,024 on 16 x 2 lanes).  Not
+  // under capture: a graph's replays come at any time beside the calls that
+  // share the working rows, and the general kernel needs none.
+  (void)hipGetLastError();
+  if (h->sel_ok && h->variant == 9 && !capturing(static_cast<hipStream_t>(stream)))
     return evaluate_selected_sim(h, a, static_cast<hipStream_t>(stream));
-  }
   const GenBytes b = general_bytes(h, h->gen_variant);
   a.tab_bytes = uint32_t(b.tab);
   a.ord_bytes = uint32_t(b.ord);

@@ -545,6 +545,23 @@ int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, cons
   return DIP_OK;
 }
 
+// The re-timed simulation's launch shapes for the current costs and memory
+// selection, and whether its times stay within int32 whatever is selected.
+// Planned with the costs, or with the selection when that comes later.
+void plan_selected(dip_sim *h) {
+  h->sel_ok = false;
+  h->dir_wpb[1] = 0;
+  if (!h->mo_ok || !h->sim_costs_ok || h->forced_wpb != 0 || h->sel_rows == 0) return;
+  int64_t total = 0;
+  for (int32_t x : h->last_cost) total += x;
+  for (int32_t x : h->last_comm) total += x;
+  for (int64_t x : h->mo_pair_extra) total += x;
+  if (total > INT32_MAX) return;
+  if (h->dir_ok) (void)direct_shape(h, true);
+  h->sel_ok = sim_shape(h, 8, 0, &h->sel_wpb[0], &h->sel_max_blocks[0], &h->sel_lds[0], true) &&
+              sim_shape(h, 32, 0, &h->sel_wpb[1], &h->sel_max_blocks[1], &h->sel_lds[1], true);
+}
+
 // The passes' shapes (the configured pools, then 16 and 32 slots for the
 // candidates whose pools filled) and the direct kernel's, for tables that hold
 // the current costs; sim_costs_ok false when they do not (costs outside the
@@ -553,7 +570,7 @@ int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, cons
 int sim_plan(dip_sim *h) {
   h->sim_costs_ok = false;
   h->dir_ok = false;
-  h->sel_planned = false;
+  h->sel_ok = false;
   h->sim2_ok = false;
   h->sim3_ok = false;
   if (!h->sim_tables_ok) return DIP_OK;
@@ -566,6 +583,7 @@ int sim_plan(dip_sim *h) {
     h->sim2_ok = sim_shape(h, 16, 0, &h->sim2_wpb, &h->sim2_max_blocks, &h->sim2_lds);
   h->sim3_ok = sim_shape(h, 32, 0, &h->sim3_wpb, &h->sim3_max_blocks, &h->sim3_lds);
   h->dir_ok = h->dir_tables_ok && direct_shape(h, false);
+  plan_selected(h);
   return DIP_OK;
 }
 

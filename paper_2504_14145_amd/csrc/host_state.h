@@ -119,15 +119,20 @@ struct dip_sim {
   int4 *d_dir_lane = nullptr;
   int dir_wpb[2] = {0, 0}, dir_max_blocks[2] = {0, 0};
   // re-timed simulation of a memory selection: 8-slot pools, then 32
-  bool sel_planned = false;            // the shapes below are the current costs'
-  bool sel_ok = false;
+  bool sel_ok = false;                 // planned for the current costs and selection, and fits
   int sel_wpb[2] = {1, 1}, sel_max_blocks[2] = {1, 1};
   int64_t sel_lds[2] = {0, 0};
-  int64_t sel_total = 0;               // op costs, latencies and largest extra times together
+  // its working rows, allocated with the selection's tables and kept with
+  // them: a call works through a larger batch in steps of sel_rows.  Eager
+  // calls share them one after the other, whatever their streams and threads.
   int32_t *d_sel_x = nullptr;          // [sel_rows][stride] extra costs
   int64_t *d_sel_list = nullptr;       // two retry lists of sel_rows
   uint32_t *d_sel_count = nullptr;     // [kRetryCounters]
-  int64_t sel_rows = 0;
+  int64_t sel_rows = 0;                // 0: none could be had
+  std::mutex sel_mu;
+  hipEvent_t sel_ev = nullptr;         // after the last call that used them
+  hipStream_t sel_stream = nullptr;    // on this stream
+  bool sel_used = false;
   // third pass over what the earlier ones could not hold, with 32-slot pools
   bool sim3_ok = false;
   int sim3_wpb = 1, sim3_max_blocks = 1;
@@ -337,6 +342,7 @@ void release_rollout_memopt(dip_sim *h);
 void release_rollouts(dip_sim *h);
 void release_memopt(dip_sim *h);
 void release_selected(dip_sim *h);
+void plan_selected(dip_sim *h);
 void release_greedy(dip_sim *h);
 void release(dip_sim *h);
 
