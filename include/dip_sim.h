@@ -134,7 +134,8 @@ typedef struct {
   int32_t greedy_lds_bytes;  /* dip_sim_greedy: LDS per block of its launch for
                                 large batches                                  */
   int64_t greedy_retry_ring_bytes; /* dip_sim_greedy: device memory held for the
-                                stages beyond the inboxes in LDS               */
+                                stages beyond the inboxes in LDS, where a rank's
+                                whole inboxes do not fit in LDS; else 0        */
 } dip_sim_info;
 
 /* Host-only checks, no device access: the same checks create / evaluate run
@@ -242,11 +243,13 @@ int dip_sim_argmin(dip_sim *h, const int32_t *makespan, const uint8_t *flags,
  * edges must be acyclic.  1 <= n_groups <= 65535, and at most 2048 groups of
  * either kind.  DIP_E_TOPO if a rule is broken, DIP_E_UNSUPPORTED if the
  * groups or the per-candidate tables do not fit the kernel.  Stages beyond
- * the inboxes in LDS lie in device memory of the handle's (up to 1 GiB, sized
- * by the candidates in flight at once; dip_sim_info.greedy_retry_ring_bytes),
- * allocated here where a rank's whole inboxes do not fit in LDS, else by the
- * first dip_sim_greedy call that needs more.  Replaces any
- * earlier grouping; the next dip_sim_greedy call must then pass costs. */
+ * the inboxes in LDS lie in device memory of the handle's, allocated here (up
+ * to 1 GiB for the candidates in flight at once, fewer where the device is
+ * short of memory; counted in dip_sim_info.scratch_bytes) and kept until the
+ * next grouping: dip_sim_greedy calls allocate none, and calls on one handle
+ * share it, so those whose kernels may overlap must be ordered by the caller.
+ * Replaces any earlier grouping; the next dip_sim_greedy call must then pass
+ * costs. */
 int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_group);
 
 /* Size of each rank's forward and backward inbox of stages that start later:

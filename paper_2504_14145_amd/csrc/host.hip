@@ -113,9 +113,8 @@ void release_greedy(dip_sim *h) {
   if (h->d_gr_ring) (void)hipFree(h->d_gr_ring);
   if (h->d_gr_joins) (void)hipFree(h->d_gr_joins);
   h->d_gr_ring = nullptr;
-  h->gr_ring_bytes = 0;
   h->d_gr_joins = nullptr;
-  h->gr_join_bytes = 0;
+  h->gr_slots = h->gr_mem_bytes = 0;
   h->h_gr_seen = nullptr;
   h->gr_seen_ev = nullptr;
   h->gr_seen_pending = false;
@@ -360,12 +359,12 @@ int dip_sim_get_info(const dip_sim *h, dip_sim_info *info) {
   info->lds_bytes = int32_t(sim ? (h->sim_costs_ok ? h->sim_lds : 0) : h->lds_bytes);
   info->max_blocks = sim ? (h->sim_costs_ok ? h->sim_max_blocks : 0) : h->max_blocks;
   info->scratch_bytes = h->scratch_gen_bytes + h->scratch_fb_bytes + h->retry_cap * (h->sim_ok ? 16 : 8) +
-                        h->sel_rows * (4 * h->stride + 16);
+                        h->sel_rows * (4 * h->stride + 16) + h->gr_mem_bytes;
   info->pool_slots = v >= 8 ? h->pool_slots : 0;
   info->check_kernel = v >= 8 ? check_kind(h) : 0;
   info->greedy_inbox = h->gr_ok ? (h->gr_direct ? -1 : h->gr_K) : 0;
   info->greedy_lds_bytes = h->gr_ok ? int32_t(h->gr_dense.lds) : 0;
-  info->greedy_retry_ring_bytes = h->gr_ok ? h->gr_ring_bytes : 0;
+  info->greedy_retry_ring_bytes = h->gr_ok && !h->gr_lds_whole ? h->gr_mem_bytes : 0;
   return DIP_OK;
 }
 

@@ -77,27 +77,6 @@ bool greedy_plan(dip_sim *h) {
   return h->gr_dense.blocks_per_cu > 0 || h->gr_wide.blocks_per_cu > 0;
 }
 
-// Device memory of the rings (and joins) for `slots` resident candidates
-static int ensure_greedy_slots(dip_sim *h, int64_t slots, bool joins) {
-  const int64_t rings = slots * h->P * 2 * int64_t(h->gr_kg) * 8;
-  if (rings > h->gr_ring_bytes) {
-    if (h->d_gr_ring) DIP_HIP(hipFree(h->d_gr_ring));
-    h->d_gr_ring = nullptr;
-    h->gr_ring_bytes = 0;
-    DIP_HIP(hipMalloc(&h->d_gr_ring, size_t(rings)));
-    h->gr_ring_bytes = rings;
-  }
-  const int64_t jb = joins ? slots * int64_t(h->gr_J) * 8 : 0;
-  if (jb > h->gr_join_bytes) {
-    if (h->d_gr_joins) DIP_HIP(hipFree(h->d_gr_joins));
-    h->d_gr_joins = nullptr;
-    h->gr_join_bytes = 0;
-    DIP_HIP(hipMalloc(&h->d_gr_joins, size_t(jb)));
-    h->gr_join_bytes = jb;
-  }
-  return DIP_OK;
-}
-
 // Resident candidate slots of a launch shape: what the CUs hold, within 1 GiB
 // of rings.
 static int64_t greedy_slots(const dip_sim *h, bool wide) {
@@ -107,6 +86,35 @@ static int64_t greedy_slots(const dip_sim *h, bool wide) {
   const int64_t blocks = std::max<int64_t>(
       1, std::min<int64_t>(int64_t(h->n_cu) * L.blocks_per_cu, (int64_t(1) << 30) / per));
   return L.blocks_per_cu > 0 ? blocks * gw : 0;
+}
+
+// Device memory of the rings (and joins) for the resident candidates of either
+// shape, fewer of them where memory is short (down to a wave's).  Allocated
+// with the grouping and kept with it: no call allocates, and a shape that holds
+// more candidates (smaller inboxes) stays within these slots.
+static int alloc_greedy_slots(dip_sim *h) {
+  const int64_t gw = kWave >> h->gr_rwl;
+  const int64_t per = h->P * 2 * int64_t(h->gr_kg) * 8;
+  const bool joins = h->gr_dense.joins_dev || h->gr_wide.joins_dev;
+  const int64_t jper = joins ? int64_t(h->gr_J) * 8 : 0;
+  for (int64_t slots = std::max(greedy_slots(h, true), greedy_slots(h, false));; slots /= 2) {
+    slots = std::max(slots, gw);
+    const hipError_t e = hipMalloc(&h->d_gr_ring, size_t(slots * per));
+    const hipError_t e2 = e == hipSuccess && jper ? hipMalloc(&h->d_gr_joins, size_t(slots * jper)) : e;
+    if (e2 == hipSuccess) {
+      h->gr_slots = slots;
+      h->gr_mem_bytes = slots * (per + jper);
+      return DIP_OK;
+    }
+    (void)hipGetLastError();
+    if (e == hipSuccess) (void)hipFree(h->d_gr_ring);
+    h->d_gr_ring = nullptr;
+    h->d_gr_joins = nullptr;
+    if (slots == gw) {
+      g_last_hip = e2;
+      return DIP_E_HIP;
+    }
+  }
 }
 
 }  // namespace dipsim_host
@@ -199,12 +207,13 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
     for (int32_t g = 0; g < N; ++g) most = std::max(most, ++per[2 * h->rank_of[g] + h->kind[g]]);
   }
   h->gr_kg = most;
-  // device rings at once where a whole rank's inboxes could not sit in LDS
-  // (they will be used), else with the first call
+  // whether a whole rank's inboxes would fit in LDS (the rings in device memory
+  // are then seldom used)
   int kr = 1;
   while (kr < most) kr *= 2;
-  bool lds_whole = false;
-  for (int w = h->gr_rwl; w <= 6 && !lds_whole; ++w) lds_whole = greedy_inbox_fits(h, kr, w);
+  h->gr_lds_whole = false;
+  for (int w = h->gr_rwl; w <= 6 && !h->gr_lds_whole; ++w)
+    h->gr_lds_whole = greedy_inbox_fits(h, kr, w);
 
   auto fail = [&](hipError_t e) {
     g_last_hip = e;
@@ -225,13 +234,10 @@ int dip_sim_configure_greedy(dip_sim *h, int32_t n_groups, const int32_t *op_gro
   if ((e = hipMalloc(&h->d_gr_spills, 16)) != hipSuccess) return fail(e);
   if ((e = launch_zero_words(h->d_gr_spills, 1, nullptr)) != hipSuccess) return fail(e);
   if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return fail(e);
-  if (!lds_whole) {
-    const int rc = ensure_greedy_slots(h, int64_t(h->n_cu), false);
-    if (rc != DIP_OK) {
-      release_greedy(h);
-      return rc;
-    }
-  }
+  if ((e = hipHostMalloc(reinterpret_cast<void **>(&h->h_gr_seen), 16, hipHostMallocDefault)) != hipSuccess)
+    return fail(e);
+  if ((e = hipEventCreateWithFlags(&h->gr_seen_ev, hipEventDisableTiming)) != hipSuccess) return fail(e);
+  if (alloc_greedy_slots(h) != DIP_OK) return fail(g_last_hip);
   h->gr_ok = true;
   h->gr_costs_ok = false;
   return DIP_OK;
@@ -287,17 +293,12 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
   }
   // a wave per candidate while every one is resident at once and the SIMDs
   // hold at most two waves each; else 64 >> rwl candidates a wave
-  const int64_t slots_w = greedy_slots(h, true), slots_d = greedy_slots(h, false);
+  const int64_t slots_w = std::min(greedy_slots(h, true), h->gr_slots);
+  const int64_t slots_d = std::min(greedy_slots(h, false), h->gr_slots);
   const bool wide = slots_d == 0 || (n_cand <= slots_w && n_cand <= 8 * int64_t(h->n_cu));
   const dip_sim::GrLaunch &L = wide ? h->gr_wide : h->gr_dense;
   const int64_t gw = wide ? 1 : kWave >> h->gr_rwl;
   const int64_t blocks = std::min<int64_t>((n_cand + gw - 1) / gw, (wide ? slots_w : slots_d) / gw);
-  {
-    // (and what any smaller batch would take, so that it allocates nothing)
-    const int64_t need = std::max(blocks * gw, std::min<int64_t>(n_cand, slots_w));
-    const int rc = ensure_greedy_slots(h, need, L.joins_dev);
-    if (rc != DIP_OK) return rc;
-  }
   (void)hipGetLastError();
   h->prof_n = 0;
   auto mark = [&](int i) -> hipError_t {
@@ -346,10 +347,6 @@ int dip_sim_greedy(dip_sim *h, const dip_costs *costs, const int32_t *prio, int6
   if (a.spill_count) {
     h->gr_unseen_n += n_cand;
     if (!h->gr_seen_pending) {
-      if (!h->h_gr_seen) {
-        DIP_HIP(hipHostMalloc(reinterpret_cast<void **>(&h->h_gr_seen), 16, hipHostMallocDefault));
-        DIP_HIP(hipEventCreateWithFlags(&h->gr_seen_ev, hipEventDisableTiming));
-      }
       DIP_HIP(hipMemcpyAsync(h->h_gr_seen, h->d_gr_spills, 4, hipMemcpyDeviceToHost, stream));
       DIP_HIP(hipEventRecord(h->gr_seen_ev, stream));
       h->gr_seen_pending = true;

@@ -239,10 +239,11 @@ struct dip_sim {
     int64_t lds = 0;
   } gr_dense, gr_wide;                 // 64 >> rwl candidates a wave; one
   int32_t gr_kg = 1;                   // device ring entries per rank and kind
+  bool gr_lds_whole = false;           // a whole rank's inboxes would fit in LDS
+  int64_t gr_slots = 0;                // candidate slots the device memory below has
   uint64_t *d_gr_ring = nullptr;       // rings beyond LDS, per resident candidate slot
-  int64_t gr_ring_bytes = 0;
   uint32_t *d_gr_joins = nullptr;
-  int64_t gr_join_bytes = 0;
+  int64_t gr_mem_bytes = 0;
   // MCTS rollouts (dip_sim_configure_rollouts / dip_sim_rollouts)
   bool rl_ok = false;
   int32_t rl_n = 0;                    // classes
