@@ -577,7 +577,9 @@ static void alloc_selected(dip_sim *h) {
     if (hipMalloc(&h->d_sel_x, size_t(rows) * size_t(h->stride) * 4) == hipSuccess &&
         hipMalloc(&h->d_sel_list, size_t(rows) * 16) == hipSuccess &&
         hipMalloc(&h->d_sel_count, kRetryCounters * 4) == hipSuccess &&
-        hipEventCreateWithFlags(&h->sel_ev, hipEventDisableTiming) == hipSuccess) {
+        // (it orders streams of one device: no system-wide fence, 1 us a call)
+        hipEventCreateWithFlags(&h->sel_ev, hipEventDisableTiming | hipEventDisableSystemFence) ==
+            hipSuccess) {
       h->sel_rows = rows;
       return;
     }
@@ -922,6 +924,25 @@ static bool capturing(hipStream_t stream) {
   return true;
 }
 
+// Whether the general kernel is the faster one for a batch: candidates of few
+// ops, where its one launch takes about 1.2 us per op and pipeline step
+// (busiest rank's ops + 2 P of them), three launches 12 us and 0.4 us a step,
+// and the selection check 0.45 ns per schedule and rank whatever its ops, most
+// lanes of a rank's wave being idle.  Past 32 ops a rank (48 of few in all) and
+// for many ranks of several ops the general kernel falls behind again once its
+// lanes are full.  us, general against simulation: 4 ranks of 16 ops, 4,000
+// schedules 33 and 30, 8,000 33 and 40, 100,000 64 and 290; one rank of 2 ops,
+// 300,000 8 and 259; 8 ranks of 32 ops, 4,000 59 and 43, 16,000 64 and 89,
+// 64,000 231 and 374; 8 of 64, 64,000 786 and 480; 64 of 4, 4,000 196 and 180,
+// of 16, 4,000 329 and 293.
+static bool selected_general(const dip_sim *h, int64_t n_cand) {
+  const int64_t P = h->P;
+  int64_t nr = 0;
+  for (int32_t n : h->n_ops) nr = std::max<int64_t>(nr, n);
+  return h->forced_variant == 0 && nr <= (h->N <= 336 ? 48 : 32) && h->N * P <= 16384 &&
+         n_cand * P > 1400 * nr + 4000 * P - 20000;
+}
+
 int dip_sim_evaluate_selected(dip_sim *h, const int16_t *orders, const uint8_t *choice,
                               int64_t n_cand, int32_t *out_makespan, int32_t *out_bubble,
                               int32_t *out_peakmem, uint8_t *out_flags, void *stream) {
@@ -972,7 +993,8 @@ int dip_sim_evaluate_selected(dip_sim *h, const int16_t *orders, const uint8_t *
   // under capture: a graph's replays come at any time beside the calls that
   // share the working rows, and the general kernel needs none.
   (void)hipGetLastError();
-  if (h->sel_ok && h->variant == 9 && !capturing(static_cast<hipStream_t>(stream)))
+  if (h->sel_ok && h->variant == 9 && !selected_general(h, n_cand) &&
+      !capturing(static_cast<hipStream_t>(stream)))
     return evaluate_selected_sim(h, a, static_cast<hipStream_t>(stream));
   const GenBytes b = general_bytes(h, h->gen_variant);
   a.tab_bytes = uint32_t(b.tab);

@@ -52,6 +52,7 @@ def same(got, want, n=None):
 @pytest.mark.parametrize("P,M,n", [(2, 2, 65536 + 1), (2, 2, 2 * 65536 + 77), (3, 2, 70001)])
 def test_batches_beyond_the_rows(P, M, n):
     sim, orders, choice, want = setup(P, M, n)
+    assert sim.configure(9) == dip.OK              # (chosen by itself, the general kernel runs)
     for _ in range(2):
         out = sim.outputs(n, DEV)
         dip.evaluate_selected(sim.h, orders, choice, n, *out)
