@@ -484,16 +484,11 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       int64_t per_block = int64_t(wpb) * h->G;
       int blocks = int(std::min<int64_t>((n_cand + per_block - 1) / per_block, max_blocks));
       if (n_cand <= int64_t(max_blocks) * per_block && h->forced_wpb == 0) {
-        // a batch within the resident groups spreads over the CUs; the waves
-        // of a block are what its share needs, and what copies the table in
-        // some eight steps
-        const int64_t tab = int64_t(h->sim_tab_vec) * 16;
-        const int64_t share = (n_cand + h->n_cu - 1) / h->n_cu;
-        const int w = int(std::min<int64_t>(wpb, std::max<int64_t>(share, (tab + 8191) / 8192)));
+        int w = wpb;
+        spread_shape(h, n_cand, int64_t(h->sim_tab_vec) * 16, &w, &blocks);
         lds -= int64_t(wpb - w) * h->G * sim_group_bytes(1 << h->pwl, slots);
         wpb = w;
         per_block = int64_t(w) * h->G;
-        blocks = int(std::min<int64_t>(n_cand, std::max<int64_t>(h->n_cu, (n_cand + per_block - 1) / per_block)));
         a.spread = 1;
       }
       a.wpb = wpb;

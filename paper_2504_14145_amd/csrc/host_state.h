@@ -322,6 +322,7 @@ bool sim_shape(dip_sim *h, int slots, int forced_wpb, int *wpb, int *max_blocks,
 int run_order_check(dip_sim *h, const int16_t *orders, int64_t n_cand, int32_t *out_ms,
                     int32_t *out_bub, uint8_t *out_flags, hipStream_t stream);
 int sim_plan(dip_sim *h);
+void spread_shape(const dip_sim *h, int64_t n_cand, int64_t tab, int *wpb, int *blocks);
 bool direct_shape(dip_sim *h, bool sel);
 // resident candidates of the direct kernel, 0 where it does not run the
 // current costs
