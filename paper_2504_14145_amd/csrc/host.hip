@@ -380,6 +380,28 @@ struct CallScratch {
   int64_t *list_b;    // [n_cand] second pass retries (variant 9)
 };
 
+// Rank counts that are no power of two: whether the pool kernel is the faster
+// first pass.  The simulation kernel keeps its tables in LDS and its rounds
+// work on the group's idle lanes too; candidates of few ops gain little from
+// that once their groups take several candidates in turn.  us with the pool
+// kernel and with the simulation kernel: 12 ranks of 32 ops, 10,000 candidates
+// 59 and 46 (direct), 40,000 134 and 172, 150,000 855 and 652 (its counter
+// serves four candidates a group and more one by one, of groups of up to 16
+// lanes above all); 20 of 16, 20,000 119 and 153, 300,000 1,610 and 1,790; 20
+// of 64, 10,000 266 and 181; 33 of 16, 10,000 144 and 172, 20,000 277 and 293.
+// And where the tables leave room for so few groups that a batch fits the pool
+// kernel's and not these: 33 of 256 ops, 5,000 345 and 473.
+bool pool_first(const dip_sim *h, int64_t n_cand) {
+  if (h->forced_variant != 0 || h->forced_pool_slots != 0 || (h->P & (h->P - 1)) == 0) return false;
+  const int64_t pool = int64_t(h->max_blocks) * h->wpb * h->G;
+  const int64_t sim = int64_t(h->sim_max_blocks) * h->sim_wpb * h->G;
+  if (n_cand <= sim) return false;
+  if (n_cand <= pool && 5 * pool > 6 * sim) return true;
+  if (h->P <= 16) return h->N <= 800 && n_cand < 4 * pool;
+  if (h->P <= 32) return h->N <= 640;
+  return h->N <= 1600 && 10 * n_cand < 17 * pool;
+}
+
 int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int64_t n_cand,
                   int32_t *out_makespan, int32_t *out_bubble, int32_t *out_peakmem,
                   uint8_t *out_flags, void *stream_, const CallScratch *sx) {
@@ -448,7 +470,7 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       for (int i = 2; i <= 5; ++i) DIP_HIP(mark(i));
       return DIP_OK;
     }
-    if (h->variant == 9 && h->sim_costs_ok) {
+    if (h->variant == 9 && h->sim_costs_ok && !pool_first(h, n_cand)) {
       SimArgs a{};
       a.orders = orders;
       a.n_cand = n_cand;
@@ -565,7 +587,7 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       DIP_HIP(mark(h->prof_n));
       return DIP_OK;
     }
-    if (last_slots > 0 && direct_slots(h, false) > 0) {
+    if ((last_slots > 0 || h->forced_variant == 0) && direct_slots(h, false) > 0) {
       rc = run_direct(h, false, orders, n_cand, nullptr, out_makespan, out_bubble, out_flags,
                       nullptr, retry_list, retry_count, stream);
       if (rc != DIP_OK) return rc;
