@@ -175,7 +175,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void cost_table_reg_kernel(
   ConstDouble *nm = reinterpret_cast<ConstDouble *>(reinterpret_cast<uintptr_t>(t.n_mem));
   ConstDouble *nn = reinterpret_cast<ConstDouble *>(reinterpret_cast<uintptr_t>(t.n_net));
   const uint32_t k0 = uint32_t(kaddr & 3);
-  const int32_t n_chunks = (t.n_items + CH - 1) / CH;
+  const int32_t n_chunks = (t.n_items - 1) / CH + 1;    // (up to 2^31 - 1 items)
   // whether a chunk's entries of a configuration are one aligned vector
   const bool vec = CH == 4 && t.n_items % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
   for (;;) {
