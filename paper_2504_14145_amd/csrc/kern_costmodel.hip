@@ -285,13 +285,21 @@ extern "C" int dip_cost_tables(const dip_op_table *t, int64_t n_configs, const d
   const int64_t gy = (n_configs + kConfigsPerBlock - 1) / kConfigsPerBlock;
   if (gx > INT32_MAX || gy > 65535) return DIP_E_INVAL;
   const dim3 grid{unsigned(gx), unsigned(gy), 1u};
-  if (t->n_kinds <= kRegKinds) {
+  // one or two items are a single wave's serial chain, which is shorter with the
+  // coefficients in LDS than through the scalar branches (one item of 300 rows
+  // and 5 kinds: 21 us against 44 with four configurations a lane, 20 and 33
+  // with one; two items 37 and 46, 36 and 33)
+  const bool few = t->n_items == 1 ? t->n_kinds >= 3 || n_configs > 256
+                                   : t->n_items == 2 && t->n_kinds >= 3 && n_configs > 256;
+  if (t->n_kinds <= kRegKinds && !few) {
     // four configurations a lane from 257 up (two waves a SIMD; 4,000 of them
     // take 172 us, at two a lane 209), two from 65 (four waves; 100 of them
-    // 39 us, at four a lane 49), else one; the blocks that are resident at once, so that each
-    // brings its coefficients in once, and items by fours where every wave
-    // still gets several chunks
-    const int cpl = n_configs > 256 ? 4 : n_configs > 64 ? 2 : 1;
+    // 39 us, at four a lane 49), else one; two at most from seven kinds on,
+    // where four configurations' coefficients leave one wave a SIMD (8 kinds,
+    // 1,280 items of 70 rows, 1,000: 86 us, at two a lane 65); the blocks that
+    // are resident at once, so that each brings its coefficients in once, and
+    // items by fours where every wave still gets several chunks
+    const int cpl = n_configs > 256 && t->n_kinds <= 6 ? 4 : n_configs > 64 ? 2 : 1;
     const int64_t ry = (n_configs + 64 * cpl - 1) / (64 * cpl);
     if (ry <= 65535) {
       const int64_t resident = cpl == 4 ? 512 : 1024;
