@@ -28,8 +28,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "dip_sim.h"

@@ -118,30 +118,39 @@ static bool table_image(const dip_sim *h, const dip_costs *c, const int32_t *bus
   // pages: each rank's records in runs of kSimPage local ids, equal runs once
   bool paged = false;
   if (direct > kSimDirectMax) {
-    std::unordered_map<std::string, int32_t> seen;
-    std::vector<uint32_t> pages;
+    // each page is put after the ones kept, looked up by a hash of its words in
+    // a table of their numbers, and dropped again when an equal one is there
+    constexpr size_t kWords = size_t(kSimPage) * 2;
+    size_t most = 0, slots = 1;
+    for (int r = 0; r < P; ++r) most += size_t(h->n_ops[r] + kSimPage - 1) / kSimPage;
+    while (slots < 2 * most) slots *= 2;
+    std::vector<int32_t> seen(slots, -1);
+    std::vector<uint32_t> pages(most * kWords, 0u);
+    int32_t n_pages = 0;
+    pmap.reserve(most);
     bool ok = true;
     for (int r = 0; r < P && ok; ++r) {
       recb[r] = int32_t(pmap.size());
       for (int32_t p0 = 0; p0 < h->n_ops[r]; p0 += kSimPage) {
-        std::string key(size_t(kSimPage) * 8, '\0');
-        const int32_t n = std::min(kSimPage, h->n_ops[r] - p0);
-        std::memcpy(&key[0], &rec[2 * size_t(h->rank_off[r] + p0)], size_t(n) * 8);
-        auto it = seen.find(key);
-        int32_t id;
-        if (it == seen.end()) {
-          id = int32_t(seen.size());
-          seen.emplace(key, id);
-          const size_t at = pages.size();
-          pages.resize(at + size_t(kSimPage) * 2);
-          std::memcpy(&pages[at], key.data(), key.size());
-        } else {
-          id = it->second;
+        uint32_t *page = &pages[size_t(n_pages) * kWords];
+        const size_t n = size_t(std::min(kSimPage, h->n_ops[r] - p0)) * 2;
+        std::copy_n(&rec[2 * size_t(h->rank_off[r] + p0)], n, page);
+        std::fill(page + n, page + kWords, 0u);
+        uint64_t hash = 0;
+        for (size_t i = 0; i < kWords; i += 2) {
+          hash = (hash ^ (page[i] | (uint64_t(page[i + 1]) << 32))) * 0x9E3779B97F4A7C15ull;
+          hash ^= hash >> 32;
         }
+        size_t s = size_t(hash) & (slots - 1);
+        while (seen[s] >= 0 && !std::equal(page, page + kWords, &pages[size_t(seen[s]) * kWords]))
+          s = (s + 1) & (slots - 1);
+        if (seen[s] < 0) seen[s] = n_pages++;
+        const int32_t id = seen[s];
         if (id >= kSimMaxPages) ok = false;
         pmap.push_back(uint16_t(id * kSimPage));
       }
     }
+    pages.resize(size_t(n_pages) * kWords);
     const int64_t pbytes = int64_t(pages.size()) * 4;
     if (ok && pbytes + align16(int64_t(pmap.size()) * 2) < direct) {
       paged = true;
