@@ -465,7 +465,7 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
     // the pools 117; twice the resident ones, 126 both)
     if (h->forced_variant == 0 && h->forced_pool_slots == 0 && n_cand <= direct_slots(h, false)) {
       rc = run_direct(h, false, orders, n_cand, nullptr, out_makespan, out_bubble, out_flags,
-                      counts + 1, nullptr, nullptr, stream);
+                      nullptr, nullptr, stream);
       if (rc != DIP_OK) return rc;
       for (int i = 2; i <= 5; ++i) DIP_HIP(mark(i));
       return DIP_OK;
@@ -589,7 +589,7 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
     }
     if ((last_slots > 0 || h->forced_variant == 0) && direct_slots(h, false) > 0) {
       rc = run_direct(h, false, orders, n_cand, nullptr, out_makespan, out_bubble, out_flags,
-                      nullptr, retry_list, retry_count, stream);
+                      retry_list, retry_count, stream);
       if (rc != DIP_OK) return rc;
       DIP_HIP(mark(h->prof_n));
       return DIP_OK;

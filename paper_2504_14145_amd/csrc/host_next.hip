@@ -834,8 +834,8 @@ static int launch_selected(dip_sim *h, const GeneralArgs &all, hipStream_t strea
     }
     const int64_t direct = direct_slots(h, true);
     if (n <= direct) {
-      const int rc = run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, h->d_sel_count + 1,
-                                nullptr, nullptr, stream);
+      const int rc =
+          run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, nullptr, nullptr, stream);
       if (rc != DIP_OK) return rc;
       continue;
     }
@@ -868,8 +868,8 @@ static int launch_selected(dip_sim *h, const GeneralArgs &all, hipStream_t strea
     if (direct > 0) {
       // (selections come with orders of many live items: under a binding cap
       // on 16 x 2 lanes every one of them fills 32 slots too)
-      const int rc = run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, nullptr,
-                                h->d_sel_list, h->d_sel_count, stream);
+      const int rc = run_direct(h, true, orders, n, h->d_sel_x, ms, bub, flags, h->d_sel_list,
+                                h->d_sel_count, stream);
       if (rc != DIP_OK) return rc;
       continue;
     }

@@ -519,8 +519,8 @@ int64_t direct_slots(const dip_sim *h, bool sel) {
 }
 
 int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, const int32_t *xcost,
-               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, uint32_t *next_cand,
-               const int64_t *list, const uint32_t *list_count, hipStream_t stream) {
+               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, const int64_t *list,
+               const uint32_t *list_count, hipStream_t stream) {
   DirectArgs a{};
   a.list = list;
   a.list_count = list_count;
@@ -540,13 +540,10 @@ int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, cons
   a.end_vec = a.off_ring / 16;
   a.P = h->P;
   a.xcost = xcost;
-  a.next_cand = next_cand;
   const int64_t tab = int64_t(h->dir_tab_vec) * 16;
   int wpb = h->dir_wpb[sel], blocks = h->dir_max_blocks[sel];
   if (n_cand <= int64_t(blocks) * wpb * h->G) spread_shape(h, n_cand, tab, &wpb, &blocks);
   a.wpb = wpb;
-  const int64_t slots = int64_t(blocks) * wpb * h->G;
-  a.static_end = !list && n_cand >= 4 * slots ? slots * ((n_cand / 10 * 9) / slots) : INT64_MAX;
   const int64_t lds = tab + int64_t(wpb) * h->G * int64_t(a.group_bytes);
   DIP_HIP(launch_direct(h->pwl, h->dir_paged, sel, int(blocks), wpb, size_t(lds), stream, a));
   return DIP_OK;

@@ -325,10 +325,11 @@ bool direct_shape(dip_sim *h, bool sel);
 // resident candidates of the direct kernel, 0 where it does not run the
 // current costs
 int64_t direct_slots(const dip_sim *h, bool sel);
-// its launch on n candidates, or on a list of at most n; their check has run
+// its launch on n candidates (at most direct_slots), or on a list of at most n;
+// their check has run
 int run_direct(dip_sim *h, bool sel, const int16_t *orders, int64_t n_cand, const int32_t *xcost,
-               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, uint32_t *next_cand,
-               const int64_t *list, const uint32_t *list_count, hipStream_t stream);
+               int32_t *out_ms, int32_t *out_bub, uint8_t *out_flags, const int64_t *list,
+               const uint32_t *list_count, hipStream_t stream);
 int choose_config(dip_sim *h);
 int64_t sim_tab_bound(const dip_sim *h);
 StageLayout stage_layout(const dip_sim *h);

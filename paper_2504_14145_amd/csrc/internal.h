@@ -369,10 +369,8 @@ struct DirectArgs {
   const int32_t *lane_info;  // [P][4] {first global op, ops, busy time, record base}
   uint32_t group_bytes, off_ring, end_vec;   // end_vec: 16-byte units of the end times
   int32_t P, wpb;
-  uint32_t *next_cand;       // candidates handed out on demand, past static_end
-  int64_t static_end;        // (a multiple of the resident groups, or INT64_MAX)
   const int32_t *xcost;      // as SimArgs::xcost
-  const int64_t *list;       // list mode, as SimArgs
+  const int64_t *list;       // list mode, as SimArgs; a batch fits the resident groups
   const uint32_t *list_count;
 };
 const void *direct_kernel_ptr(int pwl, bool paged, bool sel);

@@ -175,22 +175,13 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectArgs a) {
     if (c.x >= (kSimHasPred | kSimMulti)) ce = lds32(a.off_extra + 4u * c.y);   // several predecessors
   };
 
-  auto next_k = [&]() -> int64_t {
-    const int64_t succ = k + n_slots;
-    if (succ < a.static_end) return succ;
-    uint32_t q = 0;
-    if (r == 0) q = atomicAdd(a.next_cand, 1u);
-    q = uint32_t(__shfl(int(q), gbit, kWave));
-    return a.static_end + int64_t(q);
-  };
-
   // The lanes of one group call this together (a group without a candidate
   // keeps its lanes out of m_live).
   auto start_candidate = [&]() {
     // (candidates whose verdict the check kernel already settled: not a
     // permutation, or an op ordered before its own-rank predecessor)
     while (k < n_todo && (a.out_flags[cand_at(k)] & (DIP_FLAG_INVALID | DIP_FLAG_DEADLOCK)))
-      k = next_k();
+      k += n_slots;
     has = k < n_todo;
     if (!has) return;
     for (uint32_t i = uint32_t(r); i < a.end_vec; i += PW)
@@ -311,7 +302,7 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectArgs a) {
           if (stalled) a.out_flags[cand] = uint8_t(fl | DIP_FLAG_DEADLOCK);
         }
       }
-      k = next_k();
+      k += n_slots;
       start_candidate();
     }
     // the restarted groups' lanes: live and edge state from their new records
