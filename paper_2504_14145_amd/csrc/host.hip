@@ -488,21 +488,10 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       a.retry = sx->list_a;
       a.retry_count = counts;
       a.round_limit = round_limit;
-      // The first pass's shape.  A rank that publishes at most S end times
-      // never fills a pool of S slots: where 16 slots are that many and the
-      // batch fits the groups resident with them, they run at once, since
-      // nothing is left for the later passes then (1,024 candidates of 16 ops
-      // a rank: six launches instead of three, 39 against 25 us with the
-      // argmin).
-      int slots = h->pool_slots, wpb = h->sim_wpb, max_blocks = h->sim_max_blocks;
+      const int slots = h->pool_slots;
+      int wpb = h->sim_wpb;
+      const int max_blocks = h->sim_max_blocks;
       int64_t lds = h->sim_lds;
-      if (h->forced_pool_slots == 0 && slots < 16 && h->sim2_ok && h->sim_max_pub > slots &&
-          h->sim_max_pub <= 16 && n_cand <= int64_t(h->sim2_max_blocks) * h->sim2_wpb * h->G) {
-        slots = 16;
-        wpb = h->sim2_wpb;
-        max_blocks = h->sim2_max_blocks;
-        lds = h->sim2_lds;
-      }
       int64_t per_block = int64_t(wpb) * h->G;
       int blocks = int(std::min<int64_t>((n_cand + per_block - 1) / per_block, max_blocks));
       if (n_cand <= int64_t(max_blocks) * per_block && h->forced_wpb == 0) {
