@@ -70,7 +70,8 @@ GREEDY_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "greedy_kernel_traffic.md")
 SIM_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sim_kernel_traffic.md")
 CSRC = os.path.join(ROOT, "paper_2504_14145_amd", "csrc")
 POOL_SOURCES = [os.path.join(CSRC, f) for f in ("kern_pool.hip", "internal.h", "dev_util.h")]
-SIM_SOURCES = [os.path.join(CSRC, f) for f in ("kern_sim.hip", "internal.h", "dev_util.h")]
+SIM_SOURCES = [os.path.join(CSRC, f) for f in
+               ("kern_sim.hip", "lds_util.h", "internal.h", "dev_util.h")]
 GREEDY_SOURCES = [os.path.join(CSRC, f) for f in ("kern_greedy.hip", "internal.h", "dev_util.h")]
 MEMOPT_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "memopt_wave_kernel_traffic.md")
 MEMOPT_SOURCES = [os.path.join(CSRC, f) for f in ("kern_memopt.hip", "internal.h", "dev_util.h")]
