@@ -73,7 +73,7 @@ POOL_SOURCES = [os.path.join(CSRC, f) for f in ("kern_pool.hip", "internal.h", "
 SIM_SOURCES = [os.path.join(CSRC, f) for f in
                ("kern_sim.hip", "lds_util.h", "internal.h", "dev_util.h")]
 GREEDY_SOURCES = [os.path.join(CSRC, f) for f in ("kern_greedy.hip", "internal.h", "dev_util.h")]
-MEMOPT_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "memopt_wave_kernel_traffic.md")
+MEMOPT_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "memopt_group_kernel_traffic.md")
 MEMOPT_SOURCES = [os.path.join(CSRC, f) for f in ("kern_memopt.hip", "internal.h", "dev_util.h")]
 COST_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cost_table_kernel_traffic.md")
 COST_SOURCES = [os.path.join(CSRC, "kern_costmodel.hip"), os.path.join(ROOT, "include", "dip_sim.h")]
@@ -288,7 +288,7 @@ def main():
     ap.add_argument("--check", type=int, default=0,
                     help="check kernel (dip_sim_configure_check mode; 0: automatic)")
     ap.add_argument("--inbox", type=int, default=0,
-                    help="greedy: fix the first launch's inbox entries per kind (0: adaptive)")
+                    help="greedy: fix the inbox size per rank and kind (0: adaptive)")
     ap.add_argument("--cpu-seconds", type=float, default=6.0,
                     help="wall-time bound of each CPU oracle baseline leg (all cores, one core)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -540,7 +540,7 @@ def main():
         "kernel_us": {n: t * 1e3 for n, t in zip(names, kern_avg_ms)},
         "kernel_variant": info["variant"],
         # candidates whose pools filled in the first simulation pass, and
-        # those the second pass (16 slots) handed to the general kernel
+        # those the passes with 16 and 32 slots left to the last kernel
         "retries": {"first_pass": retries[0], "second_pass": retries[1]},
         "pool_slots": slots,
         "best": {"index": best[0], "makespan_us": best[1]},
@@ -629,7 +629,7 @@ def run_greedy(args, cfg):
     dip.profile(sim.h, False)
     nk = min(len(p) for p in per_kernel)
     kern_avg_ms = [sum(p[i] for p in per_kernel) / len(per_kernel) for i in range(nk)]
-    names = ["greedy", "greedy_retry"][:nk]
+    names = ["greedy"][:nk]
     info = sim.info
     log(f"[bench] {args.steps} steps in {wall * 1e3:.2f} ms; per-kernel avg ms: " +
         ", ".join(f"{n} {t:.4f}" for n, t in zip(names, kern_avg_ms)) +
@@ -992,7 +992,7 @@ def run_mcts(args, cfg):
                    "parallelism": "single GPU"},
         "batch_ms": batch_ms,
         "greedy_inbox": inbox,
-        "kernel_us": {n: t * 1e3 for n, t in zip(["greedy", "greedy_retry"], k_ms)},
+        "kernel_us": {n: t * 1e3 for n, t in zip(["greedy"], k_ms)},
         "search": {"rounds": iters, "workers": args.workers, "rollouts_each": search.leaves * R,
                    "mcts_best_makespan_us": mcts_best, "random_best_makespan_us": best_rand},
         "roofline": {"bound": "hbm", "kernel": "greedy",

@@ -112,7 +112,9 @@ typedef struct {
   const int32_t *slot_act;   /* [n_slots] memory units, >= 0                    */
 } dip_costs;
 
-/* Reported shape of a handle (what dip_sim_create chose). */
+/* Reported shape of a handle (what dip_sim_create chose).  Variant 9 reports the
+ * simulation kernel's first pass; smaller batches take fewer waves per block,
+ * and the direct kernel has a shape of its own. */
 typedef struct {
   int32_t n_ranks;
   int32_t n_ops_total;       /* N */
@@ -147,8 +149,9 @@ int dip_sim_check_costs(const dip_topology *topo, const dip_costs *costs);
  * kernel variant for this device.  On success *out owns device memory. */
 int dip_sim_create(const dip_topology *topo, dip_sim **out);
 
-/* Force a kernel variant (0 = automatic choice) and waves per block
- * (0 = automatic; 1, 2, 4 or 8, and 16 for variant 9).  DIP_E_UNSUPPORTED if
+/* Force a kernel variant (0 = automatic choice) and its waves per block
+ * (0 = automatic; 1, 2, 4 or 8, and 16 for variant 9; they have no effect on an
+ * automatic choice).  DIP_E_UNSUPPORTED if
  * the variant does not fit the device or the topology.
  * General kernels (any dependence DAG): 1 tables, orders and end times in
  * LDS; 2 tables in global memory, orders and end times in LDS; 3 end times
@@ -161,18 +164,23 @@ int dip_sim_create(const dip_topology *topo, dip_sim **out);
  * and at most 8,192 ops per rank): the same check,
  * then the simulation kernel with compact op records and the pools in LDS,
  * a second pass of it with 16 slots per pool over the candidates whose pools
- * filled, a third with 32 slots, and a general kernel for those that filled
- * again.  Costs that do not fit its records (a cost of 2^20 or more, a
- * latency of 2^11 or more) run variant 8 for that call.  Otherwise a general
- * kernel is chosen.
+ * filled, a third with 32 slots, and for those that filled again the direct
+ * kernel, which keeps every end time of a candidate in LDS, or a general kernel
+ * where they do not fit.  Chosen by itself, a batch whose candidates are all
+ * resident at once with the direct kernel runs on it alone, and on rank counts
+ * that are no power of two variant 8's pool kernel makes the first pass of the
+ * batches that it is faster for.  Costs that do not fit the records (a cost of
+ * 2^20 or more, a latency of 2^11 or more) run variant 8 for that call.
+ * Otherwise a general kernel is chosen.
  * Results are the same whichever kernel runs. */
 int dip_sim_configure(dip_sim *h, int32_t variant, int32_t waves_per_block);
 
 /* Variants 8 and 9: end-time slots per rank pool, 4, 8 or 16 (0 = automatic:
  * 8), set at create time and by this call only, never by earlier calls.
  * Fewer slots keep more candidates resident; a candidate whose pools fill up
- * is re-simulated (variant 9: with 16 and then 32 slots, then by the general
- * kernel; variant 8: by the general kernel), so results never depend on it.
+ * is re-simulated (variant 9: with 16 and then 32 slots, then by the direct or
+ * a general kernel; variant 8: by a general kernel), so results never depend on
+ * it.  With a count other than 0 every batch goes through the pools.
  * DIP_E_UNSUPPORTED if the topology does not fit variant 8. */
 int dip_sim_configure_pool(dip_sim *h, int32_t slots_per_rank);
 
@@ -456,21 +464,23 @@ int dip_cost_tables(const dip_op_table *t, int64_t n_configs, const double *coef
  * later evaluate records HIP events on its stream around each kernel it
  * launches; dip_sim_last_profile then waits for the last of them and writes
  * the kernel times in milliseconds, in launch order, to out_ms[0 .. *n_out-1]
- * (out_ms must hold DIP_SIM_PROFILE_MAX floats; n_out <= 5: variant 8 launches the check, pool and retry kernels;
- * variant 9 the check kernel, the simulation kernel, its passes with 16-
- * and 32-slot pools over the candidates whose pools filled (a pass that
- * does not run reports about 0), and the retry kernel; variants 1-4 one
- * kernel; dip_sim_greedy records its two launches the same way).  *n_out = 0
- * if the last evaluate recorded nothing. */
+ * (out_ms must hold DIP_SIM_PROFILE_MAX floats; n_out <= 5: variant 8, and the
+ * pool kernel as a first pass, launch the check kernel, the pool kernel and the
+ * one for the candidates whose pools filled; variant 9 the check kernel, the
+ * simulation kernel, its passes with 16- and 32-slot pools over the candidates
+ * whose pools filled, and the kernel for those that they leave (what does not
+ * run reports about 0), or the check kernel and the direct kernel, in the
+ * simulation kernel's place; variants 1-4 one kernel; dip_sim_greedy records its
+ * one launch the same way).  *n_out = 0 if the last evaluate recorded nothing. */
 #define DIP_SIM_PROFILE_MAX 8
 int dip_sim_profile(dip_sim *h, int32_t enable);
 int dip_sim_last_profile(dip_sim *h, float *out_ms, int32_t *n_out);
 
 /* Diagnostics of the last evaluate (variants 8 and 9): *out_first = the
  * candidates whose pools filled in the first simulation pass; *out_second =
- * those left to the general kernel (variant 9: the ones its passes with 16-
- * and 32-slot pools could not finish either).  Waits for that call's
- * stream. */
+ * those left to the direct or the general kernel (variant 9: the ones its
+ * passes with 16- and 32-slot pools could not finish either).  Waits for that
+ * call's stream. */
 int dip_sim_last_retries(dip_sim *h, int64_t *out_first, int64_t *out_second);
 
 /* Release the handle's device memory.  Waits for the device first. */

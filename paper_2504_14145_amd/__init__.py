@@ -222,7 +222,7 @@ def last_profile(h) -> list:
 
 def last_retries(h) -> tuple:
     """(candidates whose pools filled in the first simulation pass, those left
-    to the general kernel) of the last evaluate; waits for its stream."""
+    to the direct or the general kernel) of the last evaluate; waits for its stream."""
     a, b = ctypes.c_int64(0), ctypes.c_int64(0)
     _check(load().dip_sim_last_retries(h, ctypes.byref(a), ctypes.byref(b)), "dip_sim_last_retries")
     return int(a.value), int(b.value)

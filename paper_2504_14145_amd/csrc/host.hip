@@ -511,8 +511,9 @@ int evaluate_impl(dip_sim *h, const dip_costs *costs, const int16_t *orders, int
       // per pool (deadlocked orders fill small pools too; larger ones tell
       // them from merely crowded ones), each pass in list mode over the
       // previous one's retries, the two lists taking turns; what the last
-      // pass leaves goes to the general kernel.  (A pass that does not run
-      // still records its event: the profile keeps one entry per pass.)
+      // pass leaves goes to the direct kernel, or to the general one where that
+      // does not fit.  (A pass that does not run still records its event: the
+      // profile keeps one entry per pass.)
       auto pass = [&](bool run, int slots, int wpb, int max_blocks, int64_t lds, int next) -> int {
         if (run) {
           int64_t *out = retry_list == sx->list_a ? sx->list_b : sx->list_a;

@@ -14,12 +14,15 @@
 //                 mode for candidates whose pools filled up;
 //   variant 9     as 8 with the simulation kernel of kern_sim.hip in place of
 //                 the pool kernel: compact op records resident in LDS and the
-//                 orders staged through per-lane LDS rings, then a second
-//                 pass with 16 pool slots before the general kernel.  It
-//                 needs at most 8192 ops per rank, and per call costs below
-//                 2^20 and latencies below 2^11
-//                 (checked whenever costs change; a call outside them runs
-//                 variant 8).
+//                 orders staged through per-lane LDS rings, then passes with
+//                 16 and 32 pool slots, then the direct kernel of
+//                 kern_direct.hip (every end time in LDS) or, where that does
+//                 not fit, the general kernel.  A batch within the direct
+//                 kernel's resident groups runs on it alone, and on rank counts
+//                 that are no power of two some batches take the pool kernel
+//                 first.  It needs at most 8192 ops per rank, and per call
+//                 costs below 2^20 and latencies below 2^11 (checked whenever
+//                 costs change; a call outside them runs variant 8).
 #pragma once
 
 #include <algorithm>
@@ -138,10 +141,10 @@ struct dip_sim {
   hipStream_t last_stream = nullptr;   // stream of the last evaluate (diagnostics)
   uint32_t *last_counts = nullptr;     // its retry counters
   void *d_static = nullptr;            // this device's address of the static scratch array
-  int last_general = 0;                // counter (index) of the list its general kernel took
+  int last_general = 0;                // counter (index) of the list its last kernel took
   int4 *d_pool_rec = nullptr;          // pool records [N][2]
   int2 *d_pool_edge = nullptr;         // pool edges [E]
-  int64_t *d_retry = nullptr;          // candidates re-run by the general kernel
+  int64_t *d_retry = nullptr;          // candidates whose pools filled
   uint32_t *d_retry_count = nullptr;   // [2] retry count, on-demand candidate counter
   int64_t retry_cap = 0;
   int check_blocks_per_cu = 1;

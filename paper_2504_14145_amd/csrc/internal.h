@@ -405,9 +405,8 @@ struct SelCheckArgs {
 hipError_t launch_selcheck(int waves, hipStream_t s, const SelCheckArgs &a);
 
 // ---------------------------------------------------------------- greedy
-// Dual-queue stage interleaving (see kern_greedy.hip).  Groups are numbered
-// internally forward groups first, then backward ones, each in the caller's
-// order; "position" is a group's rank among the groups of its kind under the
+// Dual-queue stage interleaving (see kern_greedy.hip).  Groups keep the caller's
+// numbers; a group's priority rank is its place among all groups under the
 // candidate's priorities.
 struct GreedyArgs {
   const int32_t *prio;      // [n_cand][G] priorities
@@ -454,10 +453,10 @@ hipError_t launch_greedy(int rwl, bool wide, int blocks, size_t lds, hipStream_t
 struct RolloutArgs {
   int64_t n;                 // rollouts (rows), all leaves
   int64_t per_leaf;          // rows per leaf: leaf l has rows l * per_leaf ...
-  int32_t *out_prio;         // [n][G] caller-indexed group priorities
+  int32_t *out_prio;         // [n][G] group priorities
   const int32_t *seqs;       // [leaves][n_classes]: the leaf's prefix, then the other classes ascending
   const int32_t *depths;     // [leaves] prefix lengths
-  const int32_t *group_class;// [G] caller-indexed
+  const int32_t *group_class;// [G]
   uint64_t seed, draw;       // leaf l draws with draw + l
   int32_t n_classes, G;
 };

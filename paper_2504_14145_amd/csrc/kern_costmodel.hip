@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void cost_table_kernel(dip_op_table t, int64_t
 // arithmetic) and takes every gridDim.x-th chunk of CH items, its waves one
 // chunk at a time, since items differ in length by two orders of magnitude.
 // Rows come through the scalar cache, eight at a time.
-// 16,384 configurations x 1,280 items (93,904 rows): 0.99 -> 0.55 ms; 16
+// 16,384 configurations x 1,280 items (93,904 rows): 0.99 -> 0.59 ms; 16
 // configurations of 1,360 items 127 -> 33 us.  The float64 instructions issue
 // every 4.8 cycles at best (0.28 ms of it here); the scalar branches, loads
 // and kind bytes of a row take the rest.

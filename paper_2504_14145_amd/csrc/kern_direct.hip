@@ -11,8 +11,9 @@
 // of the time (64 candidates: 8 ranks 72 -> 56 us, 16 x 2 lanes 207 -> 150, 32
 // ranks 329 -> 242).  The table costs 4 N bytes a candidate, so this kernel is
 // for batches whose candidates are all resident at once, and for the few that
-// filled the pools (list mode); the pools hold many more candidates of many
-// ops (65,536 on 16 x 2 lanes: 1.2 ms against 9.3 here).
+// filled the pools (list mode, a resident group taking several in turn); the
+// pools hold many more candidates of many ops (65,536 on 16 x 2 lanes: 1.2 ms
+// against 9.3 here).
 //
 // Records are those of the simulation kernel but for the edge word, which
 // holds the predecessor's global index relative to the op's own, so that its

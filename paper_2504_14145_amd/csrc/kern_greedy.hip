@@ -21,8 +21,9 @@
 // commits are these choices, or later stages of their ranks, which start no
 // earlier.  So every rank whose t_min lies below E keeps its choice whatever
 // the others do first, and all of them commit in the same round; the rank of
-// the least t_min always does.  On the workloads that is 2 to 5 commits a
-// round (11 on 64 equal ranks), with the sequential greedy's result.
+// the least t_min always does.  On the workloads that is 1.8 to 6.2 commits a
+// round (34,896 stages of 16 ranks in 19,258 rounds, 5,184 in 832; 11 on 64
+// equal ranks), with the sequential greedy's result.
 //
 // Mapping: lane = rank; a group of 2^GWL lanes per candidate.  GWL is the
 // rank count's power of two (64 >> GWL candidates side by side in a wave), or

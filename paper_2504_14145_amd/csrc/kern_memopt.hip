@@ -55,7 +55,7 @@
 //                       with a wave per problem, its loads summed over all
 //                       pairs, its search a candidate at a time and its
 //                       tables in device memory; 1,024 rollouts of 16 ranks
-//                       (128 and 196 pairs): 1.0 ms, 2.34.
+//                       (128 and 196 pairs): 1.23 ms, 2.34.
 //   memopt_kernel       a thread per (schedule, rank), for ranks of more
 //                       than 512 pairs (steps 1 and 2); its state sits in
 //                       LDS, element-major across the block.

@@ -35,8 +35,8 @@
 // round in which no lane of a group fired an op or read an item leaves its
 // state unchanged for good: if no lane was held by back-pressure, the orders
 // deadlock; otherwise the bounded pools may be what stalls it, and the
-// candidate is appended to a retry list that the unbounded general kernel
-// re-simulates.  The permutation check and the memory scan ran before, in the
+// candidate is appended to a retry list that a kernel without pools (the direct
+// or the general one) re-simulates.  The permutation check and the memory scan ran before, in the
 // check kernel, whose flags this kernel reads (invalid candidates are skipped)
 // and extends.
 #include "dip_sim.h"

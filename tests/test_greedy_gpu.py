@@ -113,8 +113,8 @@ def test_greedy_memory_caps(cap):
 
 def test_greedy_inbox_overflow_goes_through_retry():
     """A long transfer latency piles many future arrivals into one rank's
-    inbox: those candidates are finished by the second launch, and later
-    calls get larger inboxes."""
+    inbox: it goes on into device memory, and later calls get larger
+    inboxes."""
     need_gpu()
     prob, g, G, cls = _pipeline(2, 40, 10, comm=1000)
     prio = W.rollout_priorities(cls, 19, seed=2)
@@ -129,9 +129,9 @@ def test_greedy_inbox_overflow_goes_through_retry():
 
 def test_greedy_skips_first_launch_when_most_overflow():
     """On the large 16 x 64-lane workload most candidates overflow even the
-    largest inboxes that fit in LDS: after a few calls the inboxes stop
-    growing and later calls give every candidate to the second launch
-    (greedy_inbox -1), with results equal to the oracle's on every call."""
+    largest inboxes that fit in LDS: after a few calls the inboxes stop growing
+    and stay small, their rest in device memory (greedy_inbox -1), with results
+    equal to the oracle's on every call."""
     need_gpu()
     prob = W.make_problem(5)
     g, G, cls = W.priority_groups(prob)
@@ -150,10 +150,9 @@ def test_greedy_skips_first_launch_when_most_overflow():
 
 @pytest.mark.parametrize("cid", [2, 3, 4, 5])
 def test_greedy_second_launch_for_every_candidate(cid):
-    """Inboxes of one stage in the first launch: nearly every candidate
-    overflows and is simulated by the second launch, whose inboxes hold a
-    whole rank -- in LDS on configs 2 and 3, in device memory on configs 4
-    and 5 (594 and 1,413 groups per kind)."""
+    """The smallest inboxes: nearly every candidate's go on into device memory.
+    A rank's whole inboxes would fit in LDS on configs 2 and 3, not on 4 and 5
+    (594 and 1,413 groups per kind), which report the device memory."""
     need_gpu()
     prob = W.make_problem(cid)
     g, G, cls = W.priority_groups(prob)

@@ -91,7 +91,7 @@ def test_memopt_flags_invalid_orders():
 def test_memopt_ranks_with_many_pairs(frac):
     """Ranks of more than 512 stage pairs take the one-thread-per-rank kernel
     (no search: status 3 under a cap it meets); a rank of fewer takes the
-    wave kernel in the same problem family."""
+    kernel of lane groups in the same problem family."""
     need_gpu()
     for M in (520, 200):
         inst = W.pipeline_instance(2, M, np.arange(2 * M).reshape(2, M) % 9 + 2, comm=3, act=2)

@@ -1,7 +1,8 @@
 """The re-timed evaluate through the simulation kernel against the general
 kernel (any dependence graph) on the same schedules and choices: rank counts,
 random and invalid choices, deadlocked and invalid orders, caps, batches
-beyond the resident groups; and a sample against the simulator oracle."""
+within the direct kernel's resident groups; and a sample against the simulator
+oracle."""
 import numpy as np
 import pytest
 
